@@ -122,113 +122,259 @@ __device__ inline void tile_of(int64_t t, int nb, int &b1, int &b2)
 // has slot q1 at corner a and trial triangle slot q2 at corner b.  The
 // corners of each block are ranked in slot-major order (the order of the
 // block's slot lists, built on the host), so that the corners of a slot
-// form a run of consecutive ranks.  The sum separates over the two blocks
-// and runs in two stages, each a set of independent items spread over the
-// workgroup's threads:
-//   1. item (u, q2): P[rank1(u)][q2] = sum over the run of trial slot q2 of
-//      the staged row of test corner u = (t1, a);
-//   2. item (q1, q2): entry (q1, q2) = sum over the run of test slot q1 of
-//      the P rows, written to out[4 * e + op] (tile layout [entry][op]).
-// Both stages add in run order, i.e. in slot-list order.  Each item loads
-// the first 4 (then, for longer runs, 4 more) entries of its run at once;
-// the loads past a run's end fall in the padding or the next run and are
-// not added.  Staged entries: st[u * SROW + rank2(t2, b)].
-constexpr int SROW = 3 * BT + 1;    // staged row: one entry per trial corner (+1: distinct LDS banks per lane)
-constexpr int PROW = SMAX + 1;      // partial-sum row: one entry per trial slot (+1 likewise)
-constexpr int ST_LEN = 3 * BT * SROW + 8;
-constexpr int P_LEN = (3 * BT + 8) * PROW;
-constexpr int SLOT_IT1 = (3 * BT * SMAX + 255) / 256;   // stage-1 items per thread
-constexpr int SLOT_IT2 = (SMAX * SMAX + 255) / 256;     // stage-2 items per thread
+// form a run of consecutive ranks.  The sum separates over the two blocks:
+//   trial side: P[op][rank1(u)][q2] = sum over the run of trial slot q2 of
+//      the entries of test corner u = (t1, a);
+//   test side: entry (q1, q2) = sum over the run of test slot q1 of the P
+//      rows, written to out[4 * e + op] (tile layout [entry][op]).
+// Both sides add in run order, i.e. in slot-list order.
+//
+// A wave holds the pairs of four test triangles, so the trial side needs no
+// other wave: it goes through the wave's own four staged rows (one per test
+// triangle), one (operator, test corner) at a time, ordered by the LDS queue
+// alone.  The P rows of V, K and T are kept together, so the workgroup meets
+// once before the test side, whose items load the three operators' rows
+// independently; D follows in a second pass over the same rows (a fourth
+// operator's P rows would leave room for one workgroup per compute unit).
+// The kernel is bound by VALU issue, so the places of a run are turned into LDS
+// addresses once per tile and serve every operator; places past a run's end
+// point at an entry that holds zero, and are added like the others.
+constexpr int SROW = 3 * BT + 1;        // staged row: one entry per trial corner, then the zero entry
+constexpr int ST_WAVE = 4 * SROW;       // staged rows of one wave
+constexpr int P_OP = 3 * BT * SMAX + 1; // P rows of one operator, then the zero entry
+constexpr int P_LEN = 3 * P_OP;
+constexpr int SLOT_IT1 = (SMAX + 15) / 16;   // trial-side items per lane (16 slots x 4 rows at a time)
+static_assert(LMAX <= 12, "a run is read as at most 12 entries");
 
-// sum of x[0 .. m) with x[v] = src[v * stride], in order; m <= LMAX
-template <class C2>
-__device__ inline C2 run_sum(const C2 *src, int stride, int m)
+// Orders the wave's LDS accesses before and after it for the compiler; the
+// LDS serves one wave's accesses in the order they are issued.
+__device__ inline void wave_lds_order()
 {
-    using R = decltype(C2::x);
-    const C2 x0 = src[0], x1 = src[stride], x2 = src[2 * stride], x3 = src[3 * stride];
-    R re = x0.x, im = x0.y;
-    if (m > 1) { re += x1.x; im += x1.y; }
-    if (m > 2) { re += x2.x; im += x2.y; }
-    if (m > 3) { re += x3.x; im += x3.y; }
-    if (m > 4) {
-        const C2 y0 = src[4 * stride], y1 = src[5 * stride], y2 = src[6 * stride], y3 = src[7 * stride];
-        re += y0.x; im += y0.y;
-        if (m > 5) { re += y1.x; im += y1.y; }
-        if (m > 6) { re += y2.x; im += y2.y; }
-        if (m > 7) { re += y3.x; im += y3.y; }
-        for (int v = 8; v < m; ++v) { re += src[v * stride].x; im += src[v * stride].y; }
-    }
-    return C2{re, im};
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
-// stage 1 (every run has at least one corner, so m >= 1)
-template <class C2>
-__device__ inline void slot_sums_trial(int tid, int nc1, int ns2, const uint8_t *o2, const uint8_t *r1, const C2 *st,
-                                       C2 *P)
+// The places of a run of m entries from `first` on by `stride` (m = 0: no run).
+// most: the longest run among the lanes that load together, so that they take
+// the same branches.
+struct RunPlaces {
+    int at[6], first, stride, m, zero;
+    __device__ void set(int f, int st, int len, int z)
+    {
+        first = f; stride = st; m = len; zero = z;
+#pragma unroll
+        for (int v = 0; v < 6; ++v) at[v] = v < m ? f + v * st : z;
+    }
+    __device__ int place(int v) const { return v < m ? first + v * stride : zero; }
+};
+__device__ inline int run_class(int m) { return __any(m > 6) ? 12 : (__any(m > 4) ? 6 : 4); }
+
+// the entries of a run in `base`, loaded at once, and their sum in run order
+template <class C2> struct RunValues {
+    C2 x[4], y[2], z[6];
+    __device__ void load(const C2 *base, const RunPlaces &p, int most)
+    {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] = base[p.at[v]];
+        if (most > 4) {
+#pragma unroll
+            for (int v = 0; v < 2; ++v) y[v] = base[p.at[4 + v]];
+            if (most > 6)
+#pragma unroll
+                for (int v = 0; v < 6; ++v) z[v] = base[p.place(6 + v)];
+        }
+    }
+    __device__ C2 sum(int most) const
+    {
+        C2 s = x[0];
+#pragma unroll
+        for (int v = 1; v < 4; ++v) { s.x += x[v].x; s.y += x[v].y; }
+        if (most > 4) {
+#pragma unroll
+            for (int v = 0; v < 2; ++v) { s.x += y[v].x; s.y += y[v].y; }
+            if (most > 6)
+#pragma unroll
+                for (int v = 0; v < 6; ++v) { s.x += z[v].x; s.y += z[v].y; }
+        }
+        return s;
+    }
+};
+
+// The slot sums of one tile.  entry(op, a, b): this thread's entry of
+// operator op at corners (a, b) (called with constants once unrolled, for
+// threads whose pair has a place in the tile only).  st: ST_WAVE entries of
+// this wave; P: P_LEN entries of the workgroup.
+template <class C2, class Entry>
+__device__ inline void tile_slot_sums(int tid, int n1, int n2, int ns1, int ns2, const uint8_t *o1, const uint8_t *o2,
+                                      const uint8_t *r1, const uint8_t *r2, C2 *st, C2 *P, C2 *out, Entry entry)
 {
+    const int lane = tid & 63;
+    const int t1 = tid >> 4, t2 = tid & 15;
+    const bool staged = t1 < n1 && t2 < n2;
+    int rk[3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) rk[b] = (t1 & 3) * SROW + (staged ? r2[3 * t2 + b] : 0);
+    if (lane < 4) st[lane * SROW + 3 * BT] = C2{0, 0};
+    if (tid < 3) P[tid * P_OP + P_OP - 1] = C2{0, 0};
+    // trial-side items of this lane: row (test triangle) lane % 4, slots lane / 4 and so on by 16
+    const int row = lane & 3, ti = 4 * (tid >> 6) + row;
+    RunPlaces run1[SLOT_IT1];
+    int pr[3];
 #pragma unroll
     for (int j = 0; j < SLOT_IT1; ++j) {
-        const int it = tid + 256 * j, q2 = it / (3 * BT), u = it - q2 * (3 * BT);
-        if (q2 < ns2 && u < nc1) {
-            const int s0 = o2[q2];
-            P[r1[u] * PROW + q2] = run_sum(st + u * SROW + s0, 1, o2[q2 + 1] - s0);
-        }
+        const int q2 = (lane >> 2) + 16 * j;
+        const bool live = q2 < ns2 && ti < n1;
+        const int s0 = live ? o2[q2] : 0;
+        run1[j].set(row * SROW + s0, 1, live ? o2[q2 + 1] - s0 : 0, row * SROW + 3 * BT);
     }
-}
-
-// stage 2
-template <class C2>
-__device__ inline void slot_sums_test(int tid, int op, int ns1, int ns2, const uint8_t *o1, const C2 *P, C2 *out)
-{
+    int most1[SLOT_IT1];
 #pragma unroll
-    for (int j = 0; j < SLOT_IT2; ++j) {
-        const int it = tid + 256 * j, q1 = it / SMAX, q2 = it - q1 * SMAX;
-        if (q1 < ns1 && q2 < ns2) {
+    for (int j = 0; j < SLOT_IT1; ++j) most1[j] = run_class(run1[j].m);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) pr[a] = (ti < n1 ? r1[3 * ti + a] : 0) * SMAX + (lane >> 2);
+    auto test_side = [&](int op0, int nop) {   // operators op0 .. op0 + nop - 1 from the P rows 0 .. nop - 1
+        const float inv = 1.0f / (float)ns2;
+#pragma unroll 1
+        for (int it = tid; it < ns1 * ns2; it += 256) {   // (q1, q2) of the ns1 x ns2 sums
+            const int q1 = (int)(((float)it + 0.5f) * inv), q2 = it - q1 * ns2;
             const int s0 = o1[q1];
-            out[4 * it + op] = run_sum(P + s0 * PROW + q2, PROW, o1[q1 + 1] - s0);
+            RunPlaces run2;
+            run2.set(s0 * SMAX + q2, SMAX, o1[q1 + 1] - s0, P_OP - 1);
+            const int most2 = run_class(run2.m);
+            C2 *o = out + 4 * (q1 * SMAX + q2) + op0;
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                if (q < nop) {
+                    RunValues<C2> r;
+                    r.load(P + q * P_OP, run2, most2);
+                    o[q] = r.sum(most2);
+                }
+        }
+    };
+    auto stage = [&](int op, int a) {
+        if (staged)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) st[rk[b]] = entry(op, a, b);
+    };
+    stage(0, 0);
+#pragma unroll
+    for (int op = 0; op < 4; ++op) {
+        if (op == 3) {
+            __syncthreads();
+            test_side(0, 3);
+            __syncthreads();
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            RunValues<C2> r[SLOT_IT1];
+            wave_lds_order();
+#pragma unroll
+            for (int j = 0; j < SLOT_IT1; ++j)
+                if (16 * j < ns2) r[j].load(st, run1[j], most1[j]);
+            wave_lds_order();
+            if (a < 2) stage(op, a + 1);
+            else if (op < 3) stage(op + 1, 0);
+#pragma unroll
+            for (int j = 0; j < SLOT_IT1; ++j)
+                if (16 * j < ns2 && run1[j].m > 0) P[(op % 3) * P_OP + pr[a] + 16 * j] = r[j].sum(most1[j]);
         }
     }
+    __syncthreads();
+    test_side(3, 1);
 }
 
-// sin and cos of a small angle t, |t| <= 1: Taylor polynomials of sin
-// through t^17 and of cos through t^18 (the first omitted terms are below
-// 1e-17 and 5e-19); the coefficients are 1/n!.
-__device__ inline void small_sincos(double t, double &s, double &c)
+// 1 / sqrt(x) of a positive finite x: the hardware estimate (relative error e
+// below 2^-20) with one third-order step, 1 + e/2 + 3 e^2 / 8 (error below
+// 2^-60); without the library function's handling of 0 and infinity.
+__device__ inline double rsqrt_pos(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// fma(a, b, c) with c in scalar registers (a constant): the compiler's own
+// choice copies c into vector registers first (v_fmac needs its addend
+// there), one instruction more per polynomial step.
+__device__ inline double fma_const(double a, double b, double c)
+{
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+    return r;
+}
+
+// sin and cos of a small angle t: the Taylor series of sin(t)/t and cos t as
+// polynomials in z = t^2, economised by Chebyshev polynomials (Lanczos) on
+// the range of z.  HALF: |t| <= 1/2, degrees 5 and 6, errors below 2e-17 and
+// 1e-19; else |t| <= 1, degree 7, errors below 1e-19 and 2e-18.
+template <bool HALF> __device__ inline void small_sincos(double t, double &s, double &c)
 {
     const double z = t * t;
-    double ps = 2.8114572543455206e-15;            //  1/17!
-    ps = fma(ps, z, -7.647163731819816e-13);       // -1/15!
-    ps = fma(ps, z, 1.6059043836821613e-10);       //  1/13!
-    ps = fma(ps, z, -2.505210838544172e-08);       // -1/11!
-    ps = fma(ps, z, 2.7557319223985893e-06);       //  1/9!
-    ps = fma(ps, z, -0.0001984126984126984);       // -1/7!
-    ps = fma(ps, z, 0.008333333333333333);         //  1/5!
-    ps = fma(ps, z, -0.16666666666666666);         // -1/3!
+    double ps, pc;
+    if constexpr (HALF) {
+        ps = fma_const(-2.493193700544346e-08, z, 2.7556981496282986e-06);
+        ps = fma_const(ps, z, -0.00019841269403639427);
+        ps = fma_const(ps, z, 0.008333333333076967);
+        ps = fma_const(ps, z, -0.16666666666666116);
+        pc = fma_const(2.077661169102768e-09, z, -2.7556975230704026e-07);
+        pc = fma_const(pc, z, 2.4801586715453357e-05);
+        pc = fma_const(pc, z, -0.0013888888888376136);
+        pc = fma_const(pc, z, 0.04166666666666453);
+    } else {
+        ps = fma_const(-7.535488064487613e-13, z, 1.6057233337039862e-10);
+        ps = fma_const(ps, z, -2.5052093083699724e-08);
+        ps = fma_const(ps, z, 2.7557319152309194e-06);
+        ps = fma_const(ps, z, -0.00019841269841087476);
+        ps = fma_const(ps, z, 0.008333333333333106);
+        ps = fma_const(ps, z, -0.16666666666666666);
+        pc = fma_const(-1.1281052794952459e-11, z, 2.0873682510844006e-09);
+        pc = fma_const(pc, z, -2.755729324310771e-07);
+        pc = fma_const(pc, z, 2.4801587179897263e-05);
+        pc = fma_const(pc, z, -0.0013888888888579293);
+        pc = fma_const(pc, z, 0.0416666666666628);
+    }
     s = fma(t * z, ps, t);
-    double pc = -1.5619206968586225e-16;           // -1/18!
-    pc = fma(pc, z, 4.779477332387385e-14);        //  1/16!
-    pc = fma(pc, z, -1.1470745597729725e-11);      // -1/14!
-    pc = fma(pc, z, 2.08767569878681e-09);         //  1/12!
-    pc = fma(pc, z, -2.755731922398589e-07);       // -1/10!
-    pc = fma(pc, z, 2.48015873015873e-05);         //  1/8!
-    pc = fma(pc, z, -0.001388888888888889);        // -1/6!
-    pc = fma(pc, z, 0.041666666666666664);         //  1/4!
-    pc = fma(pc, z, -0.5);                         // -1/2!
+    pc = fma(pc, z, -0.5);
     c = fma(z, pc, 1.0);
 }
 
+// The 6-point rule applied to six values g_0 .. g_5 with the P1 functions:
+// sum over q of w_q lambda_b(q) g_q for b = 0..2.  With the two orbits'
+// barycentric coordinates (a, a, 1 - 2a) it is, up to the factor kR6G,
+//   h_b + kR6H (h_0 + h_1 + h_2) + kR6S (g_3 + g_4 + g_5),  h_b = g_b + kR6C g_{b+3}:
+// two operations per value instead of three.
+constexpr double kR6G = kW1 * (1.0 - 3.0 * kA1);
+constexpr double kR6C = kW2 * (1.0 - 3.0 * kA2) / kR6G;
+constexpr double kR6H = kW1 * kA1 / kR6G;
+constexpr double kR6S = kW2 * kA2 / kR6G - kR6H * kR6C;
+template <class R> struct Rule6Sum {
+    R h[3], s;
+    __device__ void add(int b, R g0, R g1)   // g_b and g_{b+3}, b = 0, 1, 2 in this order
+    {
+        h[b] = g0 + (R)kR6C * g1;
+        s = b == 0 ? g1 : s + g1;
+    }
+    __device__ void finish()
+    {
+        const R m = (R)kR6H * (h[0] + h[1] + h[2]) + (R)kR6S * s;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) h[b] += m;
+    }
+};
+
 // 6 x 6 point pairs of one regular triangle pair (x on X, y on Y): the 3 x 3
 // element sums of V (kernel G), K (dG/dn_y), T (dG/dn_x) and the scalar sum
-// of G, unscaled (times area_X area_Y / (4 pi) later).  K uses that
-// (y - x).n_y is the same for every y on the plane of Y, so its factor is
-// applied once per test point.  BASE: phase from the per-pair base (see the
-// caller).  CK: complex wavenumber k + i kim.
-template <bool CK, bool BASE>
+// of G, unscaled (times area_X area_Y / (4 pi) later).  K and T use that
+// (y - x).n_y is the same for every y on the plane of Y and (x - y).n_x for
+// every x on the plane of X: one factor per test point and one per trial
+// point.  BASE: phase from the per-pair base (see the caller; 1 up to 1, 2 up
+// to 1/2 radian off it), whose factor exp(i k r0) is applied to the sums.  CK:
+// complex wavenumber k + i kim.
+template <bool CK, int BASE>
 __device__ inline void pair_quadrature(const TriGeo &X, const TriGeo &Y, double k, double kim, double (&vr)[9],
                                        double (&vi)[9], double (&kr)[9], double (&ki)[9], double (&tr)[9],
                                        double (&ti)[9], double &sr, double &si)
 {
-    const double nx0 = X.n[0], nx1 = X.n[1], nx2 = X.n[2];
     const double ny0 = Y.n[0], ny1 = Y.n[1], ny2 = Y.n[2];
     const double ey0 = ny0 * Y.p[0][0] + ny1 * Y.p[0][1] + ny2 * Y.p[0][2];   // n_y . (a vertex of Y)
     double e0r = 1.0, e0i = 0.0, kr0 = 0.0;
@@ -237,69 +383,86 @@ __device__ inline void pair_quadrature(const TriGeo &X, const TriGeo &Y, double 
         kr0 = k * sqrt(c0 * c0 + c1 * c1 + c2 * c2);
         phase_sincos(kr0, &e0i, &e0r);
     }
+    double dtq[6];   // (x - y).n_x
+    {
+        const double nx0 = X.n[0], nx1 = X.n[1], nx2 = X.n[2];
+        const double ex0 = nx0 * X.p[0][0] + nx1 * X.p[0][1] + nx2 * X.p[0][2];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) dtq[q] = ex0 - (nx0 * Y.qp[q][0] + nx1 * Y.qp[q][1] + nx2 * Y.qp[q][2]);
+    }
 #pragma unroll
     for (int p = 0; p < 6; ++p) {
         const double x0 = X.qp[p][0], x1 = X.qp[p][1], x2 = X.qp[p][2];
         const double dkp = ey0 - (ny0 * x0 + ny1 * x1 + ny2 * x2);   // (y - x).n_y
-        double hvr[3] = {0, 0, 0}, hvi[3] = {0, 0, 0}, hkr[3] = {0, 0, 0}, hki[3] = {0, 0, 0};
-        double htr[3] = {0, 0, 0}, hti[3] = {0, 0, 0};
+        Rule6Sum<double> hvr, hvi, hkr, hki, htr, hti;
 #pragma unroll
-        for (int q = 0; q < 6; ++q) {
-            const double d0 = x0 - Y.qp[q][0], d1 = x1 - Y.qp[q][1], d2 = x2 - Y.qp[q][2];
-            const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
-            const double rinv = rsqrt(r2);
-            const double r = r2 * rinv;
-            const double kr_ = k * r;
-            double sn, cs;
-            if constexpr (BASE) {
-                double sd, cd;
-                small_sincos(fma(k, r, -kr0), sd, cd);
-                cs = e0r * cd - e0i * sd;
-                sn = e0r * sd + e0i * cd;
-            } else {
-                phase_sincos(kr_, &sn, &cs);
-            }
-            double gr = cs * rinv, gi = sn * rinv;                 // exp(ikr)/r
-            const double rinv2 = rinv * rinv;
-            double fr, fi;                                         // exp(ikr)(ikr-1)/r^3
-            if constexpr (CK) {
-                const double dmp = exp(-kim * r), am = -1.0 - kim * r;
-                gr *= dmp; gi *= dmp;
-                fr = (gr * am - gi * kr_) * rinv2;
-                fi = (gr * kr_ + gi * am) * rinv2;
-            } else {
-                fr = (-gr - gi * kr_) * rinv2;
-                fi = (gr * kr_ - gi) * rinv2;
-            }
-            const double dt = d0 * nx0 + d1 * nx1 + d2 * nx2;     // (x-y).n_x
-            const double gtr = fr * dt, gti = fi * dt;
+        for (int b = 0; b < 3; ++b) {
+            double gr[2], gi[2], fr[2], fi[2];
 #pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                const double W = r6_w(q) * r6_bary(q, b);
-                hvr[b] += W * gr; hvi[b] += W * gi;
-                hkr[b] += W * fr; hki[b] += W * fi;
-                htr[b] += W * gtr; hti[b] += W * gti;
+            for (int o = 0; o < 2; ++o) {
+                const int q = b + 3 * o;
+                const double d0 = x0 - Y.qp[q][0], d1 = x1 - Y.qp[q][1], d2 = x2 - Y.qp[q][2];
+                const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
+                const double rinv = rsqrt_pos(r2);
+                const double r = r2 * rinv;
+                const double kr_ = k * r;
+                double sn, cs;
+                if constexpr (BASE) {
+                    small_sincos<BASE == 2>(fma(k, r, -kr0), sn, cs);
+                } else {
+                    phase_sincos(kr_, &sn, &cs);
+                }
+                gr[o] = cs * rinv; gi[o] = sn * rinv;              // exp(ikr)/r
+                const double rinv2 = rinv * rinv;
+                if constexpr (CK) {                                // exp(ikr)(ikr-1)/r^3
+                    const double dmp = exp(-kim * r), am = -1.0 - kim * r;
+                    gr[o] *= dmp; gi[o] *= dmp;
+                    fr[o] = (gr[o] * am - gi[o] * kr_) * rinv2;
+                    fi[o] = (gr[o] * kr_ + gi[o] * am) * rinv2;
+                } else {
+                    fr[o] = (-gr[o] - gi[o] * kr_) * rinv2;
+                    fi[o] = (gr[o] * kr_ - gi[o]) * rinv2;
+                }
             }
+            hvr.add(b, gr[0], gr[1]); hvi.add(b, gi[0], gi[1]);
+            hkr.add(b, fr[0], fr[1]); hki.add(b, fi[0], fi[1]);
+            htr.add(b, fr[0] * dtq[b], fr[1] * dtq[b + 3]); hti.add(b, fi[0] * dtq[b], fi[1] * dtq[b + 3]);
         }
+        hvr.finish(); hvi.finish(); hkr.finish(); hki.finish(); htr.finish(); hti.finish();
         const double wp = p < 3 ? kW1 : kW2;
         const double ap = p < 3 ? kA1 : kA2;
         const int pc = p < 3 ? p : p - 3;            // corner carrying 1 - 2a
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            const double W = wp * (a == pc ? 1.0 - 2.0 * ap : ap);
+            const double W = kR6G * wp * (a == pc ? 1.0 - 2.0 * ap : ap);
             const double Wk = W * dkp;
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
-                vr[3 * a + b] += W * hvr[b]; vi[3 * a + b] += W * hvi[b];
-                kr[3 * a + b] += Wk * hkr[b]; ki[3 * a + b] += Wk * hki[b];
-                tr[3 * a + b] += W * htr[b]; ti[3 * a + b] += W * hti[b];
+                vr[3 * a + b] += W * hvr.h[b]; vi[3 * a + b] += W * hvi.h[b];
+                kr[3 * a + b] += Wk * hkr.h[b]; ki[3 * a + b] += Wk * hki.h[b];
+                tr[3 * a + b] += W * htr.h[b]; ti[3 * a + b] += W * hti.h[b];
             }
         }
     }
     const double scale = X.area * Y.area * kInv4Pi;
+    if constexpr (BASE) {
+        const double er = scale * e0r, ei = scale * e0i;
+        auto turn = [&](double &re, double &im) {
+            const double x = re;
+            re = x * er - im * ei;
+            im = x * ei + im * er;
+        };
 #pragma unroll
-    for (int e = 0; e < 9; ++e) {
-        vr[e] *= scale; vi[e] *= scale; kr[e] *= scale; ki[e] *= scale; tr[e] *= scale; ti[e] *= scale;
+        for (int e = 0; e < 9; ++e) {
+            turn(vr[e], vi[e]);
+            turn(kr[e], ki[e]);
+            turn(tr[e], ti[e]);
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 9; ++e) {
+            vr[e] *= scale; vi[e] *= scale; kr[e] *= scale; ki[e] *= scale; tr[e] *= scale; ti[e] *= scale;
+        }
     }
     // sum G over the point pairs: the P1 functions sum to one at every point,
     // so the sum over a, b of the V entries is that sum
@@ -341,8 +504,8 @@ __global__ __launch_bounds__(256, 2) void regular_tiles_kernel(TileArgs A, int64
     __shared__ int32_t vX[BT * 3], vY[BT * 3];
     __shared__ uint8_t o1[SLOT_OFF_LD], o2[SLOT_OFF_LD];   // first slot-major rank of each slot
     __shared__ uint8_t r1[3 * BT], r2[3 * BT];             // slot-major rank of each corner
-    __shared__ double2 st[ST_LEN];   // the 9 entries of every thread's pair, one operator at a time
-    __shared__ double2 P[P_LEN];     // test-corner rank x trial slot partial sums
+    __shared__ double2 st[4][ST_WAVE];   // each wave's staged rows
+    __shared__ double2 P[P_LEN];         // test-corner rank x trial slot partial sums
 
     const int64_t tile = tile0 + blockIdx.x;
     int b1, b2;
@@ -370,10 +533,8 @@ __global__ __launch_bounds__(256, 2) void regular_tiles_kernel(TileArgs A, int64
     }
     __syncthreads();
 
-    const int t1 = tid >> 4, t2 = tid & 15, sbase = 3 * t1 * SROW;
-    const bool staged = t1 < n1 && t2 < n2;   // the pair's entries have a place in the staged rows
-    const int rk0 = staged ? r2[3 * t2] : 0, rk1 = staged ? r2[3 * t2 + 1] : 0, rk2 = staged ? r2[3 * t2 + 2] : 0;
-    bool active = staged;
+    const int t1 = tid >> 4, t2 = tid & 15;
+    bool active = t1 < n1 && t2 < n2;
     if (active) {
         for (int a = 0; a < 3; ++a)
             for (int b = 0; b < 3; ++b) active = active && (vX[3 * t1 + a] != vY[3 * t2 + b]);
@@ -382,55 +543,38 @@ __global__ __launch_bounds__(256, 2) void regular_tiles_kernel(TileArgs A, int64
 #pragma unroll
     for (int e = 0; e < 9; ++e) { vr[e] = vi[e] = kr[e] = ki[e] = tr[e] = ti[e] = 0.0; }
     const double k = A.k;
+    // Phase by a per-pair base where k (rho_X + rho_Y) <= 1 for every pair of
+    // the wave: with r0 the centroid distance, |k (r - r0)| <= 1 for every
+    // point pair, so exp(i k r) = exp(i k r0) exp(i k (r - r0)) takes one
+    // reduced sin/cos per pair and short polynomials per point pair (shorter
+    // ones up to 1/2).  The choice is the wave's, so that its lanes run one
+    // of the three forms.
+    const double spread = active ? k * (gX[t1].g.rho + gY[t2].g.rho) : 0.0;
+    const int base = CK || __any(spread > 1.0) ? 0 : (__any(spread > 0.5) ? 1 : 2);
     if (active) {
         const TriGeo &X = gX[t1].g;
         const TriGeo &Y = gY[t2].g;
-        // Phase by a per-pair base when k (rho_X + rho_Y) <= 1: with r0 the
-        // centroid distance, |k (r - r0)| <= 1 for every point pair, so
-        // exp(i k r) = exp(i k r0) exp(i k (r - r0)) takes one reduced
-        // sin/cos per pair and short polynomials per point pair.
-        if (!CK && k * (X.rho + Y.rho) <= 1.0)
-            pair_quadrature<CK, true>(X, Y, k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
-        else
-            pair_quadrature<CK, false>(X, Y, k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
+        if (base == 2) pair_quadrature<CK, CK ? 0 : 2>(X, Y, k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
+        else if (base == 1) pair_quadrature<CK, CK ? 0 : 1>(X, Y, k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
+        else pair_quadrature<CK, 0>(X, Y, k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
     }
 
-    // ---- per-slot reduction through LDS, one operator at a time (two barriers per operator)
-    double2 *out = A.scratch + (tile - A.tile_base) * (4 * SMAX * SMAX);
-#pragma unroll 1
-    for (int op = 0; op < 4; ++op) {
-        if (op == 3 && active) {
-            const TriGeo &X = gX[t1].g;
-            const TriGeo &Y = gY[t2].g;
-            const double nn = X.n[0] * Y.n[0] + X.n[1] * Y.n[1] + X.n[2] * Y.n[2];
-            for (int a = 0; a < 3; ++a)
-                for (int b = 0; b < 3; ++b) {
-                    const double cc = X.curl[a][0] * Y.curl[b][0] + X.curl[a][1] * Y.curl[b][1] + X.curl[a][2] * Y.curl[b][2];
-                    if constexpr (CK) {   // complex k^2
-                        const double k2r = k * k - A.kim * A.kim, k2i = 2.0 * k * A.kim;
-                        const double v_r = vr[3 * a + b], v_i = vi[3 * a + b];
-                        st[sbase + a * SROW + (b == 0 ? rk0 : (b == 1 ? rk1 : rk2))] = make_double2(cc * sr - nn * (k2r * v_r - k2i * v_i),
-                                                               cc * si - nn * (k2r * v_i + k2i * v_r));
-                    } else {
-                        st[sbase + a * SROW + (b == 0 ? rk0 : (b == 1 ? rk1 : rk2))] = make_double2(cc * sr - k * k * nn * vr[3 * a + b],
-                                                               cc * si - k * k * nn * vi[3 * a + b]);
-                    }
-                }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 9; ++e) {
-                double re = op == 0 ? vr[e] : (op == 1 ? kr[e] : (op == 2 ? tr[e] : 0.0));
-                double im = op == 0 ? vi[e] : (op == 1 ? ki[e] : (op == 2 ? ti[e] : 0.0));
-                if (staged)
-                    st[sbase + (e / 3) * SROW + (e % 3 == 0 ? rk0 : (e % 3 == 1 ? rk1 : rk2))] =
-                        active ? make_double2(re, im) : make_double2(0.0, 0.0);
-            }
-        }
-        __syncthreads();   // st holds this operator; the previous operator's stage 2 is done with P
-        slot_sums_trial(tid, 3 * n1, ns2, o2, r1, st, P);
-        __syncthreads();   // P complete; st free for the next operator
-        slot_sums_test(tid, op, ns1, ns2, o1, P, out);
-    }
+    const TriGeo &X = gX[t1].g;
+    const TriGeo &Y = gY[t2].g;
+    const double nn = X.n[0] * Y.n[0] + X.n[1] * Y.n[1] + X.n[2] * Y.n[2];
+    const double k2r = CK ? k * k - A.kim * A.kim : k * k, k2i = 2.0 * k * A.kim;
+    tile_slot_sums(tid, n1, n2, ns1, ns2, o1, o2, r1, r2, st[tid >> 6], P, A.scratch + (tile - A.tile_base) * (4 * SMAX * SMAX),
+                   [&](int op, int a, int b) {
+                       const int e = 3 * a + b;
+                       if (op == 0) return make_double2(vr[e], vi[e]);
+                       if (op == 1) return make_double2(kr[e], ki[e]);
+                       if (op == 2) return make_double2(tr[e], ti[e]);
+                       const double cc = X.curl[a][0] * Y.curl[b][0] + X.curl[a][1] * Y.curl[b][1] + X.curl[a][2] * Y.curl[b][2];
+                       if constexpr (CK)   // complex k^2
+                           return make_double2(cc * sr - nn * (k2r * vr[e] - k2i * vi[e]), cc * si - nn * (k2r * vi[e] + k2i * vr[e]));
+                       else
+                           return make_double2(cc * sr - k2r * nn * vr[e], cc * si - k2r * nn * vi[e]);
+                   });
 }
 
 // Mixed-precision form of the regular-pair tile (FP32 arithmetic, complex64
@@ -448,8 +592,8 @@ __global__ __launch_bounds__(256, 3) void regular_tiles_f32_kernel(TileArgsF A, 
     __shared__ int32_t vX[BT * 3], vY[BT * 3];
     __shared__ uint8_t o1[SLOT_OFF_LD], o2[SLOT_OFF_LD];   // first slot-major rank of each slot
     __shared__ uint8_t r1[3 * BT], r2[3 * BT];             // slot-major rank of each corner
-    __shared__ float2 st[ST_LEN];
-    __shared__ float2 P[P_LEN];
+    __shared__ float2 st[4][ST_WAVE];   // each wave's staged rows
+    __shared__ float2 P[P_LEN];         // test-corner rank x trial slot partial sums
 
     const int64_t tile = tile0 + blockIdx.x;
     int b1, b2;
@@ -477,10 +621,8 @@ __global__ __launch_bounds__(256, 3) void regular_tiles_f32_kernel(TileArgsF A, 
     }
     __syncthreads();
 
-    const int t1 = tid >> 4, t2 = tid & 15, sbase = 3 * t1 * SROW;
-    const bool staged = t1 < n1 && t2 < n2;   // the pair's entries have a place in the staged rows
-    const int rk0 = staged ? r2[3 * t2] : 0, rk1 = staged ? r2[3 * t2 + 1] : 0, rk2 = staged ? r2[3 * t2 + 2] : 0;
-    bool active = staged;
+    const int t1 = tid >> 4, t2 = tid & 15;
+    bool active = t1 < n1 && t2 < n2;
     if (active) {
         for (int a = 0; a < 3; ++a)
             for (int b = 0; b < 3; ++b) active = active && (vX[3 * t1 + a] != vY[3 * t2 + b]);
@@ -572,41 +714,22 @@ __global__ __launch_bounds__(256, 3) void regular_tiles_f32_kernel(TileArgsF A, 
 #pragma unroll
         for (int e = 0; e < 9; ++e) { sr += vr[e]; si += vi[e]; }
     }
-    float2 *out = A.scratch + (tile - A.tile_base) * (4 * SMAX * SMAX);
-#pragma unroll 1
-    for (int op = 0; op < 4; ++op) {
-        if (op == 3 && active) {
-            const TriGeoF &X = gX[t1];
-            const TriGeoF &Y = gY[t2];
-            const float nn = X.n[0] * Y.n[0] + X.n[1] * Y.n[1] + X.n[2] * Y.n[2];
-            for (int a = 0; a < 3; ++a)
-                for (int b = 0; b < 3; ++b) {
-                    const float cc = X.curl[a][0] * Y.curl[b][0] + X.curl[a][1] * Y.curl[b][1] + X.curl[a][2] * Y.curl[b][2];
-                    if constexpr (CK) {   // complex k^2
-                        const float k2r = (float)(A.k * A.k - A.kim * A.kim), k2i = (float)(2.0 * A.k * A.kim);
-                        const float v_r = vr[3 * a + b], v_i = vi[3 * a + b];
-                        st[sbase + a * SROW + (b == 0 ? rk0 : (b == 1 ? rk1 : rk2))] = make_float2(cc * sr - nn * (k2r * v_r - k2i * v_i),
-                                                              cc * si - nn * (k2r * v_i + k2i * v_r));
-                    } else {
-                        st[sbase + a * SROW + (b == 0 ? rk0 : (b == 1 ? rk1 : rk2))] = make_float2(cc * sr - kf * kf * nn * vr[3 * a + b],
-                                                              cc * si - kf * kf * nn * vi[3 * a + b]);
-                    }
-                }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 9; ++e) {
-                float re = op == 0 ? vr[e] : (op == 1 ? kr[e] : (op == 2 ? tr[e] : 0.f));
-                float im = op == 0 ? vi[e] : (op == 1 ? ki[e] : (op == 2 ? ti[e] : 0.f));
-                if (staged)
-                    st[sbase + (e / 3) * SROW + (e % 3 == 0 ? rk0 : (e % 3 == 1 ? rk1 : rk2))] =
-                        active ? make_float2(re, im) : make_float2(0.f, 0.f);
-            }
-        }
-        __syncthreads();   // st holds this operator; the previous operator's stage 2 is done with P
-        slot_sums_trial(tid, 3 * n1, ns2, o2, r1, st, P);
-        __syncthreads();   // P complete; st free for the next operator
-        slot_sums_test(tid, op, ns1, ns2, o1, P, out);
-    }
+    const TriGeoF &X = gX[t1];
+    const TriGeoF &Y = gY[t2];
+    const float nn = X.n[0] * Y.n[0] + X.n[1] * Y.n[1] + X.n[2] * Y.n[2];
+    const float k2r = CK ? (float)(A.k * A.k - A.kim * A.kim) : kf * kf, k2i = (float)(2.0 * A.k * A.kim);
+    tile_slot_sums(tid, n1, n2, ns1, ns2, o1, o2, r1, r2, st[tid >> 6], P, A.scratch + (tile - A.tile_base) * (4 * SMAX * SMAX),
+                   [&](int op, int a, int b) {
+                       const int e = 3 * a + b;
+                       if (op == 0) return make_float2(vr[e], vi[e]);
+                       if (op == 1) return make_float2(kr[e], ki[e]);
+                       if (op == 2) return make_float2(tr[e], ti[e]);
+                       const float cc = X.curl[a][0] * Y.curl[b][0] + X.curl[a][1] * Y.curl[b][1] + X.curl[a][2] * Y.curl[b][2];
+                       if constexpr (CK)   // complex k^2
+                           return make_float2(cc * sr - nn * (k2r * vr[e] - k2i * vi[e]), cc * si - nn * (k2r * vi[e] + k2i * vr[e]));
+                       else
+                           return make_float2(cc * sr - k2r * nn * vr[e], cc * si - k2r * nn * vi[e]);
+                   });
 }
 
 // The contributions to dense entry (i, j) of the tiles of one strip (tile
