@@ -76,7 +76,7 @@ __global__ void geometry_kernel(const double *__restrict__ xyz, const int32_t *_
     f.area = (float)g.area;
     for (int a = 0; a < 3; ++a)
         for (int c = 0; c < 3; ++c) f.curl[a][c] = (float)g.curl[a][c];
-    f.pad = 0.f;
+    f.rho = (float)(g.rho * (1.0 + 1e-6));   // not below the FP64 radius
     geof[t] = f;
 }
 
@@ -577,14 +577,129 @@ __global__ __launch_bounds__(256, 2) void regular_tiles_kernel(TileArgs A, int64
                    });
 }
 
-// Mixed-precision form of the regular-pair tile (FP32 arithmetic, complex64
-// tiles).  The phase k|x - y| is split per triangle pair: with d0 the FP64
-// centroid difference and r0 = |d0|, exp(i k r) = exp(i k r0) exp(i k D)
-// where exp(i k r0) is evaluated once in FP64 and D = r - r0 =
-// (2 d0.e + |e|^2) / (r + r0), e = (x - c_x) - (y - c_y), is small and
-// accurate in FP32; FP32 alone would lose about k r * 6e-8 of phase.
-// CK as in the FP64 kernel: the damping exp(-kim r) splits like the phase,
-// exp(-kim r0) in FP64 per pair and exp(-kim D) in FP32 per point.
+// sin and cos of a small angle t, |t| <= 1, FP32: as small_sincos, economised
+// on z = t^2 in [0, 1] to degree 4 (errors below 1e-10 and 1e-9, far below
+// FP32 rounding).
+__device__ inline void small_sincos(float t, float &s, float &c)
+{
+    const float z = t * t;
+    float ps = 2.6937597575879865e-06f;
+    ps = fmaf(ps, z, -0.0001983586640864844f);
+    ps = fmaf(ps, z, 0.008333314069456277f);
+    ps = fmaf(ps, z, -0.16666666426123591f);
+    s = fmaf(t * z, ps, t);
+    float pc = 2.412120108186752e-05f;
+    pc = fmaf(pc, z, -0.0013882960343166483f);
+    pc = fmaf(pc, z, 0.041666455375340986f);
+    pc = fmaf(pc, z, -0.49999997362171766f);
+    c = fmaf(z, pc, 1.f);
+}
+
+// The point pairs of one regular triangle pair in FP32.  The phase k|x - y|
+// is split per triangle pair: with d0 the FP64 centroid difference and r0 =
+// |d0|, exp(i k r) = exp(i k r0) exp(i k D), where exp(i k r0) is evaluated
+// once in FP64 and applied to the sums, and D = r - r0 = e.(2 d0 + e) / (r +
+// r0), e = (x - c_x) - (y - c_y), is small and accurate in FP32; FP32 alone
+// would lose about k r * 6e-8 of phase.  SMALL: |k D| <= 1 at every point
+// pair.  CK: the damping exp(-kim r) splits like the phase, exp(-kim r0) in
+// FP64 per pair and exp(-kim D) in FP32 per point.
+template <bool CK, bool SMALL>
+__device__ inline void pair_quadrature_f32(const TriGeoF &X, const TriGeoF &Y, double k, double kim, float (&vr)[9],
+                                           float (&vi)[9], float (&kr)[9], float (&ki)[9], float (&tr)[9],
+                                           float (&ti)[9], float &sr, float &si)
+{
+    const double d00 = X.c[0] - Y.c[0], d01 = X.c[1] - Y.c[1], d02 = X.c[2] - Y.c[2];
+    const double r0 = sqrt(d00 * d00 + d01 * d01 + d02 * d02);
+    double s0, c0;
+    phase_sincos(k * r0, &s0, &c0);
+    if constexpr (CK) {
+        const double dm0 = exp(-kim * r0);
+        s0 *= dm0;
+        c0 *= dm0;
+    }
+    const float kf = (float)k, kimf = (float)kim;
+    const float f00 = (float)d00, f01 = (float)d01, f02 = (float)d02, r0f = (float)r0;
+    const float ny0 = Y.n[0], ny1 = Y.n[1], ny2 = Y.n[2];
+    const float dk0 = (float)-(d00 * ny0 + d01 * ny1 + d02 * ny2);
+    float dtq[6];   // (x - y).n_x: the same for every x on the plane of X
+    {
+        const float nx0 = X.n[0], nx1 = X.n[1], nx2 = X.n[2];
+        const float dt0 = (float)(d00 * nx0 + d01 * nx1 + d02 * nx2);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) dtq[q] = dt0 - (nx0 * Y.dq[q][0] + nx1 * Y.dq[q][1] + nx2 * Y.dq[q][2]);
+    }
+#pragma unroll 1
+    for (int p = 0; p < 6; ++p) {
+        const float x0 = X.dq[p][0], x1 = X.dq[p][1], x2 = X.dq[p][2];
+        const float dkp = dk0 - (ny0 * x0 + ny1 * x1 + ny2 * x2);   // (y - x).n_y
+        Rule6Sum<float> hvr, hvi, hkr, hki, htr, hti;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            float gr[2], gi[2], fr[2], fi[2];
+#pragma unroll
+            for (int o = 0; o < 2; ++o) {
+                const int q = b + 3 * o;
+                const float q0 = x0 - Y.dq[q][0], q1 = x1 - Y.dq[q][1], q2 = x2 - Y.dq[q][2];   // e
+                const float d0 = f00 + q0, d1 = f01 + q1, d2 = f02 + q2;                         // x - y
+                const float r2 = d0 * d0 + d1 * d1 + d2 * d2;
+                const float rinv = __builtin_amdgcn_rsqf(r2);
+                const float r = r2 * rinv;
+                const float num = q0 * (f00 + d0) + q1 * (f01 + d1) + q2 * (f02 + d2);
+                const float dr = num * __builtin_amdgcn_rcpf(r + r0f);
+                float sd, cd;
+                if constexpr (SMALL) small_sincos(kf * dr, sd, cd);
+                else sincosf(kf * dr, &sd, &cd);
+                gr[o] = cd * rinv; gi[o] = sd * rinv;              // exp(ik(r - r0))/r
+                const float kr_ = kf * r, rinv2 = rinv * rinv;
+                if constexpr (CK) {
+                    const float dd = expf(-kimf * dr), am = -1.f - kimf * r;
+                    gr[o] *= dd; gi[o] *= dd;
+                    fr[o] = (gr[o] * am - gi[o] * kr_) * rinv2;
+                    fi[o] = (gr[o] * kr_ + gi[o] * am) * rinv2;
+                } else {
+                    fr[o] = (-gr[o] - gi[o] * kr_) * rinv2;
+                    fi[o] = (gr[o] * kr_ - gi[o]) * rinv2;
+                }
+            }
+            hvr.add(b, gr[0], gr[1]); hvi.add(b, gi[0], gi[1]);
+            hkr.add(b, fr[0], fr[1]); hki.add(b, fi[0], fi[1]);
+            htr.add(b, fr[0] * dtq[b], fr[1] * dtq[b + 3]); hti.add(b, fi[0] * dtq[b], fi[1] * dtq[b + 3]);
+        }
+        hvr.finish(); hvi.finish(); hkr.finish(); hki.finish(); htr.finish(); hti.finish();
+        const float wp = (float)kR6G * (p < 3 ? (float)kW1 : (float)kW2);
+        const float ap = p < 3 ? (float)kA1 : (float)kA2;
+        const float am = p < 3 ? (float)(1.0 - 2.0 * kA1) : (float)(1.0 - 2.0 * kA2);
+        const int pc = p < 3 ? p : p - 3;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float W = wp * (a == pc ? am : ap), Wk = W * dkp;
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                vr[3 * a + b] += W * hvr.h[b]; vi[3 * a + b] += W * hvi.h[b];
+                kr[3 * a + b] += Wk * hkr.h[b]; ki[3 * a + b] += Wk * hki.h[b];
+                tr[3 * a + b] += W * htr.h[b]; ti[3 * a + b] += W * hti.h[b];
+            }
+        }
+    }
+    const float scale = X.area * Y.area * (float)kInv4Pi, er = scale * (float)c0, ei = scale * (float)s0;
+    auto turn = [&](float &re, float &im) {
+        const float x = re;
+        re = x * er - im * ei;
+        im = x * ei + im * er;
+    };
+#pragma unroll
+    for (int e = 0; e < 9; ++e) {
+        turn(vr[e], vi[e]);
+        turn(kr[e], ki[e]);
+        turn(tr[e], ti[e]);
+    }
+    // the sum of G over the point pairs is the sum of the V entries (the P1 functions sum to one)
+#pragma unroll
+    for (int e = 0; e < 9; ++e) { sr += vr[e]; si += vi[e]; }
+}
+
+// Mixed-precision form of the regular-pair tile: FP32 arithmetic (the phase
+// in FP64 once per triangle pair), complex64 tiles.
 template <bool CK>
 __global__ __launch_bounds__(256, 3) void regular_tiles_f32_kernel(TileArgsF A, int64_t tile0)
 {
@@ -631,88 +746,11 @@ __global__ __launch_bounds__(256, 3) void regular_tiles_f32_kernel(TileArgsF A, 
 #pragma unroll
     for (int e = 0; e < 9; ++e) { vr[e] = vi[e] = kr[e] = ki[e] = tr[e] = ti[e] = 0.f; }
     const float kf = (float)A.k;
+    // |k (r - r0)| <= 1 at every point pair of every pair of the wave: short polynomials
+    const bool tame = !__any(active && kf * (gX[t1].rho + gY[t2].rho) > 1.f);
     if (active) {
-        const TriGeoF &X = gX[t1];
-        const TriGeoF &Y = gY[t2];
-        const double d00 = X.c[0] - Y.c[0], d01 = X.c[1] - Y.c[1], d02 = X.c[2] - Y.c[2];
-        const double r0 = sqrt(d00 * d00 + d01 * d01 + d02 * d02);
-        double s0, c0;
-        phase_sincos(A.k * r0, &s0, &c0);
-        if constexpr (CK) {
-            const double dm0 = exp(-A.kim * r0);
-            s0 *= dm0;
-            c0 *= dm0;
-        }
-        const float e0r = (float)c0, e0i = (float)s0;
-        const float f00 = (float)d00, f01 = (float)d01, f02 = (float)d02, r0f = (float)r0;
-        const float nx0 = X.n[0], nx1 = X.n[1], nx2 = X.n[2];
-        const float ny0 = Y.n[0], ny1 = Y.n[1], ny2 = Y.n[2];
-#pragma unroll 1
-        for (int p = 0; p < 6; ++p) {
-            const float x0 = X.dq[p][0], x1 = X.dq[p][1], x2 = X.dq[p][2];
-            float hvr[3] = {0, 0, 0}, hvi[3] = {0, 0, 0}, hkr[3] = {0, 0, 0}, hki[3] = {0, 0, 0};
-            float htr[3] = {0, 0, 0}, hti[3] = {0, 0, 0};
-#pragma unroll
-            for (int q = 0; q < 6; ++q) {
-                const float q0 = x0 - Y.dq[q][0], q1 = x1 - Y.dq[q][1], q2 = x2 - Y.dq[q][2];   // e
-                const float d0 = f00 + q0, d1 = f01 + q1, d2 = f02 + q2;                         // x - y
-                const float r2 = d0 * d0 + d1 * d1 + d2 * d2;
-                const float rinv = __frsqrt_rn(r2);
-                const float r = r2 * rinv;
-                const float num = 2.f * (f00 * q0 + f01 * q1 + f02 * q2) + (q0 * q0 + q1 * q1 + q2 * q2);
-                const float dr = num / (r + r0f);
-                float sd, cd;
-                sincosf(kf * dr, &sd, &cd);
-                float er = e0r * cd - e0i * sd, ei = e0r * sd + e0i * cd;   // exp(ikr)
-                const float kr_ = kf * r, rinv2 = rinv * rinv;
-                float fr, fi;
-                if constexpr (CK) {
-                    const float dd = expf(-(float)A.kim * dr), am = -1.f - (float)A.kim * r;
-                    er *= dd;
-                    ei *= dd;
-                    const float gr = er * rinv, gi = ei * rinv;
-                    fr = (gr * am - gi * kr_) * rinv2;
-                    fi = (gr * kr_ + gi * am) * rinv2;
-                } else {
-                    const float gr = er * rinv, gi = ei * rinv;
-                    fr = (-gr - gi * kr_) * rinv2;
-                    fi = (gr * kr_ - gi) * rinv2;
-                }
-                const float gr = er * rinv, gi = ei * rinv;
-                const float dk = -(d0 * ny0 + d1 * ny1 + d2 * ny2);
-                const float dt = d0 * nx0 + d1 * nx1 + d2 * nx2;
-                const float gkr = fr * dk, gki = fi * dk, gtr = fr * dt, gti = fi * dt;
-#pragma unroll
-                for (int b = 0; b < 3; ++b) {
-                    const float W = (float)(r6_w(q) * r6_bary(q, b));
-                    hvr[b] += W * gr; hvi[b] += W * gi;
-                    hkr[b] += W * gkr; hki[b] += W * gki;
-                    htr[b] += W * gtr; hti[b] += W * gti;
-                }
-            }
-            const float wp = p < 3 ? (float)kW1 : (float)kW2;
-            const float ap = p < 3 ? (float)kA1 : (float)kA2;
-            const float am = p < 3 ? (float)(1.0 - 2.0 * kA1) : (float)(1.0 - 2.0 * kA2);
-            const int pc = p < 3 ? p : p - 3;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const float W = wp * (a == pc ? am : ap);
-#pragma unroll
-                for (int b = 0; b < 3; ++b) {
-                    vr[3 * a + b] += W * hvr[b]; vi[3 * a + b] += W * hvi[b];
-                    kr[3 * a + b] += W * hkr[b]; ki[3 * a + b] += W * hki[b];
-                    tr[3 * a + b] += W * htr[b]; ti[3 * a + b] += W * hti[b];
-                }
-            }
-        }
-        const float scale = X.area * Y.area * (float)kInv4Pi;
-#pragma unroll
-        for (int e = 0; e < 9; ++e) {
-            vr[e] *= scale; vi[e] *= scale; kr[e] *= scale; ki[e] *= scale; tr[e] *= scale; ti[e] *= scale;
-        }
-        // the sum of G over the point pairs is the sum of the V entries (the P1 functions sum to one)
-#pragma unroll
-        for (int e = 0; e < 9; ++e) { sr += vr[e]; si += vi[e]; }
+        if (tame) pair_quadrature_f32<CK, true>(gX[t1], gY[t2], A.k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
+        else pair_quadrature_f32<CK, false>(gX[t1], gY[t2], A.k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
     }
     const TriGeoF &X = gX[t1];
     const TriGeoF &Y = gY[t2];

@@ -57,7 +57,7 @@ struct alignas(8) TriGeoF {
     float n[3];
     float area;
     float curl[3][3];
-    float pad;
+    float rho;          // as TriGeo::rho, rounded up
 };
 
 // Ordered singular pair: x on `tau` (test), y on `sig` (trial); kind = shared
