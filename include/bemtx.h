@@ -164,8 +164,9 @@ bem_status bem_ctx_set_strip_tiles(bem_ctx *ctx, int64_t tiles);
  * the connectivity tables (adjacent-pair classes, locality blocks).  xyz and
  * tri are host arrays, copied.  Limits: at most 2^30 vertices and
  * triangles (BEM_E_ARG); a vertex may be a corner of at most 12 of the 16
- * triangles of one locality block (consecutive triangles in Morton order of
- * their centroids; a valence above 12 can exceed it) and, for the sparse
+ * triangles of one locality block (where a vertex has a valence above 12,
+ * blocks are consecutive triangles in Morton order of their centroids, which
+ * can exceed it; else a bisection of the centroids) and, for the sparse
  * inverse-mass apply, have at most 15 neighbours (BEM_E_MESH otherwise). */
 bem_status bem_mesh_create(bem_ctx *ctx, const double *xyz, int64_t nv, const int32_t *tri, int64_t nt,
                            bem_mesh **out);

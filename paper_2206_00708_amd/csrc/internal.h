@@ -20,7 +20,7 @@ namespace bemtx {
 
 // ---------------------------------------------------------------- layout
 // Triangles are grouped into locality blocks of at most BT consecutive
-// triangles (Morton order of centroids) touching at most SMAX distinct
+// triangles (bisect_order in mesh_prep.cpp) touching at most SMAX distinct
 // vertices; a vertex appears in at most LMAX corners of one block.
 constexpr int BT = 16;
 constexpr int SMAX = 24;
