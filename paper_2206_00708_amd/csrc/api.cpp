@@ -133,10 +133,9 @@ bem_status launch_sym_corrections(bem_problem *p, int mesh, hipStream_t st);
 bem_status ext_form_solve_impl(bem_problem *p, int form, const double *dirs, int nrhs, const bem_solver_opts *opts,
                                void *traces, bem_memspace space, bem_stats *stats);
 bem_status ext_form_matvec_impl(bem_problem *p, int form, const void *x, void *y, int strong, bem_memspace space);
-bem_status launch_field_region(bem_problem *p, int region, int np, const double *pts, const int32_t *dst_index,
-                               const double2 *x_int, const double *dir, double2 *field, DevMem &dens, DevMem &part,
-                               hipStream_t st);
-bem_status launch_field_permute(bem_problem *p, const double2 *x_caller, double2 *x_int, hipStream_t st);
+bem_status launch_field(bem_problem *p, const int np[2], const double *pts, const int32_t *dst, const double2 *x,
+                        const double *dirs, int nrhs, double2 *field, DevMem &xint, DevMem &dens, DevMem &part,
+                        hipStream_t st);
 bem_status launch_winding(const bem_mesh *m, int np, const double *pts, double *w, DevMem &part, hipStream_t st);
 bem_status solve_impl(bem_problem *p, const double *dirs, int nrhs, const bem_solver_opts *opts, void *traces,
                       bem_memspace space, bem_stats *stats);
@@ -953,7 +952,6 @@ bem_status bem_field(bem_problem *p, const double *dirs, int32_t nrhs, const voi
     DevMem dpts, didx, xin, xint, fout, dens, part;
     bem_status s = upload(ctx, dpts, sp);
     if (!s) s = upload(ctx, didx, order);
-    if (!s) s = dev_alloc(ctx, xint, (size_t)n * sizeof(double2));
     if (s) return s;
     const double2 *X = static_cast<const double2 *>(traces);
     if (space == BEM_HOST) {
@@ -964,13 +962,8 @@ bem_status bem_field(bem_problem *p, const double *dirs, int32_t nrhs, const voi
         X = xin.as<double2>();
     }
     double2 *Fo = space == BEM_HOST ? fout.as<double2>() : static_cast<double2 *>(field);
-    for (int r = 0; r < nrhs; ++r) {
-        s = launch_field_permute(p, X + (size_t)r * n, xint.as<double2>(), st);
-        for (int m = 0, off = 0; m < 2 && !s; off += cnt[m], ++m)
-            s = launch_field_region(p, m, cnt[m], dpts.as<double>() + (size_t)3 * off, didx.as<int32_t>() + off,
-                                    xint.as<double2>(), dirs + 3 * r, Fo + (size_t)r * np, dens, part, st);
-        if (s) return s;
-    }
+    s = launch_field(p, cnt, dpts.as<double>(), didx.as<int32_t>(), X, dirs, nrhs, Fo, xint, dens, part, st);
+    if (s) return s;
     if (space == BEM_HOST)
         BEM_HIP(hipMemcpyAsync(field, Fo, (size_t)nrhs * np * sizeof(double2), hipMemcpyDeviceToHost, st));
     BEM_HIP(hipStreamSynchronize(st));

@@ -283,61 +283,6 @@ __device__ inline void tile_slot_sums(int tid, int n1, int n2, int ns1, int ns2,
     test_side(3, 1);
 }
 
-// 1 / sqrt(x) of a positive finite x: the hardware estimate (relative error e
-// below 2^-20) with one third-order step, 1 + e/2 + 3 e^2 / 8 (error below
-// 2^-60); without the library function's handling of 0 and infinity.
-__device__ inline double rsqrt_pos(double x)
-{
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-x * y, y, 1.0);
-    return fma(y * e, fma(e, 0.375, 0.5), y);
-}
-
-// fma(a, b, c) with c in scalar registers (a constant): the compiler's own
-// choice copies c into vector registers first (v_fmac needs its addend
-// there), one instruction more per polynomial step.
-__device__ inline double fma_const(double a, double b, double c)
-{
-    double r;
-    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
-    return r;
-}
-
-// sin and cos of a small angle t: the Taylor series of sin(t)/t and cos t as
-// polynomials in z = t^2, economised by Chebyshev polynomials (Lanczos) on
-// the range of z.  HALF: |t| <= 1/2, degrees 5 and 6, errors below 2e-17 and
-// 1e-19; else |t| <= 1, degree 7, errors below 1e-19 and 2e-18.
-template <bool HALF> __device__ inline void small_sincos(double t, double &s, double &c)
-{
-    const double z = t * t;
-    double ps, pc;
-    if constexpr (HALF) {
-        ps = fma_const(-2.493193700544346e-08, z, 2.7556981496282986e-06);
-        ps = fma_const(ps, z, -0.00019841269403639427);
-        ps = fma_const(ps, z, 0.008333333333076967);
-        ps = fma_const(ps, z, -0.16666666666666116);
-        pc = fma_const(2.077661169102768e-09, z, -2.7556975230704026e-07);
-        pc = fma_const(pc, z, 2.4801586715453357e-05);
-        pc = fma_const(pc, z, -0.0013888888888376136);
-        pc = fma_const(pc, z, 0.04166666666666453);
-    } else {
-        ps = fma_const(-7.535488064487613e-13, z, 1.6057233337039862e-10);
-        ps = fma_const(ps, z, -2.5052093083699724e-08);
-        ps = fma_const(ps, z, 2.7557319152309194e-06);
-        ps = fma_const(ps, z, -0.00019841269841087476);
-        ps = fma_const(ps, z, 0.008333333333333106);
-        ps = fma_const(ps, z, -0.16666666666666666);
-        pc = fma_const(-1.1281052794952459e-11, z, 2.0873682510844006e-09);
-        pc = fma_const(pc, z, -2.755729324310771e-07);
-        pc = fma_const(pc, z, 2.4801587179897263e-05);
-        pc = fma_const(pc, z, -0.0013888888888579293);
-        pc = fma_const(pc, z, 0.0416666666666628);
-    }
-    s = fma(t * z, ps, t);
-    pc = fma(pc, z, -0.5);
-    c = fma(z, pc, 1.0);
-}
-
 // The 6-point rule applied to six values g_0 .. g_5 with the P1 functions:
 // sum over q of w_q lambda_b(q) g_q for b = 0..2.  With the two orbits'
 // barycentric coordinates (a, a, 1 - 2a) it is, up to the factor kR6G,

@@ -1686,13 +1686,15 @@ __global__ __launch_bounds__(256) void mass_reduce_kernel(int ne, int ni, const 
 
 // ---------------------------------------------------- numbering changes
 
-// internal -> caller (dir = 0) or caller -> internal (dir = 1) for an MTF vector
+// internal -> caller (dir = 0) or caller -> internal (dir = 1) for MTF vectors, one after the other (grid y)
 __global__ void permute_vec_kernel(int ne, int ni, const int32_t *__restrict__ pe, const int32_t *__restrict__ pi,
                                    const double2 *__restrict__ src, double2 *__restrict__ dst, int dir)
 {
     const int u = blockIdx.x * blockDim.x + threadIdx.x;
     const int n = 2 * ne + 2 * ni;
     if (u >= n) return;
+    src += (int64_t)blockIdx.y * n;
+    dst += (int64_t)blockIdx.y * n;
     int base, loc;
     const int32_t *perm;
     if (u < 2 * ne) { base = u < ne ? 0 : ne; loc = u - base; perm = pe; }
@@ -1700,6 +1702,19 @@ __global__ void permute_vec_kernel(int ne, int ni, const int32_t *__restrict__ p
     const int in = base + perm[loc];
     if (dir == 0) dst[u] = src[in];
     else dst[in] = src[u];
+}
+
+constexpr int PERM_RUNS = 32768;   // vectors per launch, at most (grid y)
+
+bem_status launch_to_internal(const bem_problem *p, const double2 *x_caller, double2 *x_int, int nrhs, hipStream_t st)
+{
+    const int ne = (int)p->ext->h.nv, ni = (int)p->inte->h.nv, n = 2 * ne + 2 * ni;
+    for (int r0 = 0; r0 < nrhs; r0 += PERM_RUNS)
+        hipLaunchKernelGGL(permute_vec_kernel, dim3((n + 255) / 256, std::min(PERM_RUNS, nrhs - r0)), dim3(256), 0, st, ne,
+                           ni, p->ext->d.perm.as<int32_t>(), p->inte->d.perm.as<int32_t>(), x_caller + (int64_t)r0 * n,
+                           x_int + (int64_t)r0 * n, 1);
+    BEM_HIP(hipGetLastError());
+    return BEM_OK;
 }
 
 template <class C2>
