@@ -383,6 +383,18 @@ static bem_status launch_minv_csr_any(bem_problem *p, int nv, int mesh, hipStrea
     }
 }
 
+struct KrylovState {
+    int done;       // 1 once the residual estimate met tol (or the step limit was reached)
+    int iters;      // Arnoldi steps taken
+    double resid;   // |g_{j+1}| / beta0
+    double beta0;
+    double tol;     // relative residual target of this run
+};
+
+constexpr size_t MASS_LDS_MAX = size_t(144) << 10;   // of the 160 KB of a compute unit
+template <class MT>
+__global__ void mass_rows_kernel(int, int, int, const MT *, const MT *, const double2 *, double2 *, const KrylovState *);
+
 bem_status launch_mass_inverse(bem_problem *p, int mesh, hipStream_t st)
 {
     const bem_mesh *m = mesh == 0 ? p->ext : p->inte;
@@ -390,6 +402,9 @@ bem_status launch_mass_inverse(bem_problem *p, int mesh, hipStream_t st)
     if (nv > 16 * 1024) return set_error(BEM_E_UNSUPPORTED, "mass inverse: more than 16384 vertices on one mesh");
     const bool f32 = p->prec == BEM_C64_MIXED;
     const size_t bytes = (size_t)nv * minv_ld(nv, f32) * (f32 ? sizeof(float) : sizeof(double));
+    BEM_HIP(hipFuncSetAttribute(f32 ? reinterpret_cast<const void *>(&mass_rows_kernel<float>)
+                                    : reinterpret_cast<const void *>(&mass_rows_kernel<double>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)MASS_LDS_MAX));
     bem_status s = dev_alloc(p->ctx, p->Minv[mesh], bytes, st);
     if (s) return s;
     // padding columns must read as zero (vector loads cover them)
@@ -427,14 +442,6 @@ bem_status launch_mass_inverse(bem_problem *p, int mesh, hipStream_t st)
 }
 
 // --------------------------------------------------------------- mat-vec
-
-struct KrylovState {
-    int done;       // 1 once the residual estimate met tol (or the step limit was reached)
-    int iters;      // Arnoldi steps taken
-    double resid;   // |g_{j+1}| / beta0
-    double beta0;
-    double tol;     // relative residual target of this run
-};
 
 // Element strides between the work arrays of independent GMRES runs that
 // advance together (run r = a grid index); all zero for a single run.
@@ -508,9 +515,16 @@ template <> struct Cx<double> { using T = double2; };
 // together the row's 2 KB), for complex64 two adjacent columns (one 16-byte
 // load).  The wider rows of the tile keep DRAM accesses in longer runs than
 // 64-column tiles do.
-template <class E> constexpr int sym_tile() { return 128; }
 constexpr int SYM_TS_MIN = 64;   // the smaller tile edge the tuner may pick (sizes the partial sums)
 __host__ __device__ inline int sym_ntile(int nv, int ts) { return (nv + ts - 1) / ts; }
+// Below one 128-column tile pair per compute unit the product waits on
+// latency, and 64-column tiles (four times the workgroups, four rows in
+// flight) are always the faster ones: 162 + 162 vertices 35 -> 16.7 us.
+inline bool sym_small(int ne, int ni)
+{
+    const int64_t te = sym_ntile(ne, 128), ti = sym_ntile(ni, 128);
+    return te * (te + 1) / 2 + ti * (ti + 1) / 2 < 256;
+}
 
 // task t -> tile pair (a, b), a <= b, in row-major order of the upper triangle
 __device__ inline void sym_pair(int64_t t, int nt, int &a, int &b)
@@ -651,45 +665,57 @@ __global__ __launch_bounds__(256) void mtf_sym_tile_kernel(MtfArgs A, const doub
 #pragma unroll
     for (int u = 0; u < CPL; ++u) { vb[u] = svb[colof(u)]; wb[u] = swb[colof(u)]; va[u] = sva[colof(u)]; }
     CAcc<R> c1b[CPL], c2b[CPL], c2a[CPL];
+    // ROWS rows' loads in flight per wave.  With 128-column tiles the other
+    // workgroups of a compute unit cover a row's latency (unrolling changed
+    // nothing); 64-column tiles serve the small meshes, whose few workgroups
+    // otherwise wait out one memory latency per row.
+    constexpr int ROWS = TS == 64 ? 4 : 1;
 #pragma unroll 1
-    for (int rr = 0; rr < RPW; ++rr) {
-        const int r = wave * RPW + rr;
-        const int i = a * TS + r, ib = b * TS + r;
-        C kab[CPL], vab[CPL], dab[CPL], kba[CPL];
-        ld_cols<E, C, CPL>(Km, ld, i, j0, nv, kab);
-        ld_cols<E, C, CPL>(Vm, ld, i, j0, nv, vab);
-        ld_cols<E, C, CPL>(Dm, ld, i, j0, nv, dab);
-        if (!diag) ld_cols<E, C, CPL>(Km, ld, ib, ja0, nv, kba);
-        else
+    for (int r0 = 0; r0 < RPW; r0 += ROWS) {
+        C kabs[ROWS][CPL], vabs[ROWS][CPL], dabs[ROWS][CPL], kbas[ROWS][CPL];
 #pragma unroll
-            for (int u = 0; u < CPL; ++u) kba[u] = zero;
-        const C wi = swa[r], vi = sva[r], wbr = swb[r];
-        CAcc<R> y1, y2, y1b;
+        for (int q = 0; q < ROWS; ++q) {
+            const int i = a * TS + wave * RPW + r0 + q, ib = b * TS + wave * RPW + r0 + q;
+            ld_cols<E, C, CPL>(Km, ld, i, j0, nv, kabs[q]);
+            ld_cols<E, C, CPL>(Vm, ld, i, j0, nv, vabs[q]);
+            ld_cols<E, C, CPL>(Dm, ld, i, j0, nv, dabs[q]);
+            if (!diag) ld_cols<E, C, CPL>(Km, ld, ib, ja0, nv, kbas[q]);
+            else
 #pragma unroll
-        for (int u = 0; u < CPL; ++u) {
-            const int c = colof(u);
-            // rows of tile a: y1 -= K v, y1 += V w, y2 += D v (V, D on and above the diagonal)
-            y1.msub(kab[u], vb[u]);
-            if (!diag || c >= r) {
-                y1.mac(vab[u], wb[u]);
-                y2.mac(dab[u], vb[u]);
-            }
-            // rows of tile b (column c): y2 += K^T w; y1 += V^T w, y2 += D^T v strictly above the diagonal
-            c2b[u].mac(kab[u], wi);
-            if (!diag || c > r) {
-                c1b[u].mac(vab[u], wi);
-                c2b[u].mac(dab[u], vi);
-            }
-            // tile (b, a) of K: rows of b: y1 -= K v_a; rows of a (column c): y2 += K^T w_b
-            y1b.msub(kba[u], va[u]);
-            c2a[u].mac(kba[u], wbr);
+                for (int u = 0; u < CPL; ++u) kbas[q][u] = zero;
         }
-        const R s0 = wsum63(y1.x), s1 = wsum63(y1.y), s2 = wsum63(y2.x), s3 = wsum63(y2.y), s4 = wsum63(y1b.x),
-                s5 = wsum63(y1b.y);
-        if (lane == 63) {
-            rowres[0][r] = C{s0, s1};
-            rowres[1][r] = C{s2, s3};
-            rowres[2][r] = C{s4, s5};
+#pragma unroll
+        for (int q = 0; q < ROWS; ++q) {
+            const int r = wave * RPW + r0 + q;
+            const C (&kab)[CPL] = kabs[q], (&vab)[CPL] = vabs[q], (&dab)[CPL] = dabs[q], (&kba)[CPL] = kbas[q];
+            const C wi = swa[r], vi = sva[r], wbr = swb[r];
+            CAcc<R> y1, y2, y1b;
+#pragma unroll
+            for (int u = 0; u < CPL; ++u) {
+                const int c = colof(u);
+                // rows of tile a: y1 -= K v, y1 += V w, y2 += D v (V, D on and above the diagonal)
+                y1.msub(kab[u], vb[u]);
+                if (!diag || c >= r) {
+                    y1.mac(vab[u], wb[u]);
+                    y2.mac(dab[u], vb[u]);
+                }
+                // rows of tile b (column c): y2 += K^T w; y1 += V^T w, y2 += D^T v strictly above the diagonal
+                c2b[u].mac(kab[u], wi);
+                if (!diag || c > r) {
+                    c1b[u].mac(vab[u], wi);
+                    c2b[u].mac(dab[u], vi);
+                }
+                // tile (b, a) of K: rows of b: y1 -= K v_a; rows of a (column c): y2 += K^T w_b
+                y1b.msub(kba[u], va[u]);
+                c2a[u].mac(kba[u], wbr);
+            }
+            const R s0 = wsum63(y1.x), s1 = wsum63(y1.y), s2 = wsum63(y2.x), s3 = wsum63(y2.y), s4 = wsum63(y1b.x),
+                    s5 = wsum63(y1b.y);
+            if (lane == 63) {
+                rowres[0][r] = C{s0, s1};
+                rowres[1][r] = C{s2, s3};
+                rowres[2][r] = C{s4, s5};
+            }
         }
     }
 #pragma unroll
@@ -927,6 +953,84 @@ __global__ __launch_bounds__(256) void mass_combine_kernel(int ne, int ni, const
     double2 *za = ext ? z : z + 2 * ne;
     za[i] = make_double2(ar, ai);
     za[i + nv] = make_double2(br, bi);
+}
+
+// z = M^-1 y with both vectors of a mesh staged whole in LDS: a workgroup of 16
+// waves owns `rows` rows (the two meshes' rows spread over one workgroup per
+// compute unit), a wave takes a quarter of a row at a time (quarters interleaved
+// by steps of 64 lanes), and the four quarters are added in order.  Bound by
+// the stream of M^-1; against the split-column form above (three column chunks
+// per row at 2,562 vertices, whose partial sums a second kernel adds) it
+// stages each vector once per compute unit and needs no second launch:
+// 2,562 + 1,962 vertices FP64 20.8 + 4.8 -> 21.9 us.  For vectors that fit LDS
+// (mass_rows_fit); dynamic LDS: mass_rows_lds bytes.
+constexpr int MASS_WAVES = 16;
+inline int mass_rows_per_wg(int ne, int ni) { return std::max(1, (ne + ni + 253) / 254); }
+inline size_t mass_rows_lds(int ne, int ni)
+{
+    const size_t nv = (std::max(ne, ni) + 3) & ~3;
+    return 2 * nv * sizeof(double2) + (size_t)4 * mass_rows_per_wg(ne, ni) * sizeof(double4);
+}
+inline bool mass_rows_fit(int ne, int ni) { return mass_rows_lds(ne, ni) <= MASS_LDS_MAX; }
+
+template <class MT>
+__global__ __launch_bounds__(64 * MASS_WAVES) void mass_rows_kernel(int ne, int ni, int rows, const MT *__restrict__ Me_inv,
+                                                                    const MT *__restrict__ Mi_inv,
+                                                                    const double2 *__restrict__ y,
+                                                                    double2 *__restrict__ z,
+                                                                    const KrylovState *__restrict__ st)
+{
+    constexpr bool f32 = sizeof(MT) == 4;
+    constexpr int VW = f32 ? 4 : 2;   // entries per lane load (16 bytes)
+    if (st && st->done) return;
+    extern __shared__ double2 sh[];
+    const int be = (ne + rows - 1) / rows;
+    const bool ext = (int)blockIdx.x < be;
+    const int nv = ext ? ne : ni, nvp = (nv + 3) & ~3;
+    const int i0 = (ext ? blockIdx.x : blockIdx.x - be) * rows, nr = min(rows, nv - i0);
+    const double2 *ya = ext ? y : y + 2 * ne;
+    double4 *res = reinterpret_cast<double4 *>(sh + 2 * nvp);
+    for (int t = threadIdx.x; t < nvp; t += 64 * MASS_WAVES) {
+        sh[t] = t < nv ? ya[t] : make_double2(0, 0);
+        sh[nvp + t] = t < nv ? ya[nv + t] : make_double2(0, 0);
+    }
+    __syncthreads();
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const MT *M = (ext ? Me_inv : Mi_inv) + (int64_t)i0 * minv_ld(nv, f32);
+    for (int u = wave; u < 4 * nr; u += MASS_WAVES) {
+        const MT *row = M + (int64_t)(u >> 2) * minv_ld(nv, f32);
+        double ar = 0, ai = 0, br = 0, bi = 0;
+#pragma unroll 4
+        for (int j = VW * (64 * (u & 3) + lane); j < nv; j += VW * 256) {   // padding columns of the row: zero
+            double m[VW];
+            if constexpr (f32) {
+                const v4f q = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(row + j));
+                m[0] = q.x; m[1] = q.y; m[2] = q.z; m[3] = q.w;
+            } else {
+                const v2d q = __builtin_nontemporal_load(reinterpret_cast<const v2d *>(row + j));
+                m[0] = q.x; m[1] = q.y;
+            }
+#pragma unroll
+            for (int e = 0; e < VW; ++e) {
+                const double2 a = sh[j + e], b = sh[nvp + j + e];
+                ar += m[e] * a.x; ai += m[e] * a.y; br += m[e] * b.x; bi += m[e] * b.y;
+            }
+        }
+        ar = wave_sum(ar); ai = wave_sum(ai); br = wave_sum(br); bi = wave_sum(bi);
+        if (lane == 0) res[u] = make_double4(ar, ai, br, bi);
+    }
+    __syncthreads();
+    double2 *za = ext ? z : z + 2 * ne;
+    for (int t = threadIdx.x; t < nr; t += 64 * MASS_WAVES) {
+        double4 s = res[4 * t];
+#pragma unroll
+        for (int q = 1; q < 4; ++q) {
+            const double4 v = res[4 * t + q];
+            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+        }
+        za[i0 + t] = make_double2(s.x, s.y);
+        za[i0 + t + nv] = make_double2(s.z, s.w);
+    }
 }
 
 // ---- sparse inverse-mass apply: Chebyshev iteration on diag(M)^-1 M, whose
@@ -1571,23 +1675,29 @@ __device__ inline bool run_active(const KrylovState *st, int r, int R)
     return r < R && !(st && st[r].done);
 }
 
-// Bt_v, Bt_w [128][kld] of one mesh from its [v; w] part of every run;
-// grid (ceil(op_ld(nv) / 256), BLOCK_RHS)
-__global__ __launch_bounds__(256) void pack_ops_kernel(int nv, int kld, int R, const double2 *__restrict__ X,
-                                                       int64_t xstride, int voff, const KrylovState *__restrict__ st,
-                                                       float *__restrict__ Btv, float *__restrict__ Btw)
+// Bt_v, Bt_w [columns][kld] of both meshes from the [v; w] parts of every run;
+// grid (packed_blocks(ne) + packed_blocks(ni), runs the product's columns hold)
+struct PackArgs {
+    float *v[2], *w[2];
+    int nv[2], kld[2];
+};
+inline int packed_blocks(int nv) { return (int)((op_ld(nv) + 255) / 256); }
+__global__ __launch_bounds__(256) void pack_ops_kernel(PackArgs P, int nb0, int R, const double2 *__restrict__ X,
+                                                       int64_t xstride, const KrylovState *__restrict__ st)
 {
     const int r = blockIdx.y;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    const int m = (int)blockIdx.x < nb0 ? 0 : 1;
+    const int j = (blockIdx.x - (m ? nb0 : 0)) * blockDim.x + threadIdx.x;
+    const int nv = P.nv[m], kld = P.kld[m];
     if (2 * j >= kld) return;
     double2 v = make_double2(0, 0), w = v;
     if (j < nv && run_active(st, r, R)) {
-        const double2 *x = X + r * xstride + voff;
+        const double2 *x = X + r * xstride + (m ? 2 * P.nv[0] : 0);
         v = x[j];
         w = x[nv + j];
     }
-    float *a0 = Btv + (int64_t)(2 * r) * kld + 2 * j, *a1 = a0 + kld;
-    float *b0 = Btw + (int64_t)(2 * r) * kld + 2 * j, *b1 = b0 + kld;
+    float *a0 = P.v[m] + (int64_t)(2 * r) * kld + 2 * j, *a1 = a0 + kld;
+    float *b0 = P.w[m] + (int64_t)(2 * r) * kld + 2 * j, *b1 = b0 + kld;
     *reinterpret_cast<float2 *>(a0) = make_float2((float)v.x, -(float)v.y);
     *reinterpret_cast<float2 *>(a1) = make_float2((float)v.y, (float)v.x);
     *reinterpret_cast<float2 *>(b0) = make_float2((float)w.x, -(float)w.y);
@@ -1599,25 +1709,38 @@ __global__ __launch_bounds__(256) void pack_ops_kernel(int nv, int kld, int R, c
 struct BlockC {
     const float *C[2][4];
     int nk[2];
+    float *Btm[2];   // right-hand matrices of the inverse-mass product (null: y rows instead)
+    int kldm[2];
 };
 
 // y rows of every run = sums of the K-chunk partials (fixed order) with the
-// block signs of Eq. "mtf:discrete" plus the mortar coupling in FP64;
-// grid (ceil((ne + ni) / 256), R), one thread per row and run.
+// block signs of Eq. "mtf:discrete" plus the mortar coupling in FP64.  Where
+// an inverse-mass product follows, a row goes straight into its right-hand
+// matrix: columns 4r .. 4r + 3 = Re y1, Im y1, Re y2, Im y2 of run r (their
+// padding is zeroed once; a finished run's columns are computed and not
+// read).  Grid (ceil((ne + ni) / 64), R), four lanes per row and run: each
+// takes every fourth chunk and mortar entry, and a fixed tree adds them (a
+// thread per row waited out one memory latency per entry).
+__device__ inline double quad_sum(double v)   // sum over the four lanes of a quad, in every lane
+{
+    v += dpp_mov<0xB1>(v);   // lanes 1, 0, 3, 2
+    v += dpp_mov<0x4E>(v);   // lanes 2, 3, 0, 1
+    return v;
+}
 __global__ __launch_bounds__(256) void block_combine_kernel(MtfArgs A, BlockC bc, int R, const double2 *__restrict__ X,
                                                             int64_t xstride, double2 *__restrict__ Y, int64_t ystride,
                                                             const KrylovState *__restrict__ st)
 {
     const int r = blockIdx.y;
     if (!run_active(st, r, R)) return;
-    const int row = blockIdx.x * blockDim.x + threadIdx.x;
-    if (row >= A.ne + A.ni) return;
+    const int row = blockIdx.x * 64 + (threadIdx.x >> 2), l = threadIdx.x & 3;
+    if (row >= A.ne + A.ni) return;   // whole quads
     const bool ext = row < A.ne;
     const int mi = ext ? 0 : 1;
     const int i = ext ? row : row - A.ne;
     const int nv = ext ? A.ne : A.ni;
     double ar = 0, ai = 0, br = 0, bi = 0;
-    for (int kc = 0; kc < bc.nk[mi]; ++kc) {
+    for (int kc = l; kc < bc.nk[mi]; kc += 4) {
         const int64_t o0 = ((int64_t)kc * 128 + 2 * r) * nv + i, o1 = o0 + nv;
         ar += (double)bc.C[mi][0][o0] - (double)bc.C[mi][1][o0];
         ai += (double)bc.C[mi][0][o1] - (double)bc.C[mi][1][o1];
@@ -1633,35 +1756,26 @@ __global__ __launch_bounds__(256) void block_combine_kernel(MtfArgs A, BlockC bc
     const double2 *cwp = cv + nother;
     const double fv = ext ? A.c_ext_v : A.c_int_v, fw = ext ? A.c_ext_w : A.c_int_w;
     double sr = 0, si = 0, tr = 0, ti = 0;
-    for (int q = pp[i]; q < pp[i + 1]; ++q) {
+    const int q1 = pp[i + 1];
+#pragma unroll 2
+    for (int q = pp[i] + l; q < q1; q += 4) {
         const double pvq = pv[q];
         const double2 a = cv[pc[q]], b = cwp[pc[q]];
         sr += pvq * a.x; si += pvq * a.y; tr += pvq * b.x; ti += pvq * b.y;
     }
-    double2 *y = Y + r * ystride + (ext ? 0 : 2 * A.ne);
-    y[i] = make_double2(ar + fv * sr, ai + fv * si);
-    y[i + nv] = make_double2(br + fw * tr, bi + fw * ti);
-}
-
-// Bt [4 BLOCK_RHS][kld] of one mesh for the inverse-mass product: column
-// 4r + q = Re y1, Im y1, Re y2, Im y2 of run r; grid (ceil(kld / 256), 4 BLOCK_RHS)
-__global__ __launch_bounds__(256) void pack_mass_kernel(int nv, int kld, int R, const double2 *__restrict__ Y,
-                                                        int64_t ystride, int yoff, const KrylovState *__restrict__ st,
-                                                        float *__restrict__ Bt)
-{
-    const int c = blockIdx.y, r = c >> 2, q = c & 3;
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= kld) return;
-    float val = 0.f;
-    if (k < nv && run_active(st, r, R)) {
-        const double2 y = Y[r * ystride + yoff + (q >= 2 ? nv : 0) + k];
-        val = (float)((q & 1) ? y.y : y.x);
+    ar = quad_sum(ar + fv * sr);
+    ai = quad_sum(ai + fv * si);
+    br = quad_sum(br + fw * tr);
+    bi = quad_sum(bi + fw * ti);
+    if (bc.Btm[0]) {
+        bc.Btm[mi][(int64_t)(4 * r + l) * bc.kldm[mi] + i] = (float)(l == 0 ? ar : l == 1 ? ai : l == 2 ? br : bi);
+        return;
     }
-    Bt[(int64_t)c * kld + k] = val;
+    if (l < 2) Y[r * ystride + (ext ? 0 : 2 * A.ne) + i + (l ? nv : 0)] = l ? make_double2(br, bi) : make_double2(ar, ai);
 }
 
 // z rows of every run from the inverse-mass partials [nk][ccols][N] of each mesh;
-// grid (ceil((ne + ni) / 256), R)
+// grid (ceil((ne + ni) / 64), R), a lane for each of the four real columns of a row
 __global__ __launch_bounds__(256) void mass_reduce_kernel(int ne, int ni, const float *__restrict__ Ce,
                                                           const float *__restrict__ Ci, int nke, int nki, int ccols,
                                                           int R, double2 *__restrict__ Z, int64_t zstride,
@@ -1669,19 +1783,18 @@ __global__ __launch_bounds__(256) void mass_reduce_kernel(int ne, int ni, const 
 {
     const int r = blockIdx.y;
     if (!run_active(st, r, R)) return;
-    const int row = blockIdx.x * blockDim.x + threadIdx.x;
+    const int row = blockIdx.x * 64 + (threadIdx.x >> 2), l = threadIdx.x & 3;
     if (row >= ne + ni) return;
     const bool ext = row < ne;
     const int i = ext ? row : row - ne;
     const int nv = ext ? ne : ni;
-    const float *C = ext ? Ce : Ci;
+    const float *C = (ext ? Ce : Ci) + (int64_t)(4 * r + l) * nv + i;
     const int nk = ext ? nke : nki;
-    double s[4] = {0, 0, 0, 0};
-    for (int kc = 0; kc < nk; ++kc)
-        for (int q = 0; q < 4; ++q) s[q] += (double)C[((int64_t)kc * ccols + 4 * r + q) * nv + i];
-    double2 *z = Z + r * zstride + (ext ? 0 : 2 * ne);
-    z[i] = make_double2(s[0], s[1]);
-    z[i + nv] = make_double2(s[2], s[3]);
+    double s = 0;
+#pragma unroll 4
+    for (int kc = 0; kc < nk; ++kc) s += (double)C[(int64_t)kc * ccols * nv];
+    double *z = reinterpret_cast<double *>(Z + r * zstride + (ext ? 0 : 2 * ne) + i + (l & 2 ? nv : 0));
+    z[l & 1] = s;
 }
 
 // ---------------------------------------------------- numbering changes
@@ -1721,10 +1834,12 @@ template <class C2>
 __global__ void permute_mat_kernel(int nv, const int32_t *__restrict__ perm, const C2 *__restrict__ src,
                                    C2 *__restrict__ dst)
 {
-    const int iu = blockIdx.y;
-    const int ju = blockIdx.x * blockDim.x + threadIdx.x;
-    if (ju >= nv) return;
-    dst[(int64_t)iu * nv + ju] = src[(int64_t)perm[iu] * op_ld(nv) + perm[ju]];
+    // one workgroup per row: the scattered reads of a row stay in one XCD's L2
+    const int iu = blockIdx.x;
+    const C2 *s = src + (int64_t)perm[iu] * op_ld(nv);
+    C2 *d = dst + (int64_t)iu * nv;
+#pragma unroll 4
+    for (int ju = threadIdx.x; ju < nv; ju += 256) d[ju] = s[perm[ju]];
 }
 
 bem_status resolve_assembly_timing(bem_problem *p);
@@ -1734,7 +1849,7 @@ bem_status permute_matrix_out(const bem_problem *p, int mesh, const void *src, v
 {
     const bem_mesh *m = mesh == 0 ? p->ext : p->inte;
     const int nv = (int)m->h.nv;
-    const dim3 grid((nv + 255) / 256, nv);
+    const dim3 grid(nv);
     if (p->prec == BEM_C128)
         hipLaunchKernelGGL(permute_mat_kernel<double2>, grid, dim3(256), 0, p->ctx->stream, nv,
                            m->d.perm.as<int32_t>(), static_cast<const double2 *>(src), static_cast<double2 *>(dst));
@@ -1774,7 +1889,7 @@ MtfArgs make_args(const bem_problem *p)
     A.c_ext_w = 0.5 * p->rho_ext / p->rho_int;
     A.c_int_v = -0.5;
     A.c_int_w = -0.5 * p->rho_int / p->rho_ext;
-    A.sym_ts = p->mtf_ts ? p->mtf_ts : (p->prec == BEM_C128 ? sym_tile<double2>() : sym_tile<float2>());
+    A.sym_ts = p->mtf_ts ? p->mtf_ts : (sym_small(A.ne, A.ni) ? 64 : 128);
     A.no_mortar = 0;
     const bem_mesh *ms[2] = {p->ext, p->inte};
     for (int m = 0; m < 2; ++m) {
@@ -1868,6 +1983,29 @@ bem_status cheb_apply(const bem_problem *p, int part0, int np, int64_t base0, in
     return BEM_OK;
 }
 
+// z = blockdiag(M, M)^-1 y of the meshes with ne and ni vertices (0: without that mesh) by the dense inverses
+template <class MT>
+bem_status mass_dense_apply(const bem_problem *p, int ne, int ni, const double2 *y, double2 *z, double4 *part,
+                            const KrylovState *kst)
+{
+    hipStream_t st = p->ctx->stream;
+    const MT *me = p->Minv[0].as<MT>(), *mi = p->Minv[1].as<MT>();
+    KTimer kt(p->ctx, K_MASS_APPLY);
+    if (mass_rows_fit(ne, ni)) {
+        const int rows = mass_rows_per_wg(ne, ni);
+        launch_k(kt, mass_rows_kernel<MT>, dim3((ne + rows - 1) / rows + (ni + rows - 1) / rows), dim3(64 * MASS_WAVES),
+                 mass_rows_lds(ne, ni), st, ne, ni, rows, me, mi, y, z, kst);
+        BEM_HIP(hipGetLastError());
+        return BEM_OK;
+    }
+    constexpr int RW = sizeof(MT) == 8 ? MASS_RW64 : MASS_RW32;
+    launch_k(kt, mass_apply_part_kernel<MT, RW>, split_grid(ne, ni, MASS_CW_MAX, RW), dim3(256), 0, st, ne, ni, me, mi, y,
+             part, kst);
+    hipLaunchKernelGGL(mass_combine_kernel, dim3((ne + ni + 255) / 256), dim3(256), 0, st, ne, ni, part, z, kst);
+    BEM_HIP(hipGetLastError());
+    return BEM_OK;
+}
+
 // z = blockdiag(M_e, M_e, M_i, M_i)^-1 y; K: Chebyshev steps of the sparse
 // form (0: cheb_steps)
 bem_status apply_Minv(const bem_problem *p, const double2 *y, double2 *z, double4 *part, const KrylovState *kst,
@@ -1880,18 +2018,8 @@ bem_status apply_Minv(const bem_problem *p, const double2 *y, double2 *z, double
         return cheb_apply(p, 0, p->cheb.nparts[0] + p->cheb.nparts[1], 0, 2 * ne, n, y, 0, z, 0,
                           reinterpret_cast<double2 *>(part), 6 * n, 1, kst, K > 0 ? K : cheb_steps(p));
     }
-    {
-        KTimer kt(p->ctx, K_MASS_APPLY);
-        if (p->prec == BEM_C128)
-            launch_k(kt, mass_apply_part_kernel<double, MASS_RW64>, split_grid(ne, ni, MASS_CW_MAX, MASS_RW64),
-                     dim3(256), 0, st, ne, ni, p->Minv[0].as<double>(), p->Minv[1].as<double>(), y, part, kst);
-        else
-            launch_k(kt, mass_apply_part_kernel<float, MASS_RW32>, split_grid(ne, ni, MASS_CW_MAX, MASS_RW32),
-                     dim3(256), 0, st, ne, ni, p->Minv[0].as<float>(), p->Minv[1].as<float>(), y, part, kst);
-    }
-    hipLaunchKernelGGL(mass_combine_kernel, dim3((ne + ni + 255) / 256), dim3(256), 0, st, ne, ni, part, z, kst);
-    BEM_HIP(hipGetLastError());
-    return BEM_OK;
+    return p->prec == BEM_C128 ? mass_dense_apply<double>(p, ne, ni, y, z, part, kst)
+                               : mass_dense_apply<float>(p, ne, ni, y, z, part, kst);
 }
 
 // y = A x (weak form); z = M^-1 y when `strong`.  Complex64 operators are
@@ -1937,7 +2065,13 @@ bem_status mtf_tune(bem_problem *p, const double2 *x, double2 *y, double4 *part)
                             std::to_string(tune_class(p->ext->h.nv)) + ":i" + std::to_string(tune_class(p->inte->h.nv));
     hipStream_t st = p->ctx->stream;
     std::vector<int> v;
+    const bool small = sym_small((int)p->ext->h.nv, (int)p->inte->h.nv);
+    auto valid = [&](const std::vector<int> &q) { return q.size() == 1 && (q[0] == 64 || (q[0] == 128 && !small)); };
     bem_status s = tuned(key, v, [&](std::vector<int> &out) -> bem_status {
+        if (small) {
+            out = {64};
+            return BEM_OK;
+        }
         hipEvent_t e0, e1;
         BEM_HIP(hipEventCreate(&e0));
         BEM_HIP(hipEventCreate(&e1));
@@ -1962,9 +2096,9 @@ bem_status mtf_tune(bem_problem *p, const double2 *x, double2 *y, double4 *part)
         }
         out = {pick};
         return BEM_OK;
-    });
+    }, valid);
     if (s) return s;
-    p->mtf_ts = v.size() == 1 && (v[0] == 64 || v[0] == 128) ? v[0] : 128;
+    p->mtf_ts = valid(v) ? v[0] : 128;
     return BEM_OK;
 }
 
@@ -2035,14 +2169,7 @@ bem_status apply_Minv_mesh(const bem_problem *p, int mesh, const double2 *y, dou
         return cheb_apply(p, mesh == 0 ? 0 : p->cheb.nparts[0], p->cheb.nparts[mesh], 0, 0, wn, y, 0, z, 0,
                           reinterpret_cast<double2 *>(part), 6 * wn, 1, kst, cheb_steps(p));
     }
-    {
-        KTimer kt(p->ctx, K_MASS_APPLY);
-        launch_k(kt, mass_apply_part_kernel<double, MASS_RW64>, split_grid(ne, ni, MASS_CW_MAX, MASS_RW64), dim3(256),
-                 0, st, ne, ni, p->Minv[0].as<double>(), p->Minv[1].as<double>(), y, part, kst);
-    }
-    hipLaunchKernelGGL(mass_combine_kernel, dim3((ne + ni + 255) / 256), dim3(256), 0, st, ne, ni, part, z, kst);
-    BEM_HIP(hipGetLastError());
-    return BEM_OK;
+    return mass_dense_apply<double>(p, ne, ni, y, z, part, kst);
 }
 
 enum ExtForm { FORM_PMCHWT = 1, FORM_HCN = 2 };   // exterior formulations on [v; w] of the exterior mesh
@@ -2264,6 +2391,12 @@ constexpr int GEMM_MAX_SPLIT = 8;   // K chunks per GEMM segment, at most
 int kchunk_for(int K, int nk, int kst = 32) { return ((K + nk - 1) / nk + kst - 1) / kst * kst; }
 int nchunks(int K, int kc) { return (K + kc - 1) / kc; }
 
+__global__ void zero_kernel(int64_t n, double2 *__restrict__ x)
+{
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r < n) x[r] = make_double2(0, 0);
+}
+
 bem_status block_alloc(bem_problem *p, BlockBufs &bb)
 {
     bem_ctx *ctx = p->ctx;
@@ -2285,6 +2418,13 @@ bem_status block_alloc(bem_problem *p, BlockBufs &bb)
     }
     bem_status s = dev_alloc(ctx, bb.cop, cop * sizeof(float));
     if (!s) s = dev_alloc(ctx, bb.cm, cm * sizeof(float));
+    if (!s && p->mass_dense)   // their padding stays zero (block_combine_kernel writes the rows only)
+        for (int m = 0; m < 2; ++m) {
+            const int64_t nf2 = (int64_t)4 * BLOCK_RHS * minv_ld(nv[m], true) / 4;   // 16-byte units (rows: multiples of 32)
+            hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((nf2 + 255) / 256)), dim3(256), 0, ctx->stream, nf2,
+                               bb.btm[m].as<double2>());
+            BEM_HIP(hipGetLastError());
+        }
     if (!s && p->mass_sparse && !p->mass_dense)
         s = dev_alloc(ctx, bb.chw, (size_t)6 * BLOCK_RHS * (2 * nv[0] + 2 * nv[1]) * sizeof(double2));
     return s;
@@ -2487,11 +2627,18 @@ bem_status block_apply(bem_problem *p, const MtfArgs &A, BlockBufs &bb, int R, c
     bem_status s = block_tune(p, bb, 0, R, nk_ops, kst_ops);
     if (!s && strong && p->mass_dense) s = block_tune(p, bb, 1, R, nk_mass, kst_mass);
     if (s) return s;
+    int nt, ncb;
+    gemm_width(2 * R, nt, ncb);
+    PackArgs P;
     for (int m = 0; m < 2; ++m) {
-        const int kop = 2 * (int)op_ld(nv[m]);
-        hipLaunchKernelGGL(pack_ops_kernel, dim3((int)((op_ld(nv[m]) + 255) / 256), BLOCK_RHS), dim3(256), 0, st, nv[m],
-                           kop, R, X, xstride, m == 0 ? 0 : 2 * A.ne, kst, bb.btv[m].as<float>(), bb.btw[m].as<float>());
+        P.v[m] = bb.btv[m].as<float>();
+        P.w[m] = bb.btw[m].as<float>();
+        P.nv[m] = nv[m];
+        P.kld[m] = 2 * (int)op_ld(nv[m]);
     }
+    const int nb0 = packed_blocks(nv[0]);
+    hipLaunchKernelGGL(pack_ops_kernel, dim3(nb0 + packed_blocks(nv[1]), 16 * nt), dim3(256), 0, st, P, nb0, R, X, xstride,
+                       kst);
     BEM_HIP(hipGetLastError());
     GemmArgs G = ops_gemm_args(p, bb, nk_ops, R, kst, kst_ops);
     s = launch_gemm_f32(p->ctx, G, st, K_BLOCK_GEMM);
@@ -2500,8 +2647,10 @@ bem_status block_apply(bem_problem *p, const MtfArgs &A, BlockBufs &bb, int R, c
     for (int m = 0; m < 2; ++m) {
         for (int o = 0; o < 4; ++o) bc.C[m][o] = G.seg[4 * m + o].C;
         bc.nk[m] = nchunks(G.seg[4 * m].K, G.seg[4 * m].kchunk);
+        bc.Btm[m] = strong && p->mass_dense ? bb.btm[m].as<float>() : nullptr;
+        bc.kldm[m] = minv_ld(nv[m], true);
     }
-    hipLaunchKernelGGL(block_combine_kernel, dim3((A.ne + A.ni + 255) / 256, R), dim3(256), 0, st, A, bc, R, X, xstride,
+    hipLaunchKernelGGL(block_combine_kernel, dim3((A.ne + A.ni + 63) / 64, R), dim3(256), 0, st, A, bc, R, X, xstride,
                        Y, ystride, kst);
     BEM_HIP(hipGetLastError());
     if (!strong) return BEM_OK;
@@ -2510,16 +2659,10 @@ bem_status block_apply(bem_problem *p, const MtfArgs &A, BlockBufs &bb, int R, c
         return cheb_apply(p, 0, p->cheb.nparts[0] + p->cheb.nparts[1], 0, 2 * A.ne, n, Y, ystride, Z, zstride,
                           bb.chw.as<double2>(), 6 * n, R, kst, cheb_precond_steps(p));
     }
-    for (int m = 0; m < 2; ++m) {
-        const int km = minv_ld(nv[m], true);
-        hipLaunchKernelGGL(pack_mass_kernel, dim3((km + 255) / 256, 4 * BLOCK_RHS), dim3(256), 0, st, nv[m], km, R,
-                           (const double2 *)Y, ystride, m == 0 ? 0 : 2 * A.ne, kst, bb.btm[m].as<float>());
-    }
-    BEM_HIP(hipGetLastError());
     GemmArgs Gm = mass_gemm_args(p, bb, nk_mass, R, kst);
     s = launch_gemm_f32(p->ctx, Gm, st, K_MASS_GEMM);
     if (s) return s;
-    hipLaunchKernelGGL(mass_reduce_kernel, dim3((A.ne + A.ni + 255) / 256, R), dim3(256), 0, st, A.ne, A.ni, Gm.seg[0].C,
+    hipLaunchKernelGGL(mass_reduce_kernel, dim3((A.ne + A.ni + 63) / 64, R), dim3(256), 0, st, A.ne, A.ni, Gm.seg[0].C,
                        Gm.seg[1].C, nchunks(Gm.seg[0].K, Gm.seg[0].kchunk), nchunks(Gm.seg[1].K, Gm.seg[1].kchunk),
                        128 * Gm.seg[0].ncb, R, Z, zstride, kst);
     BEM_HIP(hipGetLastError());
@@ -2784,13 +2927,17 @@ __global__ void axpy_add_kernel(int n, const double2 *__restrict__ d, double2 *_
     if (r < n) x[r] = make_double2(x[r].x + d[r].x, x[r].y + d[r].y);
 }
 
-__global__ void zero_kernel(int64_t n, double2 *__restrict__ x)
-{
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < n) x[r] = make_double2(0, 0);
-}
-
 }  // namespace
+
+// Vectors of a product go through a device copy when they are on the host or
+// not on 16-byte boundaries (the kernels read and write whole complex128
+// entries); else the kernels use the caller's memory.
+static bool copied(bem_memspace space, const void *x, const void *y)
+{
+    return space == BEM_HOST || ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) & 15) != 0;
+}
+static hipMemcpyKind copy_in(bem_memspace space) { return space == BEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice; }
+static hipMemcpyKind copy_out(bem_memspace space) { return space == BEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice; }
 
 bem_status matvec_impl(bem_problem *p, const void *x, void *y, int strong, bem_memspace space)
 {
@@ -2799,27 +2946,27 @@ bem_status matvec_impl(bem_problem *p, const void *x, void *y, int strong, bem_m
     hipStream_t st = ctx->stream;
     const int ne = (int)p->ext->h.nv, ni = (int)p->inte->h.nv, n = 2 * ne + 2 * ni;
     const size_t bytes = (size_t)n * sizeof(double2);
-    DevMem xu, xi, yi, zi, yu, part;
-    bem_status s = dev_alloc(ctx, xu, bytes);
-    if (!s) s = dev_alloc(ctx, part, split_part_bytes(ne, ni));
+    const bool staged = copied(space, x, y);
+    DevMem xu, xi, yi, zi, part;   // xu: the caller's vector, then the result for it, when they are copied
+    bem_status s = dev_alloc(ctx, part, split_part_bytes(ne, ni));
+    if (!s && staged) s = dev_alloc(ctx, xu, bytes);
     if (!s) s = dev_alloc(ctx, xi, bytes);
     if (!s) s = dev_alloc(ctx, yi, bytes);
     if (!s) s = dev_alloc(ctx, zi, bytes);
-    if (!s) s = dev_alloc(ctx, yu, bytes);
     if (s) return s;
-    BEM_HIP(hipMemcpyAsync(xu.ptr, x, bytes, space == BEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, st));
+    if (staged) BEM_HIP(hipMemcpyAsync(xu.ptr, x, bytes, copy_in(space), st));
     const dim3 g((n + 255) / 256);
-    hipLaunchKernelGGL(permute_vec_kernel, g, dim3(256), 0, st, ne, ni, p->ext->d.perm.as<int32_t>(),
-                       p->inte->d.perm.as<int32_t>(), xu.as<double2>(), xi.as<double2>(), 1);
-    s = mtf_tune(p, xi.as<double2>(), yi.as<double2>(), part.as<double4>());
+    s = launch_to_internal(p, staged ? xu.as<double2>() : static_cast<const double2 *>(x), xi.as<double2>(), 1, st);
+    if (!s) s = mtf_tune(p, xi.as<double2>(), yi.as<double2>(), part.as<double4>());
     if (s) return s;
     MtfArgs A = make_args(p);
     s = apply_A(p, A, xi.as<double2>(), yi.as<double2>(), zi.as<double2>(), strong != 0, nullptr, part.as<double4>());
     if (s) return s;
     hipLaunchKernelGGL(permute_vec_kernel, g, dim3(256), 0, st, ne, ni, p->ext->d.perm.as<int32_t>(),
-                       p->inte->d.perm.as<int32_t>(), strong ? zi.as<double2>() : yi.as<double2>(), yu.as<double2>(), 0);
+                       p->inte->d.perm.as<int32_t>(), strong ? zi.as<double2>() : yi.as<double2>(),
+                       staged ? xu.as<double2>() : static_cast<double2 *>(y), 0);
     BEM_HIP(hipGetLastError());
-    BEM_HIP(hipMemcpyAsync(y, yu.ptr, bytes, space == BEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice, st));
+    if (staged) BEM_HIP(hipMemcpyAsync(y, xu.ptr, bytes, copy_out(space), st));
     BEM_HIP(hipStreamSynchronize(st));
     return BEM_OK;
 }
@@ -2920,10 +3067,11 @@ bem_status matvec_batch_impl(bem_problem *p, const void *x, void *y, int nrhs, i
     const int ne = (int)p->ext->h.nv, ni = (int)p->inte->h.nv, n = 2 * ne + 2 * ni;
     const int R = std::min(nrhs, BLOCK_RHS);
     const size_t vb = (size_t)n * sizeof(double2);
-    DevMem xu, xi, yi, zi;
+    const bool staged = copied(space, x, y);
+    DevMem xu, xi, yi, zi;   // xu: a block of the caller's vectors, then the results for it, when they are copied
     BlockBufs bb;
-    bem_status s = dev_alloc(ctx, xu, R * vb);
-    if (!s) s = dev_alloc(ctx, xi, R * vb);
+    bem_status s = dev_alloc(ctx, xi, R * vb);
+    if (!s && staged) s = dev_alloc(ctx, xu, R * vb);
     if (!s) s = dev_alloc(ctx, yi, R * vb);
     if (!s) s = dev_alloc(ctx, zi, R * vb);
     if (!s) s = block_alloc(p, bb);
@@ -2932,22 +3080,18 @@ bem_status matvec_batch_impl(bem_problem *p, const void *x, void *y, int nrhs, i
     const dim3 g((n + 255) / 256);
     for (int r0 = 0; r0 < nrhs; r0 += R) {
         const int Rc = std::min(R, nrhs - r0);
-        BEM_HIP(hipMemcpyAsync(xu.ptr, static_cast<const char *>(x) + r0 * vb, Rc * vb,
-                               space == BEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, st));
-        for (int r = 0; r < Rc; ++r)
-            hipLaunchKernelGGL(permute_vec_kernel, g, dim3(256), 0, st, ne, ni, p->ext->d.perm.as<int32_t>(),
-                               p->inte->d.perm.as<int32_t>(), xu.as<double2>() + (size_t)r * n,
-                               xi.as<double2>() + (size_t)r * n, 1);
+        const double2 *xr = static_cast<const double2 *>(x) + (size_t)r0 * n;
+        double2 *yr = static_cast<double2 *>(y) + (size_t)r0 * n;
+        if (staged) BEM_HIP(hipMemcpyAsync(xu.ptr, xr, Rc * vb, copy_in(space), st));
+        s = launch_to_internal(p, staged ? xu.as<double2>() : xr, xi.as<double2>(), Rc, st);
+        if (s) return s;
         s = block_apply(p, A, bb, Rc, xi.as<double2>(), n, yi.as<double2>(), n, zi.as<double2>(), n, strong != 0,
                         nullptr);
         if (s) return s;
-        for (int r = 0; r < Rc; ++r)
-            hipLaunchKernelGGL(permute_vec_kernel, g, dim3(256), 0, st, ne, ni, p->ext->d.perm.as<int32_t>(),
-                               p->inte->d.perm.as<int32_t>(), (strong ? zi : yi).as<double2>() + (size_t)r * n,
-                               xu.as<double2>() + (size_t)r * n, 0);
+        hipLaunchKernelGGL(permute_vec_kernel, dim3(g.x, Rc), dim3(256), 0, st, ne, ni, p->ext->d.perm.as<int32_t>(),
+                           p->inte->d.perm.as<int32_t>(), (strong ? zi : yi).as<double2>(), staged ? xu.as<double2>() : yr, 0);
         BEM_HIP(hipGetLastError());
-        BEM_HIP(hipMemcpyAsync(static_cast<char *>(y) + r0 * vb, xu.ptr, Rc * vb,
-                               space == BEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice, st));
+        if (staged) BEM_HIP(hipMemcpyAsync(yr, xu.ptr, Rc * vb, copy_out(space), st));
         BEM_HIP(hipStreamSynchronize(st));
     }
     return BEM_OK;
@@ -3203,13 +3347,10 @@ bem_status solve_impl(bem_problem *p, const double *dirs, int nrhs, const bem_so
             }
         }
         // traces in caller numbering
-        for (int r = 0; r < Rg; ++r) {
-            hipLaunchKernelGGL(permute_vec_kernel, gv, dim3(256), 0, st, ne, ni, p->ext->d.perm.as<int32_t>(),
-                               p->inte->d.perm.as<int32_t>(), W.xin.as<double2>() + (size_t)r * n,
-                               W.y.as<double2>() + (size_t)r * n, 0);
-            BEM_HIP(hipGetLastError());
-            worst_res = std::max(worst_res, b0[r] > 0 ? rn[r] / b0[r] : 0.0);
-        }
+        hipLaunchKernelGGL(permute_vec_kernel, dim3(nrow_blk, Rg), dim3(256), 0, st, ne, ni, p->ext->d.perm.as<int32_t>(),
+                           p->inte->d.perm.as<int32_t>(), W.xin.as<double2>(), W.y.as<double2>(), 0);
+        BEM_HIP(hipGetLastError());
+        for (int r = 0; r < Rg; ++r) worst_res = std::max(worst_res, b0[r] > 0 ? rn[r] / b0[r] : 0.0);
         BEM_HIP(hipMemcpyAsync(static_cast<double2 *>(traces) + (size_t)g0 * n, W.y.ptr, Rg * vb,
                                space == BEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice, st));
         BEM_HIP(hipStreamSynchronize(st));
