@@ -133,7 +133,8 @@ bem_status bem_ctx_trim(bem_ctx *ctx);
  * (Gram-Schmidt update), 8 "arnoldi_finish" (Hessenberg column, Givens
  * rotation, residual estimate), 9 "mass_inverse", 10 "block_gemm"
  * (multi-RHS operator product), 11 "mass_gemm" (multi-RHS inverse-mass
- * product), 12 "krylov_normalize" (new Krylov vector scaled to unit norm),
+ * product), 12 "krylov_normalize" (no launches: the scaling of a new Krylov
+ * vector is part of 7 and 8),
  * 13 "field" (field off the surface, bem_field), 14 "mortar" (the two passes
  * of the device mortar geometry, bem_problem_set_mortar).  Every launch of a kernel whose bit is set in
  * kernel_mask is bracketed by HIP events on the context stream (a few

@@ -1175,20 +1175,22 @@ static inline dim3 split_grid(int ne, int ni, int cwmax, int rw = 1)
 // orthogonalised twice, as in CGS2, but the second pass of step j shares
 // its sweeps over the basis with the first pass of step j + 1, so a step
 // reads the basis twice instead of four times.  Step j, V = v_0 .. v_{j-1}:
-//   slot j of the basis holds u_j (one Gram-Schmidt pass, unit norm) and
-//   w = M^-1 A u_j;
-//   dots:      a = V^H u_j, alpha = |u_j|^2, b = V^H w, gamma = u_j^H w;
-//   hess:      nu = sqrt(alpha - |a|^2), so that v_j = (u_j - V a) / nu;
+//   slot j of the basis holds y_j, the direction after one Gram-Schmidt pass;
+//   with s = 1 / |y_j|, u_j = s y_j is its unit vector and w = s M^-1 A y_j:
+//   the operator takes y_j as it is and every sum is scaled by s, so no
+//   kernel of its own has to scale the vector before the product;
+//   dots:      V^H y_j, |y_j|^2, V^H w / s, y_j^H w / s;
+//   hess:      s, a = V^H u_j, b = V^H w, gamma = u_j^H w; nu = sqrt(1 -
+//              |a|^2), so that v_j = (u_j - V a) / nu;
 //              the pending column j-1 of the Hessenberg matrix becomes
 //              h_{j-1} + beta_{j-1} a over the subdiagonal beta_{j-1} nu
-//              (because u_j = nu v_j + V a), then its Givens rotation and the
-//              residual estimate of the j-dimensional space;
-//              c_j = (gamma - a^H b) / nu = v_j^H w;
-//   update:    v_j into slot j and y = w - V b - v_j c_j into slot j+1;
+//              (because u_j = nu v_j + V a), beta_{j-1} = |y_j| / nu_{j-1}, then
+//              its Givens rotation and the residual estimate of the
+//              j-dimensional space; c_j = (gamma - a^H b) / nu = v_j^H w;
+//   update:    v_j into slot j and y_{j+1} = w - V b - v_j c_j into slot j+1;
 //              since w = nu M^-1 A v_j + M^-1 A V a and M^-1 A V = [V v_j] Hbar,
-//              M^-1 A v_j = [V v_j] h_j + y / nu with the pending column
-//              h_j = ([b; c_j] - Hbar a) / nu, formed by extra waves;
-//   normalise: u_{j+1} = y / |y| and beta_j = |y| / nu.
+//              M^-1 A v_j = [V v_j] h_j + y_{j+1} / nu with the pending column
+//              h_j = ([b; c_j] - Hbar a) / nu, formed by extra waves.
 // The residual estimate of dimension j appears in step j (one operator
 // product after the one that made the space).  Sums run in a fixed order;
 // every kernel returns at once when the state says the run has converged, so
@@ -1208,7 +1210,7 @@ constexpr int MAXIT_CAP = 3000;   // Hessenberg column, rotations and g staged i
 
 // partial[chunk][c] = sum over the chunk's rows of conj(V_c) u_j and
 // partial[chunk][j + 1 + c] = that of conj(V_c) w, for c = 0..j (slot j is
-// u_j itself: alpha and gamma).  One wave per (chunk, CPW consecutive
+// the direction itself: its square and gamma; both unscaled, see above).  One wave per (chunk, CPW consecutive
 // columns): with CPW = 2 the wave reads the chunks of u_j and w once for
 // both columns; each column's sum runs over the same rows in the same order
 // either way.  Grid (nchunk, ceil((j + 1) / (4 CPW)), runs), or larger (the
@@ -1269,13 +1271,13 @@ __device__ inline double2 cconj_mul(double2 a, double2 b)   // conj(a) * b
     return make_double2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x);
 }
 
-// Sums of the partials into coef ([0, j) a, [j] alpha, [j + 1, 2j + 1) b,
-// [2j + 1] gamma); nu; the final column j - 1 of the Hessenberg matrix
+// Sums of the partials, scaled, into coef ([0, j) a, [j + 1, 2j + 1) b); nu;
+// the final column j - 1 of the Hessenberg matrix
 // (kept row-major in H, row stride m) and, by the first wave, its Givens rotation
 // (the earlier rotations as a scanned affine recurrence),
-// g and the residual estimate; then coef[j] = (1 / nu, nu) and coef[2j + 1] =
-// c_j for the update.  coef[2m + 3] holds beta_{j-1}.  One workgroup per run;
-// dynamic LDS for at least 3 j + 1 complex values.
+// g and the residual estimate; then coef[j] = (1 / nu, nu), coef[2j + 1] =
+// c_j and coef[2m + 2] = (s, 0) for the update, and coef[2m + 3] = (nu, 0) for the next step.
+// One workgroup per run; dynamic LDS for at least 3 j + 1 complex values.
 __global__ __launch_bounds__(256) void dgs_hess_kernel(int j, const int *__restrict__ jb, int m, int nchunk,
                                                        const double2 *__restrict__ partial,
                                                        double2 *__restrict__ coef, const double2 *__restrict__ hsum,
@@ -1305,8 +1307,13 @@ __global__ __launch_bounds__(256) void dgs_hess_kernel(int j, const int *__restr
     __syncthreads();
     __shared__ double red[3][4];
     double aa = 0, abr = 0, abi = 0;
+    const double y2 = coef[j].x, s = y2 > 0 ? 1.0 / sqrt(y2) : 0.0;   // a zero direction: nu = 0 below
     for (int k = tid; k < j; k += 256) {
-        const double2 a = coef[k], b = coef[j + 1 + k];
+        double2 a = coef[k], b = coef[j + 1 + k];
+        a = make_double2(s * a.x, s * a.y);
+        b = make_double2(s * b.x, s * b.y);
+        coef[k] = a;   // read again by this thread below, and by the update
+        coef[j + 1 + k] = b;
         aa += a.x * a.x + a.y * a.y;
         abr += a.x * b.x + a.y * b.y;
         abi += a.x * b.y - a.y * b.x;
@@ -1323,10 +1330,10 @@ __global__ __launch_bounds__(256) void dgs_hess_kernel(int j, const int *__restr
     aa = red[0][0] + red[0][1] + red[0][2] + red[0][3];
     abr = red[1][0] + red[1][1] + red[1][2] + red[1][3];
     abi = red[2][0] + red[2][1] + red[2][2] + red[2][3];
-    const double nu2 = coef[j].x - aa;
+    const double nu2 = (y2 > 0 ? 1.0 : 0.0) - aa;
     const double nu = nu2 > 0 ? sqrt(nu2) : 0.0;
-    const double2 gamma = coef[2 * j + 1];
-    const double beta_prev = coef[2 * m + 3].x;
+    const double2 gamma = make_double2(s * s * coef[2 * j + 1].x, s * s * coef[2 * j + 1].y);
+    const double beta_prev = j > 0 ? sqrt(y2) / coef[2 * m + 3].x : 0.0;
     extern __shared__ double2 sh[];   // [h: j + 1][cs: j][sn: j]
     double2 *hl = sh, *csl = sh + (j + 1), *snl = csl + j;
     // final column j - 1: rows 0..j-1 h_{j-1} + beta_{j-1} a, row j beta_{j-1} nu
@@ -1412,11 +1419,14 @@ __global__ __launch_bounds__(256) void dgs_hess_kernel(int j, const int *__restr
     const double inv = 1.0 / nu;
     coef[j] = make_double2(inv, nu);
     coef[2 * j + 1] = make_double2((gamma.x - abr) * inv, (gamma.y - abi) * inv);
+    coef[2 * m + 2] = make_double2(s, 0.0);
+    coef[2 * m + 3] = make_double2(nu, 0.0);
 }
 
 // Blocks [0, nupd): 64 rows each (four waves split the basis columns, summed
 // in LDS in a fixed order); v_j = (u_j - V a) / nu into slot j, y = w - V b -
-// v_j c_j into slot j + 1, partial |y|^2 per block.  Blocks from nupd on: one
+// v_j c_j into slot j + 1 and, with u_out, there too (run stride B.vec): the
+// fixed operand of the next operator product.  Blocks from nupd on: one
 // wave per row r <= j of the pending column, h_j[r] = ([b; c_j][r] -
 // sum over i >= r - 1 of H[r][i] a_i) / nu.  Grid (nupd + ceil((j + 1) / 4), runs),
 // or larger (the extra waves return).
@@ -1424,7 +1434,7 @@ __global__ __launch_bounds__(256) void dgs_update_kernel(int n, int j, const int
                                                          double2 *__restrict__ Vb,
                                                          const double2 *__restrict__ w, const double2 *__restrict__ coef,
                                                          const double2 *__restrict__ H, double2 *__restrict__ hsum,
-                                                         double *__restrict__ npart, const KrylovState *__restrict__ st,
+                                                         double2 *__restrict__ u_out, const KrylovState *__restrict__ st,
                                                          KBatch B)
 {
     const int run = blockIdx.y;
@@ -1435,7 +1445,6 @@ __global__ __launch_bounds__(256) void dgs_update_kernel(int n, int j, const int
     coef += run * B.coef;
     H += run * B.hess;
     hsum += run * B.small;
-    npart += run * B.npart;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: the coefficients go through scalar loads
     const double inv_nu = coef[j].x;
@@ -1478,50 +1487,15 @@ __global__ __launch_bounds__(256) void dgs_update_kernel(int n, int j, const int
         const double4 t = acc[q][lane];
         ur += t.x; ui += t.y; wr += t.z; wi += t.w;
     }
-    double nrm = 0.0;
     if (live) {
         const double2 u = Vb[(int64_t)j * n + row], x = w[row], cj = coef[2 * j + 1];
-        const double2 v = make_double2((u.x - ur) * inv_nu, (u.y - ui) * inv_nu);
-        const double2 y = make_double2(x.x - wr - (v.x * cj.x - v.y * cj.y), x.y - wi - (v.x * cj.y + v.y * cj.x));
+        const double s = coef[2 * m + 2].x;
+        const double2 v = make_double2((s * u.x - ur) * inv_nu, (s * u.y - ui) * inv_nu);
+        const double2 y = make_double2(s * x.x - wr - (v.x * cj.x - v.y * cj.y), s * x.y - wi - (v.x * cj.y + v.y * cj.x));
         Vb[(int64_t)j * n + row] = v;
         Vb[(int64_t)(j + 1) * n + row] = y;
-        nrm = y.x * y.x + y.y * y.y;
+        if (u_out) u_out[run * B.vec + row] = y;
     }
-    nrm = wave_sum(nrm);
-    if (lane == 0) npart[blockIdx.x] = nrm;
-}
-
-// u_{j+1} = y / |y| in place in slot j + 1 (|y|^2 from the nupd partials, summed
-// in the same order by every block); block 0 stores beta_j = |y| / nu.  With
-// u_out, u_{j+1} also goes there (run stride B.vec): the fixed operand of the
-// next operator product.  Grid (ceil(n / 256), runs).
-__global__ __launch_bounds__(256) void dgs_normalize_kernel(int n, int j, const int *__restrict__ jb, int m, int nupd,
-                                                            const double *__restrict__ npart, double2 *__restrict__ Vb,
-                                                            double2 *__restrict__ coef, double2 *__restrict__ u_out,
-                                                            const KrylovState *__restrict__ st, KBatch B)
-{
-    const int run = blockIdx.y;
-    if (st[run].done) return;
-    if (jb) j += *jb;
-    npart += run * B.npart;
-    Vb += run * B.basis;
-    coef += run * B.coef;
-    __shared__ double red[4];
-    double s2 = 0;
-    for (int b = threadIdx.x; b < nupd; b += 256) s2 += npart[b];
-    s2 = wave_sum(s2);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s2;
-    __syncthreads();
-    const double yn = sqrt(red[0] + red[1] + red[2] + red[3]);
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    double2 *y = Vb + (int64_t)(j + 1) * n;
-    if (r < n) {
-        const double inv = yn > 0 ? 1.0 / yn : 0.0;
-        const double2 u = make_double2(y[r].x * inv, y[r].y * inv);
-        y[r] = u;
-        if (u_out) u_out[run * B.vec + r] = u;
-    }
-    if (r == 0) coef[2 * m + 3] = make_double2(yn / coef[j].y, 0.0);
 }
 
 // partial[blk] = sum |w|^2 over 256-row blocks; grid (row blocks, runs)
@@ -2705,7 +2679,7 @@ struct Gmres {
     // The launches of step j: the operator on u_j (vj, run stride vstride),
     // then the Gram-Schmidt kernels.  With jb the kernels take their step
     // index as j + *jb (device memory) and their grids are sized for steps up
-    // to jcap; u_out: where the normalisation also writes u_{j+1}.
+    // to jcap; u_out: where the update also writes the next direction.
     bem_status step(int j, const int *jb, int jcap, int maxit, const double2 *vj, int64_t vstride, double2 *u_out,
                     bool acc64)
     {
@@ -2713,7 +2687,6 @@ struct Gmres {
         hipStream_t st = ctx->stream;
         double2 *Vb = W.Vb.as<double2>();
         KrylovState *dst = W.state.as<KrylovState>();
-        const dim3 gv(nrow_blk, R);
         bem_status s;
         if (pm)
             s = apply_ext_form(p, *pm, vj, W.y.as<double2>(), W.z.as<double2>(), true, dst, W.part.as<double4>());
@@ -2742,15 +2715,10 @@ struct Gmres {
                      dst, B);
         }
         if (jb || j < maxit) {
-            {
-                KTimer kt(ctx, K_CGS_UPDATE);
-                launch_k(kt, dgs_update_kernel, dim3(nupd + (jcap + 1 + 3) / 4, R), dim3(256), 0, st, n, j, jb, maxit,
-                         nupd, Vb, W.z.as<double2>(), W.coef.as<double2>(), W.H.as<double2>(), W.hsum.as<double2>(),
-                         W.npart.as<double>(), dst, B);
-            }
-            KTimer kt(ctx, K_KRYLOV_NORM);
-            launch_k(kt, dgs_normalize_kernel, gv, dim3(256), 0, st, n, j, jb, maxit, nupd, W.npart.as<double>(), Vb,
-                     W.coef.as<double2>(), u_out, dst, B);
+            KTimer kt(ctx, K_CGS_UPDATE);
+            launch_k(kt, dgs_update_kernel, dim3(nupd + (jcap + 1 + 3) / 4, R), dim3(256), 0, st, n, j, jb, maxit,
+                     nupd, Vb, W.z.as<double2>(), W.coef.as<double2>(), W.H.as<double2>(), W.hsum.as<double2>(),
+                     u_out, dst, B);
         }
         BEM_HIP(hipGetLastError());
         return BEM_OK;
