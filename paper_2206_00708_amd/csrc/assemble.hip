@@ -28,6 +28,7 @@
 // bitwise reproducible run to run.
 #include <cmath>
 
+#include "dpp.h"
 #include "internal.h"
 #include "phase.h"
 #include "rule6.h"
@@ -856,6 +857,8 @@ __global__ void zero_padding_kernel(int nv, C2 *__restrict__ V, C2 *__restrict__
 
 // ----------------------------------------------------------- singular pairs
 
+constexpr int SING_WIDE_MAX = 8192;   // pairs up to which the longer ones take a whole wave (singular_pairs_kernel)
+
 struct GLTab {
     double x[NG_MAX], w[NG_MAX];
 };
@@ -894,26 +897,26 @@ __device__ inline void ss_map(int kind, int reg, double xi, double e1, double e2
     }
 }
 
-template <bool CK>
-__global__ __launch_bounds__(256, 2) void singular_pairs_kernel(const TriGeo *__restrict__ geo,
-                                                             const SingPair *__restrict__ pairs, int npairs, int ng,
-                                                             GLTab gl, double k, double kim, double2 *__restrict__ out)
+// One ordered singular pair on LPP lanes: 16 take the ng^2 points of the last
+// two coordinates among them; 64 also split the first coordinate.  Sums over
+// the lanes by DPP.  out: [pair][corner pair][V, K, T, D].
+template <bool CK, int LPP>
+__device__ inline void singular_pair(const TriGeo *__restrict__ geo, const SingPair *__restrict__ pairs, int pid, int ng,
+                                     const GLTab &gl, double k, double kim, double2 *__restrict__ out)
 {
-    const int grp = threadIdx.x >> 4, lane = threadIdx.x & 15;
-    const int pid = blockIdx.x * 16 + grp;
-    if (pid >= npairs) return;
+    const int lane = threadIdx.x & (LPP - 1);
     const SingPair sp = pairs[pid];
     const TriGeo &X = geo[sp.tau];
     const TriGeo &Y = geo[sp.sig];
     int px[3], py[3];
     for (int r = 0; r < 3; ++r) { px[r] = (sp.perm >> (2 * r)) & 3; py[r] = (sp.perm >> (6 + 2 * r)) & 3; }
-    double Qx[3][3], Qy[3][3];
-    for (int r = 0; r < 3; ++r)
-        for (int c = 0; c < 3; ++c) { Qx[r][c] = X.p[px[r]][c]; Qy[r][c] = Y.p[py[r]][c]; }
+    // x - y = xs0 ax0 + xs1 ax1 - ys0 ay0 - ys1 ay1: the first reference corner is shared
     double ax[2][3], ay[2][3];
     for (int c = 0; c < 3; ++c) {
-        ax[0][c] = Qx[1][c] - Qx[0][c]; ax[1][c] = Qx[2][c] - Qx[1][c];
-        ay[0][c] = Qy[1][c] - Qy[0][c]; ay[1][c] = Qy[2][c] - Qy[1][c];
+        const double x0 = X.p[px[0]][c], x1 = X.p[px[1]][c], x2 = X.p[px[2]][c];
+        const double y0 = Y.p[py[0]][c], y1 = Y.p[py[1]][c], y2 = Y.p[py[2]][c];
+        ax[0][c] = x1 - x0; ax[1][c] = x2 - x1;
+        ay[0][c] = y1 - y0; ay[1][c] = y2 - y1;
     }
     const double nx[3] = {X.n[0], X.n[1], X.n[2]}, ny[3] = {Y.n[0], Y.n[1], Y.n[2]};
     const int kind = sp.kind;
@@ -922,11 +925,11 @@ __global__ __launch_bounds__(256, 2) void singular_pairs_kernel(const TriGeo *__
 #pragma unroll
     for (int e = 0; e < 9; ++e) { vr[e] = vi[e] = kr[e] = ki[e] = tr[e] = ti[e] = 0.0; }
     const int ng2 = ng * ng;
-    for (int inner = lane; inner < ng2; inner += 16) {
+    for (int inner = lane & 15; inner < ng2; inner += 16) {
         const int i2 = inner / ng, i3 = inner - i2 * ng;
         const double e2 = gl.x[i2], e3 = gl.x[i3], w23 = gl.w[i2] * gl.w[i3];
         for (int reg = 0; reg < nreg; ++reg)
-            for (int i0 = 0; i0 < ng; ++i0)
+            for (int i0 = lane >> 4; i0 < ng; i0 += LPP / 16)
                 for (int i1 = 0; i1 < ng; ++i1) {
                     const double xi = gl.x[i0], e1 = gl.x[i1];
                     double xs0, xs1, ys0, ys1, jac;
@@ -934,9 +937,9 @@ __global__ __launch_bounds__(256, 2) void singular_pairs_kernel(const TriGeo *__
                     const double wt = gl.w[i0] * gl.w[i1] * w23 * jac;
                     double d[3];
                     for (int c = 0; c < 3; ++c)
-                        d[c] = (Qx[0][c] + xs0 * ax[0][c] + xs1 * ax[1][c]) - (Qy[0][c] + ys0 * ay[0][c] + ys1 * ay[1][c]);
+                        d[c] = (xs0 * ax[0][c] + xs1 * ax[1][c]) - (ys0 * ay[0][c] + ys1 * ay[1][c]);
                     const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-                    const double rinv = rsqrt(r2);
+                    const double rinv = rsqrt_pos(r2);
                     const double r = r2 * rinv, kr_ = k * r;
                     double sn, cs;
                     phase_sincos(kr_, &sn, &cs);
@@ -967,68 +970,96 @@ __global__ __launch_bounds__(256, 2) void singular_pairs_kernel(const TriGeo *__
                         }
                 }
     }
+    // over the lanes of the pair, into its last lane
+    auto total = [](double v) { return LPP == 64 ? wsum63(v) : rsum15(v); };
+#pragma unroll
+    for (int e = 0; e < 9; ++e) {
+        vr[e] = total(vr[e]); vi[e] = total(vi[e]);
+        kr[e] = total(kr[e]); ki[e] = total(ki[e]);
+        tr[e] = total(tr[e]); ti[e] = total(ti[e]);
+    }
+    if (lane != LPP - 1) return;
     // the sum of G over the points: the P1 functions of each side sum to one
     // at every point, so it is the sum of the nine V entries
     double sr = 0.0, si = 0.0;
 #pragma unroll
     for (int e = 0; e < 9; ++e) { sr += vr[e]; si += vi[e]; }
-    // reduce over the 16 lanes of the group
-#pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) {
-#pragma unroll
-        for (int e = 0; e < 9; ++e) {
-            vr[e] += __shfl_xor(vr[e], off, 16); vi[e] += __shfl_xor(vi[e], off, 16);
-            kr[e] += __shfl_xor(kr[e], off, 16); ki[e] += __shfl_xor(ki[e], off, 16);
-            tr[e] += __shfl_xor(tr[e], off, 16); ti[e] += __shfl_xor(ti[e], off, 16);
-        }
-        sr += __shfl_xor(sr, off, 16);
-        si += __shfl_xor(si, off, 16);
-    }
-    if (lane != 0) return;
     const double scale = 4.0 * X.area * Y.area * kInv4Pi;
     const double nn = nx[0] * ny[0] + nx[1] * ny[1] + nx[2] * ny[2];
     double2 *o = out + (int64_t)pid * 36;
+#pragma unroll
     for (int ra = 0; ra < 3; ++ra)
+#pragma unroll
         for (int rb = 0; rb < 3; ++rb) {
             const int a = px[ra], b = py[rb];        // own corners
             const int e = 3 * a + b, re = 3 * ra + rb;
             const double cc = X.curl[a][0] * Y.curl[b][0] + X.curl[a][1] * Y.curl[b][1] + X.curl[a][2] * Y.curl[b][2];
             const double Vr = vr[re] * scale, Vi = vi[re] * scale;
-            o[e] = make_double2(Vr, Vi);
-            o[9 + e] = make_double2(kr[re] * scale, ki[re] * scale);
-            o[18 + e] = make_double2(tr[re] * scale, ti[re] * scale);
+            o[4 * e] = make_double2(Vr, Vi);
+            o[4 * e + 1] = make_double2(kr[re] * scale, ki[re] * scale);
+            o[4 * e + 2] = make_double2(tr[re] * scale, ti[re] * scale);
             if constexpr (CK) {
                 const double k2r = k * k - kim * kim, k2i = 2.0 * k * kim;
-                o[27 + e] = make_double2(cc * sr * scale - nn * (k2r * Vr - k2i * Vi),
-                                         cc * si * scale - nn * (k2r * Vi + k2i * Vr));
+                o[4 * e + 3] = make_double2(cc * sr * scale - nn * (k2r * Vr - k2i * Vi),
+                                            cc * si * scale - nn * (k2r * Vi + k2i * Vr));
             } else {
-                o[27 + e] = make_double2(cc * sr * scale - k * k * nn * Vr, cc * si * scale - k * k * nn * Vi);
+                o[4 * e + 3] = make_double2(cc * sr * scale - k * k * nn * Vr, cc * si * scale - k * k * nn * Vi);
             }
         }
 }
 
-// add the singular contributions (FP64) to their dense entries (fixed order)
+// The first nwide pairs (4 per workgroup) take a whole wave each, the others
+// (16 per workgroup) 16 lanes.  On meshes whose pairs leave most SIMDs with
+// one wave or none, the coincident and edge pairs (96 and 80 points per lane
+// on 16 lanes, against 32 of a vertex pair) are the wide ones, since the kernel
+// then takes the time of its longest pair (162 vertices, 4,300 pairs: 67 ->
+// 33 us); larger meshes fill the device with 16 lanes per pair and sum over
+// fewer lanes.
+template <bool CK>
+__global__ __launch_bounds__(256, 2) void singular_pairs_kernel(const TriGeo *__restrict__ geo,
+                                                             const SingPair *__restrict__ pairs, int npairs, int nwide,
+                                                             int ng, GLTab gl, double k, double kim,
+                                                             double2 *__restrict__ out)
+{
+    const int bw = (nwide + 3) / 4, b = blockIdx.x;
+    if (b < bw) {
+        const int pid = 4 * b + (threadIdx.x >> 6);
+        if (pid < nwide) singular_pair<CK, 64>(geo, pairs, pid, ng, gl, k, kim, out);
+    } else {
+        const int pid = nwide + 16 * (b - bw) + (threadIdx.x >> 4);
+        if (pid < npairs) singular_pair<CK, 16>(geo, pairs, pid, ng, gl, k, kim, out);
+    }
+}
+
+// Add the singular contributions (FP64) to their dense entries (fixed order):
+// a thread per entry and operator, so that four neighbours read a
+// contribution's 64 bytes together, four contributions in flight (a thread per
+// entry waited out the latency of one after the other: 23 us on the smallest
+// meshes).
 template <class C2>
-__global__ void near_scatter_kernel(int nv, int nnear, const int32_t *__restrict__ ni, const int32_t *__restrict__ nj,
-                                    const int32_t *__restrict__ nptr, const int32_t *__restrict__ nsrc,
-                                    const double2 *__restrict__ contrib, C2 *__restrict__ V, C2 *__restrict__ K,
-                                    C2 *__restrict__ T, C2 *__restrict__ D)
+__global__ __launch_bounds__(256) void near_scatter_kernel(int nv, int nnear, const int32_t *__restrict__ ni,
+                                                           const int32_t *__restrict__ nj,
+                                                           const int32_t *__restrict__ nptr,
+                                                           const int32_t *__restrict__ nsrc,
+                                                           const double2 *__restrict__ contrib, C2 *__restrict__ V,
+                                                           C2 *__restrict__ K, C2 *__restrict__ T, C2 *__restrict__ D)
 {
     using R = decltype(C2::x);
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t e = u >> 2;
+    const int op = (int)u & 3;
     if (e >= nnear) return;
-    double2 s[4] = {make_double2(0, 0), make_double2(0, 0), make_double2(0, 0), make_double2(0, 0)};
-    for (int q = nptr[e]; q < nptr[e + 1]; ++q) {
-        const int src = nsrc[q], pid = src / 9, ab = src - 9 * pid;
-        const double2 *c = contrib + (int64_t)pid * 36 + ab;
-        for (int op = 0; op < 4; ++op) { s[op].x += c[9 * op].x; s[op].y += c[9 * op].y; }
+    double sx = 0, sy = 0;
+    const int q1 = nptr[e + 1];
+#pragma unroll 4
+    for (int q = nptr[e]; q < q1; ++q) {
+        const double2 c = contrib[4 * (int64_t)nsrc[q] + op];   // nsrc: pair * 9 + corner pair
+        sx += c.x;
+        sy += c.y;
     }
-    const int64_t o = (int64_t)ni[e] * op_ld(nv) + nj[e];
-    C2 *dst[4] = {V, K, T, D};
-    for (int op = 0; op < 4; ++op) {
-        const C2 x = dst[op][o];
-        dst[op][o] = C2{(R)((double)x.x + s[op].x), (R)((double)x.y + s[op].y)};
-    }
+    C2 *dst = (op == 0 ? V : op == 1 ? K : op == 2 ? T : D) + (int64_t)ni[e] * op_ld(nv) + nj[e];
+    const C2 x = *dst;
+    *dst = C2{(R)((double)x.x + sx), (R)((double)x.y + sy)};
 }
 
 // ------------------------------------------------------------- launchers
@@ -1171,12 +1202,11 @@ bem_status launch_singular(const bem_mesh *m, double k, double kim, int ng, cons
     const int np = (int)m->h.sing.size();
     if (np > 0) {
         KTimer kt(m->ctx, K_SINGULAR);
-        if (kim != 0.0)
-            launch_k(kt, singular_pairs_kernel<true>, dim3((np + 15) / 16), dim3(256), 0, st, m->d.geo.as<TriGeo>(),
-                     m->d.sing.as<SingPair>(), np, ng, gl, k, kim, contrib);
-        else
-            launch_k(kt, singular_pairs_kernel<false>, dim3((np + 15) / 16), dim3(256), 0, st, m->d.geo.as<TriGeo>(),
-                     m->d.sing.as<SingPair>(), np, ng, gl, k, kim, contrib);
+        const int nwide = np <= SING_WIDE_MAX ? m->h.nsing_kind[3] + m->h.nsing_kind[2] : 0;   // (sorted by kind: 3, 2, 1)
+        const dim3 grid((nwide + 3) / 4 + (np - nwide + 15) / 16);
+        auto kernel = kim != 0.0 ? singular_pairs_kernel<true> : singular_pairs_kernel<false>;
+        launch_k(kt, kernel, grid, dim3(256), 0, st, m->d.geo.as<TriGeo>(), m->d.sing.as<SingPair>(), np, nwide, ng, gl, k,
+                 kim, contrib);
         BEM_HIP(hipGetLastError());
     }
     const int nn = (int)m->h.near_i.size();
@@ -1184,12 +1214,12 @@ bem_status launch_singular(const bem_mesh *m, double k, double kim, int ng, cons
         KTimer kt(m->ctx, K_NEAR);
         const int nv = (int)m->h.nv;
         if (!fp32)
-            launch_k(kt, near_scatter_kernel<double2>, dim3((nn + 255) / 256), dim3(256), 0, st, nv, nn,
+            launch_k(kt, near_scatter_kernel<double2>, dim3((unsigned)((4 * (int64_t)nn + 255) / 256)), dim3(256), 0, st, nv, nn,
                      m->d.near_i.as<int32_t>(), m->d.near_j.as<int32_t>(), m->d.near_ptr.as<int32_t>(),
                      m->d.near_src.as<int32_t>(), (const double2 *)contrib, static_cast<double2 *>(ops[0]),
                      static_cast<double2 *>(ops[1]), static_cast<double2 *>(ops[2]), static_cast<double2 *>(ops[3]));
         else
-            launch_k(kt, near_scatter_kernel<float2>, dim3((nn + 255) / 256), dim3(256), 0, st, nv, nn,
+            launch_k(kt, near_scatter_kernel<float2>, dim3((unsigned)((4 * (int64_t)nn + 255) / 256)), dim3(256), 0, st, nv, nn,
                      m->d.near_i.as<int32_t>(), m->d.near_j.as<int32_t>(), m->d.near_ptr.as<int32_t>(),
                      m->d.near_src.as<int32_t>(), (const double2 *)contrib, static_cast<float2 *>(ops[0]),
                      static_cast<float2 *>(ops[1]), static_cast<float2 *>(ops[2]), static_cast<float2 *>(ops[3]));

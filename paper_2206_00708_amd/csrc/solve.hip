@@ -42,6 +42,7 @@
 #include <string>
 #include <vector>
 
+#include "dpp.h"
 #include "internal.h"
 #include "phase.h"
 
@@ -547,30 +548,6 @@ __device__ inline float2 ld_entry(const float2 *p)   // one complex64 entry, str
 }
 __device__ inline float4 ld_entry2(const float2 *p) { return ld_stream2c(p); }   // two adjacent complex64
 
-// Sum over the 64 lanes of a wave with DPP moves (row shifts within each row
-// of 16 lanes, then row broadcasts 15 and 31); the total lands in lane 63.
-template <int CTRL, int RM = 0xF> __device__ inline float dpp_mov(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, RM, 0xF, true));
-}
-template <int CTRL, int RM = 0xF> __device__ inline double dpp_mov(double v)
-{
-    int2 q = __builtin_bit_cast(int2, v);
-    q.x = __builtin_amdgcn_update_dpp(0, q.x, CTRL, RM, 0xF, true);
-    q.y = __builtin_amdgcn_update_dpp(0, q.y, CTRL, RM, 0xF, true);
-    return __builtin_bit_cast(double, q);
-}
-template <class R> __device__ inline R wsum63(R v)
-{
-    v += dpp_mov<0x111>(v);        // row_shr:1
-    v += dpp_mov<0x112>(v);        // row_shr:2
-    v += dpp_mov<0x114>(v);        // row_shr:4
-    v += dpp_mov<0x118>(v);        // row_shr:8  (lane 15 of each row: the row's sum)
-    v += dpp_mov<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
-    v += dpp_mov<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
 template <class R> struct CAcc {   // complex accumulator in the arithmetic type R
     R x = 0, y = 0;
     template <class A, class B> __device__ void mac(const A &a, const B &b)
@@ -755,15 +732,6 @@ __global__ __launch_bounds__(256) void mtf_sym_tile_kernel(MtfArgs A, const doub
 // + mortar coupling.  16 lanes per row (one DPP row): each lane takes every
 // 16th term of the three sums, and a fixed reduction tree within the row
 // finishes them (deterministic).
-template <class R> __device__ inline R rsum15(R v)   // sum over the 16 lanes of a DPP row, in lane 15
-{
-    v += dpp_mov<0x111>(v);
-    v += dpp_mov<0x112>(v);
-    v += dpp_mov<0x114>(v);
-    v += dpp_mov<0x118>(v);
-    return v;
-}
-
 __global__ __launch_bounds__(256) void mtf_sym_combine_kernel(MtfArgs A, const double2 *__restrict__ x,
                                                               const double4 *__restrict__ part,
                                                               double2 *__restrict__ y,
