@@ -485,6 +485,29 @@ bem_status bem_problem_mass_apply(const bem_problem *p, int32_t *sparse)
     return BEM_OK;
 }
 
+// Assembly scratch of a problem: one region that the meshes use in turn, or,
+// where two regions are small, one for each (the interior mesh's at off1 > 0):
+// the two meshes are then assembled side by side.  A small mesh's chain of
+// launches leaves most of the device idle (162 + 162 vertices: 375 us one
+// after the other and read back, 300 side by side); meshes of more than a few hundred
+// tiles per compute unit fill it by themselves.
+constexpr size_t kAssemblyPairMax = size_t(256) << 20;
+
+static size_t assembly_scratch(const bem_problem *p, size_t &off1)
+{
+    const bem_mesh *ms[2] = {p->ext, p->inte};
+    const size_t eb = p->prec == BEM_C128 ? sizeof(double2) : sizeof(float2);
+    size_t need[2];
+    bool one = true;   // a single assembly strip each
+    for (int m = 0; m < 2; ++m) {
+        need[m] = std::max(tile_scratch_bytes(ms[m], eb), ms[m]->h.sing.size() * 36 * sizeof(double2));
+        need[m] = (std::max<size_t>(need[m], 16) + 255) & ~size_t(255);
+        one = one && ms[m]->h.strip_b.size() == 2;
+    }
+    off1 = one && need[0] + need[1] <= kAssemblyPairMax ? need[0] : 0;
+    return off1 ? need[0] + need[1] : std::max(need[0], need[1]);
+}
+
 bem_status bem_problem_footprint(const bem_problem *p, int32_t nrhs, int32_t maxit, size_t *bytes)
 {
     if (!p || !bytes || nrhs < 1 || maxit < 1) return set_error(BEM_E_ARG, "bad argument");
@@ -496,9 +519,8 @@ bem_status bem_problem_footprint(const bem_problem *p, int32_t nrhs, int32_t max
         b += 8 * (ne + ni) * (3 * sizeof(int32_t) + sizeof(double) + 14 * (sizeof(int32_t) + sizeof(double)));
     if (!sparse_mass || block_dense_mass(p, p->prec == BEM_C64_MIXED ? std::min(nrhs, 64) : 1))
         b += (ne * ne + ni * ni) * (p->prec == BEM_C128 ? sizeof(double) : sizeof(float));   // dense inverse masses
-    size_t scratch = std::max(tile_scratch_bytes(p->ext, eb), tile_scratch_bytes(p->inte, eb));
-    scratch = std::max(scratch, std::max(p->ext->h.sing.size(), p->inte->h.sing.size()) * 36 * sizeof(double2));
-    b += scratch;
+    size_t off;
+    b += assembly_scratch(p, off);
     // runs that advance together: every right-hand side of a complex64 problem (up to 64 per block), else one
     const size_t R = p->prec == BEM_C64_MIXED ? (size_t)std::min(nrhs, 64) : 1;
     b += R * ((size_t)(maxit + 1) * n + 8 * n) * sizeof(double2);                 // Krylov bases + work vectors
@@ -530,11 +552,8 @@ bem_status bem_assemble_operators(bem_problem *p, int32_t parts)
     const double kims[2] = {0.0, p->k_int_im};
     const bool fp32 = p->prec == BEM_C64_MIXED;
     const size_t eb = fp32 ? sizeof(float2) : sizeof(double2);
-    size_t scratch_bytes = 16;
-    for (int m = 0; m < 2; ++m) {
-        scratch_bytes = std::max(scratch_bytes, tile_scratch_bytes(meshes[m], eb));
-        scratch_bytes = std::max(scratch_bytes, meshes[m]->h.sing.size() * 36 * sizeof(double2));
-    }
+    size_t off1 = 0;
+    const size_t scratch_bytes = assembly_scratch(p, off1);
     for (int m = 0; m < 2; ++m) {
         const size_t nv = meshes[m]->h.nv;
         for (int op = 0; op < 4; ++op) {
@@ -564,14 +583,25 @@ bem_status bem_assemble_operators(bem_problem *p, int32_t parts)
         ctx->scratch_bytes = scratch_bytes;
         ctx->in_use += scratch_bytes;
     }
-    void *scratch = ctx->scratch;
     // events: [mesh][0] before regular, [1] before singular, [2] after; resolved lazily
     for (int m = 0; m < 2; ++m)
         for (int q = 0; q < 3; ++q)
             if (!p->asm_ev[m][q]) BEM_HIP(hipEventCreate(&p->asm_ev[m][q]));
+    hipStream_t side = st;   // stream of the interior mesh
+    if (off1) {
+        if (!ctx->gather) BEM_HIP(hipStreamCreateWithFlags(&ctx->gather, hipStreamNonBlocking));
+        side = ctx->gather;
+        hipEvent_t &ev = ctx->strip_ev[0];
+        if (!ev) BEM_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+        BEM_HIP(hipEventRecord(ev, st));
+        BEM_HIP(hipStreamWaitEvent(side, ev, 0));   // the operator and scratch blocks may have served earlier main-stream work
+    }
+    hipStream_t const main_stream = st;
     for (int m = 0; m < 2; ++m) {
+        st = m == 0 ? main_stream : side;
         void *ops[4];
         for (int op = 0; op < 4; ++op) ops[op] = p->ops[m][op].ptr;
+        void *const scratch = static_cast<char *>(ctx->scratch) + (m == 1 ? off1 : 0);
         const size_t nv = meshes[m]->h.nv;
         BEM_HIP(hipEventRecord(p->asm_ev[m][0], st));
         if (parts & 1) {
@@ -586,9 +616,16 @@ bem_status bem_assemble_operators(bem_problem *p, int32_t parts)
                                            static_cast<double2 *>(scratch), ops, st);
             if (s) return s;
         }
-        BEM_HIP(hipEventRecord(p->asm_ev[m][2], st));
+        if (!(off1 && m == 1)) BEM_HIP(hipEventRecord(p->asm_ev[m][2], st));
         bem_status s = launch_sym_corrections(p, m, st);
         if (s) return s;
+    }
+    if (off1) {   // the main stream waits for the interior mesh; the assembly ends with the later of the two
+        hipEvent_t &ev = ctx->strip_ev[1];
+        if (!ev) BEM_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+        BEM_HIP(hipEventRecord(ev, side));
+        BEM_HIP(hipStreamWaitEvent(main_stream, ev, 0));
+        BEM_HIP(hipEventRecord(p->asm_ev[1][2], main_stream));
     }
     p->asm_timing_pending = true;
     p->ops_ready = true;

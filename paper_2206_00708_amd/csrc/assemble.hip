@@ -1088,7 +1088,8 @@ size_t tile_scratch_bytes(const bem_mesh *m, size_t entry_bytes)
 // of the scratch on the main stream; its gather into the operators on the
 // context's gather stream, which overlaps the next strip's tiles.  The main
 // stream reuses a half once the gather of two strips before is done, and
-// waits for the last gather before returning.
+// waits for the last gather before returning.  A mesh of one strip has
+// nothing to overlap: all of it goes to `st`, without the events between streams.
 bem_status launch_regular(const bem_mesh *m, double k, double kim, bool fp32, void *scratch, void *ops[4], hipStream_t st)
 {
     bem_ctx *ctx = m->ctx;
@@ -1100,15 +1101,18 @@ bem_status launch_regular(const bem_mesh *m, double k, double kim, bool fp32, vo
     int64_t most = 0;
     for (int s = 0; s < ns; ++s) most = std::max(most, strip_tiles(h, s));
     const size_t half = (size_t)most * 4 * SMAX * SMAX * eb;
-    if (!ctx->gather) BEM_HIP(hipStreamCreateWithFlags(&ctx->gather, hipStreamNonBlocking));
-    hipStream_t gs = ctx->gather;
+    const bool one = ns == 1;
+    if (!one && !ctx->gather) BEM_HIP(hipStreamCreateWithFlags(&ctx->gather, hipStreamNonBlocking));
+    hipStream_t gs = one ? st : ctx->gather;
     // events (kept by the context, so that no event is destroyed while a wait on it is queued): [0] main-stream
     // work before the assembly, [1 + b] tiles of half b done, [3 + b] its gather done
     hipEvent_t *ev = ctx->strip_ev;
-    for (int q = 0; q < 5; ++q)
-        if (!ev[q]) BEM_HIP(hipEventCreateWithFlags(&ev[q], hipEventDisableTiming));
-    BEM_HIP(hipEventRecord(ev[0], st));
-    BEM_HIP(hipStreamWaitEvent(gs, ev[0], 0));   // the operator blocks may have served earlier main-stream work
+    if (!one) {
+        for (int q = 0; q < 5; ++q)
+            if (!ev[q]) BEM_HIP(hipEventCreateWithFlags(&ev[q], hipEventDisableTiming));
+        BEM_HIP(hipEventRecord(ev[0], st));
+        BEM_HIP(hipStreamWaitEvent(gs, ev[0], 0));   // the operator blocks may have served earlier main-stream work
+    }
     if ((int64_t)op_ld(nv) > nv) {
         const int64_t npad = (int64_t)nv * (op_ld(nv) - nv);
         const dim3 gz((unsigned)((npad + 255) / 256));
@@ -1164,8 +1168,10 @@ bem_status launch_regular(const bem_mesh *m, double k, double kim, bool fp32, vo
             }
         }
         BEM_HIP(hipGetLastError());
-        BEM_HIP(hipEventRecord(ev[1 + hb], st));
-        BEM_HIP(hipStreamWaitEvent(gs, ev[1 + hb], 0));
+        if (!one) {
+            BEM_HIP(hipEventRecord(ev[1 + hb], st));
+            BEM_HIP(hipStreamWaitEvent(gs, ev[1 + hb], 0));
+        }
         const int r0 = h.strip_rptr[s], nr = h.strip_rptr[s + 1] - r0, lo = h.strip_lo[s];
         const int32_t *rows = m->d.strip_rows.as<int32_t>() + r0;
         const unsigned cr = (unsigned)((nr + 15) / 16);
@@ -1188,9 +1194,9 @@ bem_status launch_regular(const bem_mesh *m, double k, double kim, bool fp32, vo
         }
 #undef GATHER_ARGS
         BEM_HIP(hipGetLastError());
-        BEM_HIP(hipEventRecord(ev[3 + hb], gs));
+        if (!one) BEM_HIP(hipEventRecord(ev[3 + hb], gs));
     }
-    BEM_HIP(hipStreamWaitEvent(st, ev[3 + (ns - 1) % 2], 0));   // gathers run in order: the last covers all
+    if (!one) BEM_HIP(hipStreamWaitEvent(st, ev[3 + (ns - 1) % 2], 0));   // gathers run in order: the last covers all
     return BEM_OK;
 }
 
