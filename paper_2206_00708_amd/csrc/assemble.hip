@@ -145,7 +145,6 @@ constexpr int ST_WAVE = 4 * SROW;       // staged rows of one wave
 constexpr int P_OP = 3 * BT * SMAX + 1; // P rows of one operator, then the zero entry
 constexpr int P_LEN = 3 * P_OP;
 constexpr int SLOT_IT1 = (SMAX + 15) / 16;   // trial-side items per lane (16 slots x 4 rows at a time)
-static_assert(LMAX <= 12, "a run is read as at most 12 entries");
 
 // Orders the wave's LDS accesses before and after it for the compiler; the
 // LDS serves one wave's accesses in the order they are issued.
@@ -155,47 +154,49 @@ __device__ inline void wave_lds_order()
     __builtin_amdgcn_wave_barrier();
 }
 
-// The places of a run of m entries from `first` on by `stride` (m = 0: no run).
+// The places of a run's m entries (m = 0: no run), the others at `zero`.
 // most: the longest run among the lanes that load together, so that they take
 // the same branches.
 struct RunPlaces {
-    int at[6], first, stride, m, zero;
-    __device__ void set(int f, int st, int len, int z)
+    int at[LMAX], m, most;
+    template <class Place> __device__ void set(int len, int zero, Place place)
     {
-        first = f; stride = st; m = len; zero = z;
+        m = len;
+        most = __any(m > 6) ? LMAX : (__any(m > 4) ? 6 : 4);
 #pragma unroll
-        for (int v = 0; v < 6; ++v) at[v] = v < m ? f + v * st : z;
+        for (int v = 0; v < 6; ++v) at[v] = v < m ? place(v) : zero;
+        if (most > 6)
+#pragma unroll
+            for (int v = 6; v < LMAX; ++v) at[v] = v < m ? place(v) : zero;
     }
-    __device__ int place(int v) const { return v < m ? first + v * stride : zero; }
 };
-__device__ inline int run_class(int m) { return __any(m > 6) ? 12 : (__any(m > 4) ? 6 : 4); }
 
 // the entries of a run in `base`, loaded at once, and their sum in run order
 template <class C2> struct RunValues {
-    C2 x[4], y[2], z[6];
-    __device__ void load(const C2 *base, const RunPlaces &p, int most)
+    C2 x[LMAX];
+    __device__ void load(const C2 *base, const RunPlaces &p)
     {
 #pragma unroll
         for (int v = 0; v < 4; ++v) x[v] = base[p.at[v]];
-        if (most > 4) {
+        if (p.most > 4) {
 #pragma unroll
-            for (int v = 0; v < 2; ++v) y[v] = base[p.at[4 + v]];
-            if (most > 6)
+            for (int v = 4; v < 6; ++v) x[v] = base[p.at[v]];
+            if (p.most > 6)
 #pragma unroll
-                for (int v = 0; v < 6; ++v) z[v] = base[p.place(6 + v)];
+                for (int v = 6; v < LMAX; ++v) x[v] = base[p.at[v]];
         }
     }
-    __device__ C2 sum(int most) const
+    __device__ C2 sum(const RunPlaces &p) const
     {
         C2 s = x[0];
 #pragma unroll
         for (int v = 1; v < 4; ++v) { s.x += x[v].x; s.y += x[v].y; }
-        if (most > 4) {
+        if (p.most > 4) {
 #pragma unroll
-            for (int v = 0; v < 2; ++v) { s.x += y[v].x; s.y += y[v].y; }
-            if (most > 6)
+            for (int v = 4; v < 6; ++v) { s.x += x[v].x; s.y += x[v].y; }
+            if (p.most > 6)
 #pragma unroll
-                for (int v = 0; v < 6; ++v) { s.x += z[v].x; s.y += z[v].y; }
+                for (int v = 6; v < LMAX; ++v) { s.x += x[v].x; s.y += x[v].y; }
         }
         return s;
     }
@@ -205,34 +206,33 @@ template <class C2> struct RunValues {
 // operator op at corners (a, b) (called with constants once unrolled, for
 // threads whose pair has a place in the tile only).  st: ST_WAVE entries of
 // this wave; P: P_LEN entries of the workgroup.
+// r1: slot-major rank of each test corner; c2: place in a staged row of the
+// trial corner of each slot-major rank.
 template <class C2, class Entry>
 __device__ inline void tile_slot_sums(int tid, int n1, int n2, int ns1, int ns2, const uint8_t *o1, const uint8_t *o2,
-                                      const uint8_t *r1, const uint8_t *r2, C2 *st, C2 *P, C2 *out, Entry entry)
+                                      const uint8_t *r1, const uint8_t *c2, C2 *st, C2 *P, C2 *out, Entry entry)
 {
     const int lane = tid & 63;
     const int t1 = tid >> 4, t2 = tid & 15;
     const bool staged = t1 < n1 && t2 < n2;
-    int rk[3];
-#pragma unroll
-    for (int b = 0; b < 3; ++b) rk[b] = (t1 & 3) * SROW + (staged ? r2[3 * t2 + b] : 0);
     if (lane < 4) st[lane * SROW + 3 * BT] = C2{0, 0};
     if (tid < 3) P[tid * P_OP + P_OP - 1] = C2{0, 0};
-    // trial-side items of this lane: row (test triangle) lane % 4, slots lane / 4 and so on by 16
-    const int row = lane & 3, ti = 4 * (tid >> 6) + row;
+    // A row is staged corner by corner in the order of the trial triangles (neighbouring lanes write
+    // neighbouring places).  Trial-side items of this lane: row (test triangle) lane / 16, slots
+    // lane % 16 and so on by 16 (neighbouring lanes write neighbouring sums)
+    C2 *const mine = st + (t1 & 3) * SROW + t2;
+    const int row = lane >> 4, ti = 4 * (tid >> 6) + row;
     RunPlaces run1[SLOT_IT1];
     int pr[3];
 #pragma unroll
     for (int j = 0; j < SLOT_IT1; ++j) {
-        const int q2 = (lane >> 2) + 16 * j;
+        const int q2 = (lane & 15) + 16 * j;
         const bool live = q2 < ns2 && ti < n1;
         const int s0 = live ? o2[q2] : 0;
-        run1[j].set(row * SROW + s0, 1, live ? o2[q2 + 1] - s0 : 0, row * SROW + 3 * BT);
+        run1[j].set(live ? o2[q2 + 1] - s0 : 0, row * SROW + 3 * BT, [&](int v) { return row * SROW + c2[s0 + v]; });
     }
-    int most1[SLOT_IT1];
 #pragma unroll
-    for (int j = 0; j < SLOT_IT1; ++j) most1[j] = run_class(run1[j].m);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) pr[a] = (ti < n1 ? r1[3 * ti + a] : 0) * SMAX + (lane >> 2);
+    for (int a = 0; a < 3; ++a) pr[a] = (ti < n1 ? r1[3 * ti + a] : 0) * SMAX + (lane & 15);
     auto test_side = [&](int op0, int nop) {   // operators op0 .. op0 + nop - 1 from the P rows 0 .. nop - 1
         const float inv = 1.0f / (float)ns2;
 #pragma unroll 1
@@ -240,22 +240,21 @@ __device__ inline void tile_slot_sums(int tid, int n1, int n2, int ns1, int ns2,
             const int q1 = (int)(((float)it + 0.5f) * inv), q2 = it - q1 * ns2;
             const int s0 = o1[q1];
             RunPlaces run2;
-            run2.set(s0 * SMAX + q2, SMAX, o1[q1 + 1] - s0, P_OP - 1);
-            const int most2 = run_class(run2.m);
+            run2.set(o1[q1 + 1] - s0, P_OP - 1, [&](int v) { return (s0 + v) * SMAX + q2; });
             C2 *o = out + 4 * (q1 * SMAX + q2) + op0;
 #pragma unroll
             for (int q = 0; q < 3; ++q)
                 if (q < nop) {
                     RunValues<C2> r;
-                    r.load(P + q * P_OP, run2, most2);
-                    o[q] = r.sum(most2);
+                    r.load(P + q * P_OP, run2);
+                    o[q] = r.sum(run2);
                 }
         }
     };
     auto stage = [&](int op, int a) {
         if (staged)
 #pragma unroll
-            for (int b = 0; b < 3; ++b) st[rk[b]] = entry(op, a, b);
+            for (int b = 0; b < 3; ++b) mine[BT * b] = entry(op, a, b);
     };
     stage(0, 0);
 #pragma unroll
@@ -271,13 +270,13 @@ __device__ inline void tile_slot_sums(int tid, int n1, int n2, int ns1, int ns2,
             wave_lds_order();
 #pragma unroll
             for (int j = 0; j < SLOT_IT1; ++j)
-                if (16 * j < ns2) r[j].load(st, run1[j], most1[j]);
+                if (16 * j < ns2) r[j].load(st, run1[j]);
             wave_lds_order();
             if (a < 2) stage(op, a + 1);
             else if (op < 3) stage(op + 1, 0);
 #pragma unroll
             for (int j = 0; j < SLOT_IT1; ++j)
-                if (16 * j < ns2 && run1[j].m > 0) P[(op % 3) * P_OP + pr[a] + 16 * j] = r[j].sum(most1[j]);
+                if (16 * j < ns2 && run1[j].m > 0) P[(op % 3) * P_OP + pr[a] + 16 * j] = r[j].sum(run1[j]);
         }
     }
     __syncthreads();
@@ -449,7 +448,7 @@ __global__ __launch_bounds__(256, 2) void regular_tiles_kernel(TileArgs A, int64
     __shared__ TriGeoLds gX[BT], gY[BT];
     __shared__ int32_t vX[BT * 3], vY[BT * 3];
     __shared__ uint8_t o1[SLOT_OFF_LD], o2[SLOT_OFF_LD];   // first slot-major rank of each slot
-    __shared__ uint8_t r1[3 * BT], r2[3 * BT];             // slot-major rank of each corner
+    __shared__ uint8_t r1[3 * BT], c2[3 * BT];             // slot-major rank of each test corner; see tile_slot_sums
     __shared__ double2 st[4][ST_WAVE];   // each wave's staged rows
     __shared__ double2 P[P_LEN];         // test-corner rank x trial slot partial sums
 
@@ -473,8 +472,9 @@ __global__ __launch_bounds__(256, 2) void regular_tiles_kernel(TileArgs A, int64
             o1[tid] = A.slot_off[(size_t)b1 * SLOT_OFF_LD + tid];
             o2[tid] = A.slot_off[(size_t)b2 * SLOT_OFF_LD + tid];
         } else if (tid >= 64 && tid < 64 + 3 * BT) {
-            r1[tid - 64] = A.slot_rank[(size_t)b1 * 3 * BT + tid - 64];
-            r2[tid - 64] = A.slot_rank[(size_t)b2 * 3 * BT + tid - 64];
+            const int c = tid - 64;
+            r1[c] = A.slot_rank[(size_t)b1 * 3 * BT + c];
+            if (c < 3 * n2) c2[A.slot_rank[(size_t)b2 * 3 * BT + c]] = (uint8_t)(BT * (c % 3) + c / 3);
         }
     }
     __syncthreads();
@@ -509,7 +509,7 @@ __global__ __launch_bounds__(256, 2) void regular_tiles_kernel(TileArgs A, int64
     const TriGeo &Y = gY[t2].g;
     const double nn = X.n[0] * Y.n[0] + X.n[1] * Y.n[1] + X.n[2] * Y.n[2];
     const double k2r = CK ? k * k - A.kim * A.kim : k * k, k2i = 2.0 * k * A.kim;
-    tile_slot_sums(tid, n1, n2, ns1, ns2, o1, o2, r1, r2, st[tid >> 6], P, A.scratch + (tile - A.tile_base) * (4 * SMAX * SMAX),
+    tile_slot_sums(tid, n1, n2, ns1, ns2, o1, o2, r1, c2, st[tid >> 6], P, A.scratch + (tile - A.tile_base) * (4 * SMAX * SMAX),
                    [&](int op, int a, int b) {
                        const int e = 3 * a + b;
                        if (op == 0) return make_double2(vr[e], vi[e]);
@@ -652,7 +652,7 @@ __global__ __launch_bounds__(256, 3) void regular_tiles_f32_kernel(TileArgsF A, 
     __shared__ TriGeoF gX[BT], gY[BT];
     __shared__ int32_t vX[BT * 3], vY[BT * 3];
     __shared__ uint8_t o1[SLOT_OFF_LD], o2[SLOT_OFF_LD];   // first slot-major rank of each slot
-    __shared__ uint8_t r1[3 * BT], r2[3 * BT];             // slot-major rank of each corner
+    __shared__ uint8_t r1[3 * BT], c2[3 * BT];             // slot-major rank of each test corner; see tile_slot_sums
     __shared__ float2 st[4][ST_WAVE];   // each wave's staged rows
     __shared__ float2 P[P_LEN];         // test-corner rank x trial slot partial sums
 
@@ -676,8 +676,9 @@ __global__ __launch_bounds__(256, 3) void regular_tiles_f32_kernel(TileArgsF A, 
             o1[tid] = A.slot_off[(size_t)b1 * SLOT_OFF_LD + tid];
             o2[tid] = A.slot_off[(size_t)b2 * SLOT_OFF_LD + tid];
         } else if (tid >= 64 && tid < 64 + 3 * BT) {
-            r1[tid - 64] = A.slot_rank[(size_t)b1 * 3 * BT + tid - 64];
-            r2[tid - 64] = A.slot_rank[(size_t)b2 * 3 * BT + tid - 64];
+            const int c = tid - 64;
+            r1[c] = A.slot_rank[(size_t)b1 * 3 * BT + c];
+            if (c < 3 * n2) c2[A.slot_rank[(size_t)b2 * 3 * BT + c]] = (uint8_t)(BT * (c % 3) + c / 3);
         }
     }
     __syncthreads();
@@ -702,7 +703,7 @@ __global__ __launch_bounds__(256, 3) void regular_tiles_f32_kernel(TileArgsF A, 
     const TriGeoF &Y = gY[t2];
     const float nn = X.n[0] * Y.n[0] + X.n[1] * Y.n[1] + X.n[2] * Y.n[2];
     const float k2r = CK ? (float)(A.k * A.k - A.kim * A.kim) : kf * kf, k2i = (float)(2.0 * A.k * A.kim);
-    tile_slot_sums(tid, n1, n2, ns1, ns2, o1, o2, r1, r2, st[tid >> 6], P, A.scratch + (tile - A.tile_base) * (4 * SMAX * SMAX),
+    tile_slot_sums(tid, n1, n2, ns1, ns2, o1, o2, r1, c2, st[tid >> 6], P, A.scratch + (tile - A.tile_base) * (4 * SMAX * SMAX),
                    [&](int op, int a, int b) {
                        const int e = 3 * a + b;
                        if (op == 0) return make_float2(vr[e], vi[e]);
