@@ -90,6 +90,7 @@ struct TileArgs {
     const int32_t *blk_nslot;
     const uint8_t *slot_off;    // [nb][SLOT_OFF_LD] first slot-major rank of each slot
     const uint8_t *slot_rank;   // [nb][3 * BT] slot-major rank of each corner
+    const SlotPlaces *slot_place;   // [nb][SMAX]
     int32_t nb;
     double k;
     double kim;            // imaginary part of the wavenumber (read by the absorbing instantiation only)
@@ -154,20 +155,15 @@ __device__ inline void wave_lds_order()
     __builtin_amdgcn_wave_barrier();
 }
 
-// The places of a run's m entries (m = 0: no run), the others at `zero`.
-// most: the longest run among the lanes that load together, so that they take
-// the same branches.
+// The places of a run's m entries as byte offsets (m = 0: no run), the others
+// at an entry that holds zero.  most: the longest run among the lanes that
+// load together, so that they take the same branches.
 struct RunPlaces {
     int at[LMAX], m, most;
-    template <class Place> __device__ void set(int len, int zero, Place place)
+    __device__ void set_length(int len)
     {
         m = len;
         most = __any(m > 6) ? LMAX : (__any(m > 4) ? 6 : 4);
-#pragma unroll
-        for (int v = 0; v < 6; ++v) at[v] = v < m ? place(v) : zero;
-        if (most > 6)
-#pragma unroll
-            for (int v = 6; v < LMAX; ++v) at[v] = v < m ? place(v) : zero;
     }
 };
 
@@ -176,14 +172,16 @@ template <class C2> struct RunValues {
     C2 x[LMAX];
     __device__ void load(const C2 *base, const RunPlaces &p)
     {
+        const char *b = reinterpret_cast<const char *>(base);
+        auto get = [&](int v) { x[v] = *reinterpret_cast<const C2 *>(b + p.at[v]); };
 #pragma unroll
-        for (int v = 0; v < 4; ++v) x[v] = base[p.at[v]];
+        for (int v = 0; v < 4; ++v) get(v);
         if (p.most > 4) {
 #pragma unroll
-            for (int v = 4; v < 6; ++v) x[v] = base[p.at[v]];
+            for (int v = 4; v < 6; ++v) get(v);
             if (p.most > 6)
 #pragma unroll
-                for (int v = 6; v < LMAX; ++v) x[v] = base[p.at[v]];
+                for (int v = 6; v < LMAX; ++v) get(v);
         }
     }
     __device__ C2 sum(const RunPlaces &p) const
@@ -204,32 +202,35 @@ template <class C2> struct RunValues {
 
 // The slot sums of one tile.  entry(op, a, b): this thread's entry of
 // operator op at corners (a, b) (called with constants once unrolled, for
-// threads whose pair has a place in the tile only).  st: ST_WAVE entries of
-// this wave; P: P_LEN entries of the workgroup.
-// r1: slot-major rank of each test corner; c2: place in a staged row of the
-// trial corner of each slot-major rank.
+// threads whose pair has a place in the tile only).  st: the workgroup's
+// staged rows (ST_WAVE entries per wave); P: P_LEN entries.  o1, r1: first
+// slot-major rank of each test slot and rank of each test corner; w2: per trial
+// slot the places of its corners in a staged row and their number (SlotPlaces).
 template <class C2, class Entry>
-__device__ inline void tile_slot_sums(int tid, int n1, int n2, int ns1, int ns2, const uint8_t *o1, const uint8_t *o2,
-                                      const uint8_t *r1, const uint8_t *c2, C2 *st, C2 *P, C2 *out, Entry entry)
+__device__ inline void tile_slot_sums(int tid, int n1, int n2, int ns1, int ns2, const uint8_t *o1, const uint8_t *r1,
+                                      const SlotPlaces *w2, C2 *st, C2 *P, C2 *out, Entry entry)
 {
-    const int lane = tid & 63;
+    constexpr int EB = sizeof(C2);
+    const int lane = tid & 63, wave = tid >> 6;
     const int t1 = tid >> 4, t2 = tid & 15;
     const bool staged = t1 < n1 && t2 < n2;
-    if (lane < 4) st[lane * SROW + 3 * BT] = C2{0, 0};
+    if (lane < 4) st[wave * ST_WAVE + lane * SROW + 3 * BT] = C2{0, 0};
     if (tid < 3) P[tid * P_OP + P_OP - 1] = C2{0, 0};
     // A row is staged corner by corner in the order of the trial triangles (neighbouring lanes write
     // neighbouring places).  Trial-side items of this lane: row (test triangle) lane / 16, slots
     // lane % 16 and so on by 16 (neighbouring lanes write neighbouring sums)
-    C2 *const mine = st + (t1 & 3) * SROW + t2;
-    const int row = lane >> 4, ti = 4 * (tid >> 6) + row;
+    C2 *const mine = st + wave * ST_WAVE + (t1 & 3) * SROW + t2;
+    const int row = lane >> 4, ti = 4 * wave + row;
+    const int row_at = EB * (wave * ST_WAVE + row * SROW);
     RunPlaces run1[SLOT_IT1];
     int pr[3];
 #pragma unroll
     for (int j = 0; j < SLOT_IT1; ++j) {
         const int q2 = (lane & 15) + 16 * j;
-        const bool live = q2 < ns2 && ti < n1;
-        const int s0 = live ? o2[q2] : 0;
-        run1[j].set(live ? o2[q2 + 1] - s0 : 0, row * SROW + 3 * BT, [&](int v) { return row * SROW + c2[s0 + v]; });
+        const SlotPlaces w = w2[min(q2, SMAX - 1)];
+        run1[j].set_length(q2 < ns2 && ti < n1 ? (int)(w.n & 255u) : 0);
+#pragma unroll
+        for (int v = 0; v < LMAX; ++v) run1[j].at[v] = row_at + EB * (int)(w.at[v >> 2] >> (8 * (v & 3)) & 255u);
     }
 #pragma unroll
     for (int a = 0; a < 3; ++a) pr[a] = (ti < n1 ? r1[3 * ti + a] : 0) * SMAX + (lane & 15);
@@ -240,7 +241,9 @@ __device__ inline void tile_slot_sums(int tid, int n1, int n2, int ns1, int ns2,
             const int q1 = (int)(((float)it + 0.5f) * inv), q2 = it - q1 * ns2;
             const int s0 = o1[q1];
             RunPlaces run2;
-            run2.set(o1[q1 + 1] - s0, P_OP - 1, [&](int v) { return (s0 + v) * SMAX + q2; });
+            run2.set_length(o1[q1 + 1] - s0);
+#pragma unroll
+            for (int v = 0; v < LMAX; ++v) run2.at[v] = EB * (v < run2.m ? (s0 + v) * SMAX + q2 : P_OP - 1);
             C2 *o = out + 4 * (q1 * SMAX + q2) + op0;
 #pragma unroll
             for (int q = 0; q < 3; ++q)
@@ -433,6 +436,7 @@ struct TileArgsF {
     const int32_t *blk_nslot;
     const uint8_t *slot_off;    // [nb][SLOT_OFF_LD] first slot-major rank of each slot
     const uint8_t *slot_rank;   // [nb][3 * BT] slot-major rank of each corner
+    const SlotPlaces *slot_place;   // [nb][SMAX]
     int32_t nb;
     double k;
     double kim;            // imaginary part of the wavenumber (read by the absorbing instantiation only)
@@ -447,8 +451,8 @@ __global__ __launch_bounds__(256, 2) void regular_tiles_kernel(TileArgs A, int64
 {
     __shared__ TriGeoLds gX[BT], gY[BT];
     __shared__ int32_t vX[BT * 3], vY[BT * 3];
-    __shared__ uint8_t o1[SLOT_OFF_LD], o2[SLOT_OFF_LD];   // first slot-major rank of each slot
-    __shared__ uint8_t r1[3 * BT], c2[3 * BT];             // slot-major rank of each test corner; see tile_slot_sums
+    __shared__ uint8_t o1[SLOT_OFF_LD], r1[3 * BT];   // see tile_slot_sums
+    __shared__ SlotPlaces w2[SMAX];
     __shared__ double2 st[4][ST_WAVE];   // each wave's staged rows
     __shared__ double2 P[P_LEN];         // test-corner rank x trial slot partial sums
 
@@ -470,11 +474,10 @@ __global__ __launch_bounds__(256, 2) void regular_tiles_kernel(TileArgs A, int64
         if (tid < n2 * 3) vY[tid] = A.tri[3 * s2 + tid];
         if (tid < SLOT_OFF_LD) {
             o1[tid] = A.slot_off[(size_t)b1 * SLOT_OFF_LD + tid];
-            o2[tid] = A.slot_off[(size_t)b2 * SLOT_OFF_LD + tid];
         } else if (tid >= 64 && tid < 64 + 3 * BT) {
-            const int c = tid - 64;
-            r1[c] = A.slot_rank[(size_t)b1 * 3 * BT + c];
-            if (c < 3 * n2) c2[A.slot_rank[(size_t)b2 * 3 * BT + c]] = (uint8_t)(BT * (c % 3) + c / 3);
+            r1[tid - 64] = A.slot_rank[(size_t)b1 * 3 * BT + tid - 64];
+        } else if (tid >= 128 && tid < 128 + SMAX) {
+            w2[tid - 128] = A.slot_place[(size_t)b2 * SMAX + tid - 128];
         }
     }
     __syncthreads();
@@ -509,7 +512,7 @@ __global__ __launch_bounds__(256, 2) void regular_tiles_kernel(TileArgs A, int64
     const TriGeo &Y = gY[t2].g;
     const double nn = X.n[0] * Y.n[0] + X.n[1] * Y.n[1] + X.n[2] * Y.n[2];
     const double k2r = CK ? k * k - A.kim * A.kim : k * k, k2i = 2.0 * k * A.kim;
-    tile_slot_sums(tid, n1, n2, ns1, ns2, o1, o2, r1, c2, st[tid >> 6], P, A.scratch + (tile - A.tile_base) * (4 * SMAX * SMAX),
+    tile_slot_sums(tid, n1, n2, ns1, ns2, o1, r1, w2, &st[0][0], P, A.scratch + (tile - A.tile_base) * (4 * SMAX * SMAX),
                    [&](int op, int a, int b) {
                        const int e = 3 * a + b;
                        if (op == 0) return make_double2(vr[e], vi[e]);
@@ -651,8 +654,8 @@ __global__ __launch_bounds__(256, 3) void regular_tiles_f32_kernel(TileArgsF A, 
 {
     __shared__ TriGeoF gX[BT], gY[BT];
     __shared__ int32_t vX[BT * 3], vY[BT * 3];
-    __shared__ uint8_t o1[SLOT_OFF_LD], o2[SLOT_OFF_LD];   // first slot-major rank of each slot
-    __shared__ uint8_t r1[3 * BT], c2[3 * BT];             // slot-major rank of each test corner; see tile_slot_sums
+    __shared__ uint8_t o1[SLOT_OFF_LD], r1[3 * BT];   // see tile_slot_sums
+    __shared__ SlotPlaces w2[SMAX];
     __shared__ float2 st[4][ST_WAVE];   // each wave's staged rows
     __shared__ float2 P[P_LEN];         // test-corner rank x trial slot partial sums
 
@@ -674,11 +677,10 @@ __global__ __launch_bounds__(256, 3) void regular_tiles_f32_kernel(TileArgsF A, 
         if (tid < n2 * 3) vY[tid] = A.tri[3 * s2 + tid];
         if (tid < SLOT_OFF_LD) {
             o1[tid] = A.slot_off[(size_t)b1 * SLOT_OFF_LD + tid];
-            o2[tid] = A.slot_off[(size_t)b2 * SLOT_OFF_LD + tid];
         } else if (tid >= 64 && tid < 64 + 3 * BT) {
-            const int c = tid - 64;
-            r1[c] = A.slot_rank[(size_t)b1 * 3 * BT + c];
-            if (c < 3 * n2) c2[A.slot_rank[(size_t)b2 * 3 * BT + c]] = (uint8_t)(BT * (c % 3) + c / 3);
+            r1[tid - 64] = A.slot_rank[(size_t)b1 * 3 * BT + tid - 64];
+        } else if (tid >= 128 && tid < 128 + SMAX) {
+            w2[tid - 128] = A.slot_place[(size_t)b2 * SMAX + tid - 128];
         }
     }
     __syncthreads();
@@ -703,7 +705,7 @@ __global__ __launch_bounds__(256, 3) void regular_tiles_f32_kernel(TileArgsF A, 
     const TriGeoF &Y = gY[t2];
     const float nn = X.n[0] * Y.n[0] + X.n[1] * Y.n[1] + X.n[2] * Y.n[2];
     const float k2r = CK ? (float)(A.k * A.k - A.kim * A.kim) : kf * kf, k2i = (float)(2.0 * A.k * A.kim);
-    tile_slot_sums(tid, n1, n2, ns1, ns2, o1, o2, r1, c2, st[tid >> 6], P, A.scratch + (tile - A.tile_base) * (4 * SMAX * SMAX),
+    tile_slot_sums(tid, n1, n2, ns1, ns2, o1, r1, w2, &st[0][0], P, A.scratch + (tile - A.tile_base) * (4 * SMAX * SMAX),
                    [&](int op, int a, int b) {
                        const int e = 3 * a + b;
                        if (op == 0) return make_float2(vr[e], vi[e]);
@@ -1140,6 +1142,7 @@ bem_status launch_regular(const bem_mesh *m, double k, double kim, bool fp32, vo
                 A.blk_nslot = m->d.blk_nslot.as<int32_t>();
                 A.slot_off = m->d.slot_off.as<uint8_t>();
                 A.slot_rank = m->d.slot_rank.as<uint8_t>();
+                A.slot_place = m->d.slot_place.as<SlotPlaces>();
                 A.nb = (int32_t)nb;
                 A.k = k;
                 A.kim = kim;
@@ -1157,6 +1160,7 @@ bem_status launch_regular(const bem_mesh *m, double k, double kim, bool fp32, vo
                 A.blk_nslot = m->d.blk_nslot.as<int32_t>();
                 A.slot_off = m->d.slot_off.as<uint8_t>();
                 A.slot_rank = m->d.slot_rank.as<uint8_t>();
+                A.slot_place = m->d.slot_place.as<SlotPlaces>();
                 A.nb = (int32_t)nb;
                 A.k = k;
                 A.kim = kim;

@@ -69,6 +69,14 @@ struct SingPair {
     int32_t perm;   // px0 | px1<<2 | px2<<4 | py0<<6 | py1<<8 | py2<<10
 };
 
+// The corners of one block slot for the tile kernels: their places in a staged
+// row of the block's 3 BT corners (BT * corner + triangle, 8 bits each; 3 BT, the
+// row's zero entry, past the last) and, in the low byte of n, their number.
+struct alignas(16) SlotPlaces {
+    uint32_t at[LMAX / 4], n;
+};
+static_assert(sizeof(SlotPlaces) == 16, "one 16-byte load per slot");
+
 // Device allocation tracked against the context budget.
 struct DevMem {
     void *ptr = nullptr;
@@ -136,6 +144,7 @@ struct MeshData {
     // slot q (slot_off[b][nslot] = number of corners), slot_rank[b][tlocal * 3 + corner] the corner's rank
     HVec<uint8_t> slot_off;     // [nb][SLOT_OFF_LD]
     HVec<uint8_t> slot_rank;    // [nb][3 * BT]
+    HVec<SlotPlaces> slot_place;   // [nb][SMAX]
     HVec<int32_t> memb_ptr;     // [nv+1]
     HVec<int32_t> memb;         // block<<8 | slot
     // assembly strips: tile rows (first block of the tile) [strip_b[s], strip_b[s+1]), at most ASM_STRIP_TILES
@@ -155,7 +164,7 @@ struct MeshData {
 struct MeshDev {
     DevMem perm;   // caller vertex -> internal vertex (int32)
     DevMem geof;   // TriGeoF table
-    DevMem xyz, tri, blk_start, blk_nslot, slot_off, slot_rank, memb_ptr, memb, sing, near_i, near_j,
+    DevMem xyz, tri, blk_start, blk_nslot, slot_off, slot_rank, slot_place, memb_ptr, memb, sing, near_i, near_j,
         near_ptr, near_src, near_row, star_ptr, star_ent, geo, strip_rows;
 };
 

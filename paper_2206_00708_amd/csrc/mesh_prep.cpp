@@ -408,6 +408,7 @@ bem_status mesh_prepare(MeshData &m, int64_t strip_tiles)
     m.slot_ent.assign((size_t)nb * SMAX * LMAX, 0);
     m.slot_off.assign((size_t)nb * SLOT_OFF_LD, 0);
     m.slot_rank.assign((size_t)nb * 3 * BT, 0);
+    m.slot_place.assign((size_t)nb * SMAX, SlotPlaces{});
     m.memb_ptr.assign(nv + 1, 0);
     // blocks are independent (each writes only its own slot tables): in parallel
     std::atomic<int> slot_err{0};   // 1: vertex overflow, 2: valence
@@ -433,9 +434,15 @@ bem_status mesh_prepare(MeshData &m, int64_t strip_tiles)
             int off = 0;
             for (int q = 0; q < nvs; ++q) {
                 m.slot_off[(size_t)b * SLOT_OFF_LD + q] = (uint8_t)off;
-                for (int v = 0; v < m.slot_cnt[(size_t)b * SMAX + q]; ++v)
-                    m.slot_rank[(size_t)b * 3 * BT + m.slot_ent[((size_t)b * SMAX + q) * LMAX + v]] = (uint8_t)(off + v);
-                off += m.slot_cnt[(size_t)b * SMAX + q];
+                const int cnt = m.slot_cnt[(size_t)b * SMAX + q];
+                SlotPlaces &w = m.slot_place[(size_t)b * SMAX + q];
+                w.n = (uint32_t)cnt;
+                for (int v = 0; v < LMAX; ++v) {
+                    const int c = m.slot_ent[((size_t)b * SMAX + q) * LMAX + v];   // triangle * 3 + corner
+                    if (v < cnt) m.slot_rank[(size_t)b * 3 * BT + c] = (uint8_t)(off + v);
+                    w.at[v / 4] |= (uint32_t)(v < cnt ? BT * (c % 3) + c / 3 : 3 * BT) << (8 * (v % 4));
+                }
+                off += cnt;
             }
             m.slot_off[(size_t)b * SLOT_OFF_LD + nvs] = (uint8_t)off;
         }
