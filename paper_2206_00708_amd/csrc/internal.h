@@ -233,9 +233,9 @@ struct ChebTables {
     HVec<int32_t> rptr;               // [local vertex + 1] row starts into col / val (rows within s - 1 edges)
     HVec<int32_t> col;                // local column index within the patch
     HVec<double> val;
-    int ell_w = 0;                    // the rows as ELL blocks: patch p at ell_w vbeg[p], [q][local row]
-    HVec<uint16_t> ecol;
-    HVec<double> eval;
+    int ell_w = 0;                    // entries beside the diagonal, at most; the rows as ELL blocks [q][local row]:
+    HVec<uint16_t> ecol;              // patch p at ell_w vbeg[p], local columns
+    HVec<double> eval;                // patch p at (ell_w + 1) vbeg[p], the diagonal first
 };
 bem_status cheb_tables(const Csr M[2], int s, ChebTables &T);
 

@@ -158,22 +158,30 @@ bem_status cheb_tables(const Csr M[2], int s, ChebTables &T)
             T.vbeg.push_back((int32_t)T.vert.size());
         }
         T.rptr.push_back((int32_t)T.col.size());
-        // the same rows as ELL blocks of width w per patch, [q][local row], padded with zero entries on the
-        // row's own vertex: the kernel keeps a row's entries in registers for all steps of a launch
+        // the same rows as ELL blocks per patch, [q][local row], for the kernel, which keeps a row's entries in
+        // registers for all steps of a launch: w columns beside the diagonal, padded with zero entries on the
+        // row's own vertex, and w + 1 values, the diagonal first
         int w = 1;
-        for (size_t l = 0; l + 1 < T.rptr.size(); ++l) w = std::max(w, T.rptr[l + 1] - T.rptr[l]);
+        for (size_t l = 0; l + 1 < T.rptr.size(); ++l) w = std::max(w, T.rptr[l + 1] - T.rptr[l] - 1);
         T.ell_w = w;
         T.ecol.assign((size_t)w * T.vert.size(), 0);
-        T.eval.assign((size_t)w * T.vert.size(), 0.0);
+        T.eval.assign((size_t)(w + 1) * T.vert.size(), 0.0);
         for (size_t q = 0; q + 1 < T.vbeg.size(); ++q) {
             const int32_t vb = T.vbeg[q], L = T.vbeg[q + 1] - vb;
+            uint16_t *ec = T.ecol.data() + (size_t)w * vb;
+            double *ev = T.eval.data() + (size_t)(w + 1) * vb;
             for (int32_t l = 0; l < L; ++l) {
                 int e = 0;
-                for (int32_t k = T.rptr[vb + l]; k < T.rptr[vb + l + 1]; ++k, ++e) {
-                    T.ecol[(size_t)w * vb + (size_t)e * L + l] = (uint16_t)T.col[k];
-                    T.eval[(size_t)w * vb + (size_t)e * L + l] = T.val[k];
+                for (int32_t k = T.rptr[vb + l]; k < T.rptr[vb + l + 1]; ++k) {
+                    if (T.col[k] == l) {
+                        ev[l] += T.val[k];
+                        continue;
+                    }
+                    ec[(size_t)e * L + l] = (uint16_t)T.col[k];
+                    ev[(size_t)(e + 1) * L + l] = T.val[k];
+                    ++e;
                 }
-                for (; e < w; ++e) T.ecol[(size_t)w * vb + (size_t)e * L + l] = (uint16_t)l;
+                for (; e < w; ++e) ec[(size_t)e * L + l] = (uint16_t)l;
             }
         }
         return BEM_OK;

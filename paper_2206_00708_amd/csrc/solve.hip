@@ -1005,13 +1005,20 @@ __global__ __launch_bounds__(64 * MASS_WAVES) void mass_rows_kernel(int ne, int 
 // spectrum lies in [1/2, 2] on every P1 mesh (error 4 3^-k after k steps),
 // s steps per launch on the overlapping patches of ChebTables: a workgroup
 // loads its patch's iterate x, residual r and direction d (from y in the
-// first launch), keeps x, r and its rows of M (ELL, up to W entries) in
-// registers and d in LDS, and at step t updates the vertices within s - t
-// edges of its owned range, which read only vertices updated at step t - 1.
-// The owned range's state goes to the other work set (launches alternate
-// between two, so that no patch reads what another writes in the same
-// launch), and in the last launch x goes to z.  Fixed summation order:
+// first launch), keeps x, r and its rows of M (the diagonal and up to W more
+// entries) in registers and d in LDS, and at step t updates the vertices
+// within s - t edges of its owned range, which read only vertices updated at
+// step t - 1.  The owned range's state goes to the other work set (launches
+// alternate between two, so that no patch reads what another writes in the
+// same launch), and in the last launch x goes to z.  Fixed summation order:
 // deterministic.
+// The gathers of d from LDS bound it, then the loads in front of the first
+// step: the diagonal's term comes from registers, d has two copies in turn (one
+// barrier per step), and a workgroup takes up to `nvec` vectors (u = 2 run +
+// vector) with the rows it has loaded, the next one's y read during the steps
+// of the one before.  12 steps on 10,242 + 7,842 vertices: 64 runs 616 -> 421 us,
+// one run 16.2 -> 14.9 us, against the form with the diagonal among eight gathers, two
+// barriers per step and one vector per workgroup.
 struct ChebArgs {
     const int32_t *pmesh, *vbeg, *cnt, *vert;
     const uint16_t *ecol;
@@ -1025,104 +1032,121 @@ struct ChebArgs {
 constexpr double CHEB_THETA = 1.25, CHEB_DELTA = 0.75;   // centre and half-width of [1/2, 2]
 
 template <int RPT, int W>
-__global__ __launch_bounds__(1024) void mass_cheb_kernel(ChebArgs A, int part0, int first, int last, int nsteps,
-                                                          double rho0, const double2 *__restrict__ y, int64_t ystride,
-                                                          double2 *__restrict__ z, int64_t zstride,
+__global__ __launch_bounds__(1024) void mass_cheb_kernel(ChebArgs A, int part0, int nu, int nvec, int first, int last,
+                                                          int nsteps, double rho0, const double2 *__restrict__ y,
+                                                          int64_t ystride, double2 *__restrict__ z, int64_t zstride,
                                                           const double2 *__restrict__ win, double2 *__restrict__ wout,
                                                           int64_t wstride, const KrylovState *__restrict__ st)
 {
-    __shared__ double2 dsh[CHEB_LMAX];
-    const int run = blockIdx.z;
-    if (st && st[run].done) return;
-    const int p = part0 + (int)blockIdx.x, vec = blockIdx.y;
+    __shared__ double2 dsh[2][1024 * RPT];
+    const int p = part0 + (int)blockIdx.x, tid = threadIdx.x;
+    int u = (int)blockIdx.y * nvec;
+    const int u1 = min(u + nvec, nu);
+    if (st) while (u < u1 && st[u >> 1].done) ++u;
+    if (u >= u1) return;
     const int m = A.pmesh[p];
-    const int64_t off = A.base[m] + (int64_t)vec * A.nvm[m];
     const int vb = A.vbeg[p], L = A.vbeg[p + 1] - vb;
     const int32_t *cnt = A.cnt + (int64_t)p * (A.s + 1);
     const int rows = cnt[A.s - 1];   // rows with entries: within s - 1 edges
+    const int own = cnt[0];
     const uint16_t *ec = A.ecol + (int64_t)A.w * vb;
-    const double *ev = A.eval + (int64_t)A.w * vb;
-    const double2 *Xi = win + run * wstride, *Ri = Xi + A.wn, *Di = Ri + A.wn;
-    const double2 *yr = y + run * ystride;
-    const int tid = threadIdx.x;
-    double xr[RPT], xi[RPT], rr[RPT], ri[RPT], dr[RPT], di[RPT], dg[RPT];
-    int cc[RPT][W];
-    double vv[RPT][W];
+    const double *ev = A.eval + (int64_t)(A.w + 1) * vb;
+    double dg[RPT], vd[RPT], vv[RPT][W];
+    // byte offsets into a copy of d; for wide rows two to a register, which costs an instruction for each entry
+    // but spares the registers that would spill
+    constexpr bool PACK = W > 8;
+    constexpr int WC = PACK ? (W + 1) / 2 : W;
+    int gv[RPT], cc[RPT][WC];
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
         const int l = tid + 1024 * k;
-        xr[k] = xi[k] = rr[k] = ri[k] = dr[k] = di[k] = dg[k] = 0.0;
+        gv[k] = l < L ? A.vert[vb + l] : 0;
+        dg[k] = l < L ? A.dinv[vb + l] : 0.0;
+        vd[k] = l < rows ? ev[l] : 0.0;
+#pragma unroll
+        for (int q = 0; q < WC; ++q) cc[k][q] = 0;
 #pragma unroll
         for (int q = 0; q < W; ++q) {
             const bool has = l < rows && q < A.w;
-            cc[k][q] = has ? (int)ec[(int64_t)q * L + l] : 0;
-            vv[k][q] = has ? ev[(int64_t)q * L + l] : 0.0;
-        }
-        if (l < L) {
-            const int64_t g = off + A.vert[vb + l];
-            dg[k] = A.dinv[vb + l];
-            if (first) {
-                const double2 yy = yr[g];
-                rr[k] = yy.x;
-                ri[k] = yy.y;
-                dr[k] = dg[k] * yy.x / CHEB_THETA;
-                di[k] = dg[k] * yy.y / CHEB_THETA;
-            } else {
-                const double2 a = Xi[g], b = Ri[g], c = Di[g];
-                xr[k] = a.x; xi[k] = a.y; rr[k] = b.x; ri[k] = b.y; dr[k] = c.x; di[k] = c.y;
-            }
-            dsh[l] = make_double2(dr[k], di[k]);
+            const int c = (has ? (int)ec[(int64_t)q * L + l] : 0) * (int)sizeof(double2);
+            if (PACK) cc[k][q / 2] |= c << (16 * (q % 2));
+            else cc[k][q] = c;
+            vv[k][q] = has ? ev[(int64_t)(q + 1) * L + l] : 0.0;
         }
     }
     const double sigma1 = CHEB_THETA / CHEB_DELTA;
-    double rho = rho0;
-    __syncthreads();
-    for (int t = 1; t <= nsteps; ++t) {
-        const int act = cnt[A.s - t];
-        double ar[RPT], ai[RPT];
+    double2 yn[RPT];   // the next vector's y (first launch)
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) yn[k] = make_double2(0, 0);
+    if (first)
+#pragma unroll
+        for (int k = 0; k < RPT; ++k)
+            if (tid + 1024 * k < L) yn[k] = y[(u >> 1) * ystride + A.base[m] + (int64_t)(u & 1) * A.nvm[m] + gv[k]];
+    while (u < u1) {
+        const int run = u >> 1;
+        const int64_t off = A.base[m] + (int64_t)(u & 1) * A.nvm[m];
+        double xr[RPT], xi[RPT], rr[RPT], ri[RPT], dr[RPT], di[RPT];
 #pragma unroll
         for (int k = 0; k < RPT; ++k) {
-            ar[k] = ai[k] = 0.0;
-            if (tid + 1024 * k < act)
+            xr[k] = xi[k] = rr[k] = ri[k] = dr[k] = di[k] = 0.0;
+            const int l = tid + 1024 * k;
+            if (l >= L) continue;
+            if (first) {
+                rr[k] = yn[k].x;
+                ri[k] = yn[k].y;
+                dr[k] = dg[k] * rr[k] / CHEB_THETA;
+                di[k] = dg[k] * ri[k] / CHEB_THETA;
+            } else {
+                const double2 *Xi = win + run * wstride + off + gv[k];
+                const double2 a = Xi[0], b = Xi[A.wn], c = Xi[2 * A.wn];
+                xr[k] = a.x; xi[k] = a.y; rr[k] = b.x; ri[k] = b.y; dr[k] = c.x; di[k] = c.y;
+            }
+            dsh[0][l] = make_double2(dr[k], di[k]);
+        }
+        do ++u;
+        while (st && u < u1 && st[u >> 1].done);
+        if (first && u < u1)
+#pragma unroll
+            for (int k = 0; k < RPT; ++k)
+                if (tid + 1024 * k < L) yn[k] = y[(u >> 1) * ystride + A.base[m] + (int64_t)(u & 1) * A.nvm[m] + gv[k]];
+        double rho = rho0;
+        __syncthreads();
+        for (int t = 1; t <= nsteps; ++t) {
+            const int act = cnt[A.s - t];
+            const char *dp = reinterpret_cast<const char *>(dsh[(t - 1) & 1]);
+            const double rho_new = 1.0 / (2.0 * sigma1 - rho);
+            const double c1 = rho_new * rho, c2 = 2.0 * rho_new / CHEB_DELTA;
+#pragma unroll
+            for (int k = 0; k < RPT; ++k) {
+                const int l = tid + 1024 * k;
+                if (l >= act) continue;
+                double ar = vd[k] * dr[k], ai = vd[k] * di[k];
 #pragma unroll
                 for (int q = 0; q < W; ++q) {
-                    const double2 dd = dsh[cc[k][q]];
-                    ar[k] += vv[k][q] * dd.x;
-                    ai[k] += vv[k][q] * dd.y;
+                    const unsigned c = PACK ? ((unsigned)cc[k][q / 2] >> (16 * (q % 2))) & 0xffffu : (unsigned)cc[k][q];
+                    const double2 dd = *reinterpret_cast<const double2 *>(dp + c);
+                    ar += vv[k][q] * dd.x;
+                    ai += vv[k][q] * dd.y;
                 }
-        }
-        __syncthreads();
-        const double rho_new = 1.0 / (2.0 * sigma1 - rho);
-        const double c1 = rho_new * rho, c2 = 2.0 * rho_new / CHEB_DELTA;
-#pragma unroll
-        for (int k = 0; k < RPT; ++k) {
-            const int l = tid + 1024 * k;
-            if (l < act) {
                 xr[k] += dr[k];
                 xi[k] += di[k];
-                rr[k] -= ar[k];
-                ri[k] -= ai[k];
+                rr[k] -= ar;
+                ri[k] -= ai;
                 dr[k] = c1 * dr[k] + c2 * dg[k] * rr[k];
                 di[k] = c1 * di[k] + c2 * dg[k] * ri[k];
-                dsh[l] = make_double2(dr[k], di[k]);
+                dsh[t & 1][l] = make_double2(dr[k], di[k]);
             }
+            rho = rho_new;
+            __syncthreads();   // also in front of the next vector's first copy of d
         }
-        rho = rho_new;
-        __syncthreads();
-    }
-    const int own = cnt[0];
-    double2 *Xo = wout + run * wstride, *Ro = Xo + A.wn, *Do = Ro + A.wn;
+        double2 *zo = last ? z + run * zstride + off : wout + run * wstride + off;
 #pragma unroll
-    for (int k = 0; k < RPT; ++k) {
-        const int l = tid + 1024 * k;
-        if (l < own) {
-            const int64_t g = off + A.vert[vb + l];
-            if (last) {
-                z[run * zstride + g] = make_double2(xr[k], xi[k]);
-            } else {
-                Xo[g] = make_double2(xr[k], xi[k]);
-                Ro[g] = make_double2(rr[k], ri[k]);
-                Do[g] = make_double2(dr[k], di[k]);
+        for (int k = 0; k < RPT; ++k) {
+            if (tid + 1024 * k >= own) continue;
+            zo[gv[k]] = make_double2(xr[k], xi[k]);
+            if (!last) {
+                zo[A.wn + gv[k]] = make_double2(rr[k], ri[k]);
+                zo[2 * A.wn + gv[k]] = make_double2(dr[k], di[k]);
             }
         }
     }
@@ -1864,13 +1888,28 @@ constexpr int CHEB_PRECOND_STEPS = 12;
 int cheb_precond_steps(const bem_problem *p) { return std::min(CHEB_PRECOND_STEPS, cheb_steps(p)); }
 
 template <int RPT, int W>
-void launch_cheb(const bem_problem *p, dim3 grid, hipStream_t st, const ChebArgs &A, int part0, int first, int last,
-                 int nsteps, double rho, const double2 *y, int64_t ystride, double2 *z, int64_t zstride,
+void launch_cheb(const bem_problem *p, dim3 grid, hipStream_t st, const ChebArgs &A, int part0, int nu, int nvec, int first,
+                 int last, int nsteps, double rho, const double2 *y, int64_t ystride, double2 *z, int64_t zstride,
                  const double2 *win, double2 *wout, int64_t wstride, const KrylovState *kst)
 {
     KTimer kt(p->ctx, K_MASS_APPLY);
-    launch_k(kt, mass_cheb_kernel<RPT, W>, grid, dim3(1024), 0, st, A, part0, first, last, nsteps, rho, y, ystride, z,
-             zstride, win, wout, wstride, kst);
+    launch_k(kt, mass_cheb_kernel<RPT, W>, grid, dim3(1024), 0, st, A, part0, nu, nvec, first, last, nsteps, rho, y,
+             ystride, z, zstride, win, wout, wstride, kst);
+}
+
+// Vectors per workgroup of one launch over np patches and nu vectors: a
+// workgroup takes a compute unit to itself (registers), and loading a patch's
+// rows costs about half of the steps on one vector, so more vectors pay as
+// long as they do not lengthen the launch's last round of workgroups.
+int cheb_vectors(int np, int nu, int ncu)
+{
+    int best = 1;
+    double cost = 1e300;
+    for (int v = 1; v <= 8 && v <= nu; ++v) {
+        const double c = (((int64_t)np * ((nu + v - 1) / v) + ncu - 1) / ncu) * (v + 0.5);
+        if (c < cost) { cost = c; best = v; }
+    }
+    return best;
 }
 
 // z = M^-1 y by K steps of the sparse Chebyshev apply on the patches
@@ -1901,22 +1940,26 @@ bem_status cheb_apply(const bem_problem *p, int part0, int np, int64_t base0, in
     const double sigma1 = CHEB_THETA / CHEB_DELTA;
     double rho = 1.0 / sigma1;
     const int rpt = (T.lmax + 1023) / 1024;
-    const dim3 grid(np, 2, R);
+    const int nu = 2 * R, nvec = cheb_vectors(np, nu, 256);
+    const dim3 grid(np, (nu + nvec - 1) / nvec);
     hipStream_t st = p->ctx->stream;
     for (int j = 0; j < nl; ++j) {
         const int steps = std::min(T.s, K - j * T.s);
         const double2 *win = work + (j % 2) * 3 * wn;
         double2 *wout = work + ((j + 1) % 2) * 3 * wn;
         const int first = j == 0, last = j == nl - 1;
-#define CHEB_ARGS p, grid, st, A, part0, first, last, steps, rho, y, ystride, z, zstride, win, wout, wstride, kst
+#define CHEB_ARGS \
+    p, grid, st, A, part0, nu, nvec, first, last, steps, rho, y, ystride, z, zstride, win, wout, wstride, kst
         if (rpt <= 1) {
-            if (T.ell_w <= 8) launch_cheb<1, 8>(CHEB_ARGS);
-            else if (T.ell_w <= 12) launch_cheb<1, 12>(CHEB_ARGS);
-            else launch_cheb<1, 16>(CHEB_ARGS);
+            if (T.ell_w <= 6) launch_cheb<1, 6>(CHEB_ARGS);
+            else if (T.ell_w <= 8) launch_cheb<1, 8>(CHEB_ARGS);
+            else if (T.ell_w <= 11) launch_cheb<1, 11>(CHEB_ARGS);
+            else launch_cheb<1, CHEB_WMAX - 1>(CHEB_ARGS);
         } else {
-            if (T.ell_w <= 8) launch_cheb<2, 8>(CHEB_ARGS);
-            else if (T.ell_w <= 12) launch_cheb<2, 12>(CHEB_ARGS);
-            else launch_cheb<2, 16>(CHEB_ARGS);
+            if (T.ell_w <= 6) launch_cheb<2, 6>(CHEB_ARGS);
+            else if (T.ell_w <= 8) launch_cheb<2, 8>(CHEB_ARGS);
+            else if (T.ell_w <= 11) launch_cheb<2, 11>(CHEB_ARGS);
+            else launch_cheb<2, CHEB_WMAX - 1>(CHEB_ARGS);
         }
 #undef CHEB_ARGS
         BEM_HIP(hipGetLastError());

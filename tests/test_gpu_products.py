@@ -108,3 +108,53 @@ def test_dense_mass_apply_either_side_of_lds(ne, ni):
         y.append(p.mtf_matvec(torch.from_numpy(x[0] + 1j * x[1]), strong=True).cpu().numpy())
         del p
     assert _rel(y[0], y[1]) < 1e-13
+
+
+def _rosette(n, points):
+    """A sphere of about `points` vertices of valence up to 7, one of valence n."""
+    from scipy.spatial import ConvexHull
+    x = synth.fibonacci_sphere(points)[0]
+    h = np.sqrt(4 * np.pi / points)
+    a = max(n / (2 * np.pi), 1.0) * h
+    ph = 2 * np.pi * np.arange(n) / n + 0.01
+    ring = np.stack([np.sin(a) * np.cos(ph), np.sin(a) * np.sin(ph), 0 * ph + np.cos(a)], axis=1)
+    x = np.concatenate([x[np.arccos(np.clip(x[:, 2], -1, 1)) > a + 0.8 * h], [[0, 0, 1.0]], ring])
+    return x, synth.orient_outward(x, ConvexHull(x).simplices.astype(np.int32))
+
+
+# the widths of the sparse apply's rows (6, 8, 11 and 15 neighbours) at their ends, in patches of one vertex
+# per thread and of two
+@pytest.mark.parametrize("n", [6, 7, 8, 9, 11, 12, 15])
+@pytest.mark.parametrize("points", [162, 2562])
+def test_sparse_mass_row_widths(n, points):
+    """Sparse against dense, both FP64: areas of a mesh's vertices differ by up
+    to a factor of about 10, so rounding (1e-16 by 36 steps) stays below 1e-12."""
+    ctx = B.Context(0)
+    y = []
+    xyz, tri = synth.icosphere(2 if points == 162 else 4) if n == 6 else _rosette(n, points)
+    assert np.bincount(tri.ravel()).max() == n
+    m = B.Mesh(ctx, xyz, tri)
+    for mode in (1, 2):
+        p = B.Problem(ctx, m, m, 2.0, 3.0, 1.0, 1.5, precision=B.C128)
+        p.set_mass_apply(mode)
+        p.assemble_operators()
+        p.assemble_projection()
+        assert p.mass_apply_sparse() == (mode == 2)
+        x = np.random.default_rng(9).standard_normal((2, p.n))
+        y.append(p.mtf_matvec(torch.from_numpy(x[0] + 1j * x[1]), strong=True).cpu().numpy())
+    assert _rel(y[1], y[0]) < 1e-12
+
+
+@pytest.mark.parametrize("ne,ni,R", [(642, 642, 64), (1500, 700, 37), (2600, 2000, 64)])
+def test_sparse_mass_several_vectors_a_workgroup(ne, ni, R):
+    """Runs that are one vector times powers of two: the same bits but for the exponent."""
+    p = _problem(B.Context(0), ne, ni, B.C64_MIXED, 2)
+    assert p.mass_apply_sparse()
+    x = np.random.default_rng(3).standard_normal((2, p.n))
+    scale = 2.0 ** (np.arange(R) % 9 - 4)
+    X = scale[:, None] * (x[0] + 1j * x[1])
+    Y = p.mtf_matvec_batch(torch.from_numpy(X), strong=True).cpu().numpy()
+    assert np.abs(Y[0]).max() > 0 and all(np.array_equal(Y[r] / scale[r], Y[0] / scale[0]) for r in range(R))
+    # one vector alone: the FP32 sums of another tile width, times at most 2 by M^-1
+    one = p.mtf_matvec_batch(torch.from_numpy(X[:1]), strong=True).cpu().numpy()
+    assert _rel(Y[0], one[0]) < 4e-6
