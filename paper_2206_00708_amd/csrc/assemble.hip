@@ -56,6 +56,7 @@ __global__ void geometry_kernel(const double *__restrict__ xyz, const int32_t *_
     double len = sqrt(dot3(cr, cr));
     g.area = 0.5 * len;
     for (int c = 0; c < 3; ++c) g.n[c] = cr[c] / len;
+    g.off = dot3(g.n, g.p[0]);
     for (int a = 0; a < 3; ++a)
         for (int c = 0; c < 3; ++c) g.curl[a][c] = (g.p[(a + 1) % 3][c] - g.p[(a + 2) % 3][c]) / len;
 #pragma unroll
@@ -94,8 +95,8 @@ struct TileArgs {
     int32_t nb;
     double k;
     double kim;            // imaginary part of the wavenumber (read by the absorbing instantiation only)
-    double2 *scratch;      // [tile - tile_base][SMAX*SMAX][op]
-    int64_t tile_base;     // first tile of the strip the scratch holds
+    double2 *scratch;      // [tile of the strip][SMAX*SMAX][op]
+    int32_t b0, nrow;      // first tile row of the strip, rows
 };
 
 // tiles of assembly strip s: rows b in [strip_b[s], strip_b[s + 1]), nb - b each
@@ -106,17 +107,79 @@ inline int64_t strip_tiles(const MeshData &h, int s)
     return n;
 }
 
-__device__ inline void tile_of(int64_t t, int nb, int &b1, int &b2)
+// The tiles (b1, b2), b1 <= b2, of a strip's rows b0 .. b0 + nrow - 1: row i of the grid holds row i
+// of the strip, nb - b0 - i tiles, and after it row nrow - 1 - i, so that all rows of the grid are of one
+// length; a middle row fills the first part of its grid row only (false past its end).
+inline dim3 tile_grid(int nb, int b0, int nrow) { return dim3(2 * (nb - b0) - (nrow - 1), (nrow + 1) / 2); }
+template <class TA> __device__ inline bool tile_of(const TA &A, int &b1, int &b2)
 {
-    // tiles enumerate (b1, b2), b1 <= b2, row by row; offset(b) = b*nb - b*(b-1)/2
-    double B = 2.0 * nb + 1.0;
-    int b = (int)floor(0.5 * (B - sqrt(B * B - 8.0 * (double)t)));
-    if (b < 0) b = 0;
-    if (b > nb - 1) b = nb - 1;
-    while (b > 0 && (int64_t)b * nb - (int64_t)b * (b - 1) / 2 > t) --b;
-    while (b + 1 < nb && (int64_t)(b + 1) * nb - (int64_t)(b + 1) * b / 2 <= t) ++b;
-    b1 = b;
-    b2 = b + (int)(t - ((int64_t)b * nb - (int64_t)b * (b - 1) / 2));
+    const int i = blockIdx.y, x = blockIdx.x, len = A.nb - A.b0 - i;
+    b1 = A.b0 + (x < len ? i : A.nrow - 1 - i);
+    b2 = b1 + (x < len ? x : x - len);
+    return x < len || A.nrow - 1 - i > i;
+}
+
+// the blocks of a tile: first triangle, triangles and slots of each
+struct TileBlocks {
+    int b1, b2, s1, n1, s2, n2, ns1, ns2;
+    int64_t at;   // the tile's place in the scratch: row by row from the strip's first
+    template <class TA> __device__ TileBlocks(const TA &A, int b1_, int b2_) : b1(b1_), b2(b2_)
+    {
+        s1 = A.blk_start[b1];
+        n1 = A.blk_start[b1 + 1] - s1;
+        s2 = A.blk_start[b2];
+        n2 = A.blk_start[b2 + 1] - s2;
+        ns1 = A.blk_nslot[b1];
+        ns2 = A.blk_nslot[b2];
+        const int64_t i = b1 - A.b0;
+        at = i * (A.nb - A.b0) - i * (i - 1) / 2 + (b2 - b1);
+    }
+};
+
+// A tile's tables come to LDS by loads that are all in flight at once: a
+// triangle's members by eight threads, then one 32-bit word per thread of
+// the corners' vertices and the slot tables, in the order of TileSlots.  (One
+// loop per table waits for memory in each of its turns, and at two or three
+// workgroups per compute unit nothing hides that: 10,242 + 7,842 vertices
+// FP64 60.2 -> 54.2 ms, mixed 37.3 -> 35.4 ms, with the tile numbers from the
+// grid in place of a square root.)
+struct TileSlots {
+    int32_t vtx[2 * 3 * BT];        // corners' vertices
+    uint8_t r1[3 * BT];             // rank of each test corner
+    SlotPlaces w2[SMAX];
+    uint8_t o1[SLOT_OFF_LD];        // see tile_slot_sums
+};
+
+constexpr int TW_R1 = 6 * BT, TW_W2 = TW_R1 + 3 * BT / 4, TW_O1 = TW_W2 + SMAX * (int)sizeof(SlotPlaces) / 4,
+              TW_END = TW_O1 + SLOT_OFF_LD / 4;
+static_assert(TW_END <= 256 && offsetof(TileSlots, r1) == 4 * TW_R1 && offsetof(TileSlots, w2) == 4 * TW_W2 &&
+                  offsetof(TileSlots, o1) == 4 * TW_O1,
+              "one word per thread");
+
+template <class TA> __device__ inline uint32_t tile_slots_word(const TA &A, const TileBlocks &B, int tid)
+{
+    // one load for all; vertices of triangles past a block's last repeat its last
+    const uint32_t *p = reinterpret_cast<const uint32_t *>(A.tri) + 3 * B.s1;
+    int i = min(tid, 3 * B.n1 - 1);
+    if (tid >= 3 * BT) { p = reinterpret_cast<const uint32_t *>(A.tri) + 3 * B.s2; i = min(tid - 3 * BT, 3 * B.n2 - 1); }
+    if (tid >= TW_R1) { p = reinterpret_cast<const uint32_t *>(A.slot_rank) + B.b1 * (3 * BT / 4); i = tid - TW_R1; }
+    if (tid >= TW_W2) { p = reinterpret_cast<const uint32_t *>(A.slot_place + (int64_t)B.b2 * SMAX); i = tid - TW_W2; }
+    if (tid >= TW_O1) {
+        p = reinterpret_cast<const uint32_t *>(A.slot_off) + B.b1 * (SLOT_OFF_LD / 4);
+        i = min(tid, TW_END - 1) - TW_O1;
+    }
+    return p[i];
+}
+
+// The pair (test triangle t1, trial triangle t2) has a place in the tile and shares no vertex.
+__device__ inline bool tile_pair_active(const TileSlots &S, const TileBlocks &B, int t1, int t2)
+{
+    bool active = t1 < B.n1 && t2 < B.n2;
+    if (active) {
+        for (int a = 0; a < 3; ++a)
+            for (int b = 0; b < 3; ++b) active = active && (S.vtx[3 * t1 + a] != S.vtx[3 * BT + 3 * t2 + b]);
+    }
+    return active;
 }
 
 // Per-slot sums of the 9 entries of every triangle pair of the tile:
@@ -310,6 +373,16 @@ template <class R> struct Rule6Sum {
     }
 };
 
+// A triangle's table in LDS: TriGeo up to its vertices, padded to an odd number of 16-byte units (19): the 16
+// trial triangles a wave reads at once then fall on distinct LDS banks.
+struct alignas(16) TileGeo {
+    double qp[6][3], n[3], off, area, c[3], rho, curl[3][3];
+    double pad[2];
+};
+static_assert(sizeof(TileGeo) == (TRI_TILE + 2) * sizeof(double) && offsetof(TriGeo, p) == TRI_TILE * sizeof(double) &&
+                  offsetof(TileGeo, curl) == offsetof(TriGeo, curl),
+              "LDS tables of the tile kernels");
+
 // 6 x 6 point pairs of one regular triangle pair (x on X, y on Y): the 3 x 3
 // element sums of V (kernel G), K (dG/dn_y), T (dG/dn_x) and the scalar sum
 // of G, unscaled (times area_X area_Y / (4 pi) later).  K and T use that
@@ -319,12 +392,12 @@ template <class R> struct Rule6Sum {
 // to 1/2 radian off it), whose factor exp(i k r0) is applied to the sums.  CK:
 // complex wavenumber k + i kim.
 template <bool CK, int BASE>
-__device__ inline void pair_quadrature(const TriGeo &X, const TriGeo &Y, double k, double kim, double (&vr)[9],
+__device__ inline void pair_quadrature(const TileGeo &X, const TileGeo &Y, double k, double kim, double (&vr)[9],
                                        double (&vi)[9], double (&kr)[9], double (&ki)[9], double (&tr)[9],
                                        double (&ti)[9], double &sr, double &si)
 {
     const double ny0 = Y.n[0], ny1 = Y.n[1], ny2 = Y.n[2];
-    const double ey0 = ny0 * Y.p[0][0] + ny1 * Y.p[0][1] + ny2 * Y.p[0][2];   // n_y . (a vertex of Y)
+    const double ey0 = Y.off;
     double e0r = 1.0, e0i = 0.0, kr0 = 0.0;
     if constexpr (BASE) {
         const double c0 = X.c[0] - Y.c[0], c1 = X.c[1] - Y.c[1], c2 = X.c[2] - Y.c[2];
@@ -334,7 +407,7 @@ __device__ inline void pair_quadrature(const TriGeo &X, const TriGeo &Y, double 
     double dtq[6];   // (x - y).n_x
     {
         const double nx0 = X.n[0], nx1 = X.n[1], nx2 = X.n[2];
-        const double ex0 = nx0 * X.p[0][0] + nx1 * X.p[0][1] + nx2 * X.p[0][2];
+        const double ex0 = X.off;
 #pragma unroll
         for (int q = 0; q < 6; ++q) dtq[q] = ex0 - (nx0 * Y.qp[q][0] + nx1 * Y.qp[q][1] + nx2 * Y.qp[q][2]);
     }
@@ -420,15 +493,6 @@ __device__ inline void pair_quadrature(const TriGeo &X, const TriGeo &Y, double 
     for (int e = 0; e < 9; ++e) { sr += vr[e]; si += vi[e]; }
 }
 
-// A triangle's table in LDS, padded to an odd number of 16-byte units (23):
-// the 16 trial triangles a wave reads at once then fall on distinct LDS banks
-// (the unpadded 22 units put triangles t and t + 8 on the same banks).
-struct alignas(16) TriGeoLds {
-    TriGeo g;
-    double pad[2];
-};
-static_assert(sizeof(TriGeoLds) % 32 == 16, "LDS stride of the triangle tables must be an odd number of 16-byte units");
-
 struct TileArgsF {
     const TriGeoF *geof;
     const int32_t *tri;
@@ -440,79 +504,63 @@ struct TileArgsF {
     int32_t nb;
     double k;
     double kim;            // imaginary part of the wavenumber (read by the absorbing instantiation only)
-    float2 *scratch;       // [tile - tile_base][SMAX*SMAX][op]
-    int64_t tile_base;
+    float2 *scratch;       // [tile of the strip][SMAX*SMAX][op]
+    int32_t b0, nrow;      // first tile row of the strip, rows
 };
 
 // CK: complex wavenumber k + i kim (an absorbing medium), G = exp(i k r - kim r) / (4 pi r);
 // the real-k instantiation is the one the benchmarks time.
 template <bool CK>
-__global__ __launch_bounds__(256, 2) void regular_tiles_kernel(TileArgs A, int64_t tile0)
+__global__ __launch_bounds__(256, 2) void regular_tiles_kernel(TileArgs A)
 {
-    __shared__ TriGeoLds gX[BT], gY[BT];
-    __shared__ int32_t vX[BT * 3], vY[BT * 3];
-    __shared__ uint8_t o1[SLOT_OFF_LD], r1[3 * BT];   // see tile_slot_sums
-    __shared__ SlotPlaces w2[SMAX];
+    __shared__ TileGeo geo[2 * BT];      // the test block's triangles, then the trial block's
+    __shared__ TileSlots S;
     __shared__ double2 st[4][ST_WAVE];   // each wave's staged rows
     __shared__ double2 P[P_LEN];         // test-corner rank x trial slot partial sums
 
-    const int64_t tile = tile0 + blockIdx.x;
     int b1, b2;
-    tile_of(tile, A.nb, b1, b2);
-    const int s1 = A.blk_start[b1], n1 = A.blk_start[b1 + 1] - s1;
-    const int s2 = A.blk_start[b2], n2 = A.blk_start[b2 + 1] - s2;
-    const int ns1 = A.blk_nslot[b1], ns2 = A.blk_nslot[b2];
-    const int tid = threadIdx.x;
+    if (!tile_of(A, b1, b2)) return;
+    const TileBlocks B(A, b1, b2);
+    const int tid = threadIdx.x, t1 = tid >> 4, t2 = tid & 15;
     {
-        const double *src1 = reinterpret_cast<const double *>(A.geo + s1);
-        const double *src2 = reinterpret_cast<const double *>(A.geo + s2);
-        double *d1 = reinterpret_cast<double *>(gX), *d2 = reinterpret_cast<double *>(gY);
-        constexpr int w = sizeof(TriGeo) / sizeof(double), wl = sizeof(TriGeoLds) / sizeof(double);
-        for (int q = tid; q < n1 * w; q += 256) d1[(q / w) * wl + q % w] = src1[q];
-        for (int q = tid; q < n2 * w; q += 256) d2[(q / w) * wl + q % w] = src2[q];
-        if (tid < n1 * 3) vX[tid] = A.tri[3 * s1 + tid];
-        if (tid < n2 * 3) vY[tid] = A.tri[3 * s2 + tid];
-        if (tid < SLOT_OFF_LD) {
-            o1[tid] = A.slot_off[(size_t)b1 * SLOT_OFF_LD + tid];
-        } else if (tid >= 64 && tid < 64 + 3 * BT) {
-            r1[tid - 64] = A.slot_rank[(size_t)b1 * 3 * BT + tid - 64];
-        } else if (tid >= 128 && tid < 128 + SMAX) {
-            w2[tid - 128] = A.slot_place[(size_t)b2 * SMAX + tid - 128];
-        }
+        constexpr int GN = (TRI_TILE + 7) / 8;
+        const int t = tid >> 3;   // (triangles past a block's last repeat its last)
+        const double *src = reinterpret_cast<const double *>(
+            A.geo + (t < BT ? B.s1 + min(t, B.n1 - 1) : B.s2 + min(t - BT, B.n2 - 1)));
+        double g[GN];
+#pragma unroll
+        for (int i = 0; i < GN; ++i) g[i] = src[min((tid & 7) + 8 * i, TRI_TILE - 1)];
+        const uint32_t w = tile_slots_word(A, B, tid);
+#pragma unroll
+        for (int i = 0; i < GN; ++i)
+            if ((tid & 7) + 8 * i < TRI_TILE) reinterpret_cast<double *>(geo + t)[(tid & 7) + 8 * i] = g[i];
+        if (tid < TW_END) reinterpret_cast<uint32_t *>(&S)[tid] = w;
     }
     __syncthreads();
-
-    const int t1 = tid >> 4, t2 = tid & 15;
-    bool active = t1 < n1 && t2 < n2;
-    if (active) {
-        for (int a = 0; a < 3; ++a)
-            for (int b = 0; b < 3; ++b) active = active && (vX[3 * t1 + a] != vY[3 * t2 + b]);
-    }
+    const double k = A.k;
+    const double k2r = CK ? k * k - A.kim * A.kim : k * k, k2i = 2.0 * k * A.kim;
+    const TileGeo &X = geo[t1], &Y = geo[BT + t2];
+    const bool active = tile_pair_active(S, B, t1, t2);
     double vr[9], vi[9], kr[9], ki[9], tr[9], ti[9], sr = 0.0, si = 0.0;
 #pragma unroll
     for (int e = 0; e < 9; ++e) { vr[e] = vi[e] = kr[e] = ki[e] = tr[e] = ti[e] = 0.0; }
-    const double k = A.k;
     // Phase by a per-pair base where k (rho_X + rho_Y) <= 1 for every pair of
     // the wave: with r0 the centroid distance, |k (r - r0)| <= 1 for every
     // point pair, so exp(i k r) = exp(i k r0) exp(i k (r - r0)) takes one
     // reduced sin/cos per pair and short polynomials per point pair (shorter
     // ones up to 1/2).  The choice is the wave's, so that its lanes run one
     // of the three forms.
-    const double spread = active ? k * (gX[t1].g.rho + gY[t2].g.rho) : 0.0;
+    const double spread = active ? k * (X.rho + Y.rho) : 0.0;
     const int base = CK || __any(spread > 1.0) ? 0 : (__any(spread > 0.5) ? 1 : 2);
     if (active) {
-        const TriGeo &X = gX[t1].g;
-        const TriGeo &Y = gY[t2].g;
         if (base == 2) pair_quadrature<CK, CK ? 0 : 2>(X, Y, k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
         else if (base == 1) pair_quadrature<CK, CK ? 0 : 1>(X, Y, k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
         else pair_quadrature<CK, 0>(X, Y, k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
     }
 
-    const TriGeo &X = gX[t1].g;
-    const TriGeo &Y = gY[t2].g;
     const double nn = X.n[0] * Y.n[0] + X.n[1] * Y.n[1] + X.n[2] * Y.n[2];
-    const double k2r = CK ? k * k - A.kim * A.kim : k * k, k2i = 2.0 * k * A.kim;
-    tile_slot_sums(tid, n1, n2, ns1, ns2, o1, r1, w2, &st[0][0], P, A.scratch + (tile - A.tile_base) * (4 * SMAX * SMAX),
+    tile_slot_sums(tid, B.n1, B.n2, B.ns1, B.ns2, S.o1, S.r1, S.w2, &st[0][0], P,
+                   A.scratch + B.at * (4 * SMAX * SMAX),
                    [&](int op, int a, int b) {
                        const int e = 3 * a + b;
                        if (op == 0) return make_double2(vr[e], vi[e]);
@@ -650,62 +698,48 @@ __device__ inline void pair_quadrature_f32(const TriGeoF &X, const TriGeoF &Y, d
 // Mixed-precision form of the regular-pair tile: FP32 arithmetic (the phase
 // in FP64 once per triangle pair), complex64 tiles.
 template <bool CK>
-__global__ __launch_bounds__(256, 3) void regular_tiles_f32_kernel(TileArgsF A, int64_t tile0)
+__global__ __launch_bounds__(256, 3) void regular_tiles_f32_kernel(TileArgsF A)
 {
-    __shared__ TriGeoF gX[BT], gY[BT];
-    __shared__ int32_t vX[BT * 3], vY[BT * 3];
-    __shared__ uint8_t o1[SLOT_OFF_LD], r1[3 * BT];   // see tile_slot_sums
-    __shared__ SlotPlaces w2[SMAX];
-    __shared__ float2 st[4][ST_WAVE];   // each wave's staged rows
-    __shared__ float2 P[P_LEN];         // test-corner rank x trial slot partial sums
+    __shared__ TriGeoF geo[2 * BT];      // the test block's triangles, then the trial block's
+    __shared__ TileSlots S;
+    __shared__ float2 st[4][ST_WAVE];    // each wave's staged rows
+    __shared__ float2 P[P_LEN];          // test-corner rank x trial slot partial sums
 
-    const int64_t tile = tile0 + blockIdx.x;
     int b1, b2;
-    tile_of(tile, A.nb, b1, b2);
-    const int s1 = A.blk_start[b1], n1 = A.blk_start[b1 + 1] - s1;
-    const int s2 = A.blk_start[b2], n2 = A.blk_start[b2 + 1] - s2;
-    const int ns1 = A.blk_nslot[b1], ns2 = A.blk_nslot[b2];
-    const int tid = threadIdx.x;
+    if (!tile_of(A, b1, b2)) return;
+    const TileBlocks B(A, b1, b2);
+    const int tid = threadIdx.x, t1 = tid >> 4, t2 = tid & 15;
     {
-        const double *src1 = reinterpret_cast<const double *>(A.geof + s1);
-        const double *src2 = reinterpret_cast<const double *>(A.geof + s2);
-        double *d1 = reinterpret_cast<double *>(gX), *d2 = reinterpret_cast<double *>(gY);
-        const int w = sizeof(TriGeoF) / sizeof(double);
-        for (int q = tid; q < n1 * w; q += 256) d1[q] = src1[q];
-        for (int q = tid; q < n2 * w; q += 256) d2[q] = src2[q];
-        if (tid < n1 * 3) vX[tid] = A.tri[3 * s1 + tid];
-        if (tid < n2 * 3) vY[tid] = A.tri[3 * s2 + tid];
-        if (tid < SLOT_OFF_LD) {
-            o1[tid] = A.slot_off[(size_t)b1 * SLOT_OFF_LD + tid];
-        } else if (tid >= 64 && tid < 64 + 3 * BT) {
-            r1[tid - 64] = A.slot_rank[(size_t)b1 * 3 * BT + tid - 64];
-        } else if (tid >= 128 && tid < 128 + SMAX) {
-            w2[tid - 128] = A.slot_place[(size_t)b2 * SMAX + tid - 128];
-        }
+        constexpr int GW = sizeof(TriGeoF) / sizeof(double), GN = (GW + 7) / 8;
+        const int t = tid >> 3;   // (triangles past a block's last repeat its last)
+        const double *src = reinterpret_cast<const double *>(
+            A.geof + (t < BT ? B.s1 + min(t, B.n1 - 1) : B.s2 + min(t - BT, B.n2 - 1)));
+        double g[GN];
+#pragma unroll
+        for (int i = 0; i < GN; ++i) g[i] = src[min((tid & 7) + 8 * i, GW - 1)];
+        const uint32_t w = tile_slots_word(A, B, tid);
+#pragma unroll
+        for (int i = 0; i < GN; ++i)
+            if ((tid & 7) + 8 * i < GW) reinterpret_cast<double *>(geo + t)[(tid & 7) + 8 * i] = g[i];
+        if (tid < TW_END) reinterpret_cast<uint32_t *>(&S)[tid] = w;
     }
     __syncthreads();
-
-    const int t1 = tid >> 4, t2 = tid & 15;
-    bool active = t1 < n1 && t2 < n2;
-    if (active) {
-        for (int a = 0; a < 3; ++a)
-            for (int b = 0; b < 3; ++b) active = active && (vX[3 * t1 + a] != vY[3 * t2 + b]);
-    }
+    const float kf = (float)A.k;
+    const float k2r = CK ? (float)(A.k * A.k - A.kim * A.kim) : kf * kf, k2i = (float)(2.0 * A.k * A.kim);
+    const TriGeoF &X = geo[t1], &Y = geo[BT + t2];
+    const bool active = tile_pair_active(S, B, t1, t2);
     float vr[9], vi[9], kr[9], ki[9], tr[9], ti[9], sr = 0.f, si = 0.f;
 #pragma unroll
     for (int e = 0; e < 9; ++e) { vr[e] = vi[e] = kr[e] = ki[e] = tr[e] = ti[e] = 0.f; }
-    const float kf = (float)A.k;
     // |k (r - r0)| <= 1 at every point pair of every pair of the wave: short polynomials
-    const bool tame = !__any(active && kf * (gX[t1].rho + gY[t2].rho) > 1.f);
+    const bool tame = !__any(active && kf * (X.rho + Y.rho) > 1.f);
     if (active) {
-        if (tame) pair_quadrature_f32<CK, true>(gX[t1], gY[t2], A.k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
-        else pair_quadrature_f32<CK, false>(gX[t1], gY[t2], A.k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
+        if (tame) pair_quadrature_f32<CK, true>(X, Y, A.k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
+        else pair_quadrature_f32<CK, false>(X, Y, A.k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
     }
-    const TriGeoF &X = gX[t1];
-    const TriGeoF &Y = gY[t2];
     const float nn = X.n[0] * Y.n[0] + X.n[1] * Y.n[1] + X.n[2] * Y.n[2];
-    const float k2r = CK ? (float)(A.k * A.k - A.kim * A.kim) : kf * kf, k2i = (float)(2.0 * A.k * A.kim);
-    tile_slot_sums(tid, n1, n2, ns1, ns2, o1, r1, w2, &st[0][0], P, A.scratch + (tile - A.tile_base) * (4 * SMAX * SMAX),
+    tile_slot_sums(tid, B.n1, B.n2, B.ns1, B.ns2, S.o1, S.r1, S.w2, &st[0][0], P,
+                   A.scratch + B.at * (4 * SMAX * SMAX),
                    [&](int op, int a, int b) {
                        const int e = 3 * a + b;
                        if (op == 0) return make_float2(vr[e], vi[e]);
@@ -1129,11 +1163,12 @@ bem_status launch_regular(const bem_mesh *m, double k, double kim, bool fp32, vo
     }
     for (int s = 0; s < ns; ++s) {
         const int b0 = h.strip_b[s], b1 = h.strip_b[s + 1], hb = s % 2;
-        const int64_t t0 = b0 * nb - (int64_t)b0 * (b0 - 1) / 2, n = strip_tiles(h, s);
+        const int64_t t0 = b0 * nb - (int64_t)b0 * (b0 - 1) / 2;
         char *buf = static_cast<char *>(scratch) + hb * half;
         if (s >= 2) BEM_HIP(hipStreamWaitEvent(st, ev[3 + hb], 0));
         {
             KTimer kt(ctx, K_REGULAR);
+            const dim3 grid = tile_grid((int)nb, b0, b1 - b0);
             if (!fp32) {
                 TileArgs A;
                 A.geo = m->d.geo.as<TriGeo>();
@@ -1147,11 +1182,12 @@ bem_status launch_regular(const bem_mesh *m, double k, double kim, bool fp32, vo
                 A.k = k;
                 A.kim = kim;
                 A.scratch = reinterpret_cast<double2 *>(buf);
-                A.tile_base = t0;
+                A.b0 = b0;
+                A.nrow = b1 - b0;
                 if (kim != 0.0)
-                    launch_k(kt, regular_tiles_kernel<true>, dim3((unsigned)n), dim3(256), 0, st, A, t0);
+                    launch_k(kt, regular_tiles_kernel<true>, grid, dim3(256), 0, st, A);
                 else
-                    launch_k(kt, regular_tiles_kernel<false>, dim3((unsigned)n), dim3(256), 0, st, A, t0);
+                    launch_k(kt, regular_tiles_kernel<false>, grid, dim3(256), 0, st, A);
             } else {
                 TileArgsF A;
                 A.geof = m->d.geof.as<TriGeoF>();
@@ -1165,11 +1201,12 @@ bem_status launch_regular(const bem_mesh *m, double k, double kim, bool fp32, vo
                 A.k = k;
                 A.kim = kim;
                 A.scratch = reinterpret_cast<float2 *>(buf);
-                A.tile_base = t0;
+                A.b0 = b0;
+                A.nrow = b1 - b0;
                 if (kim != 0.0)
-                    launch_k(kt, regular_tiles_f32_kernel<true>, dim3((unsigned)n), dim3(256), 0, st, A, t0);
+                    launch_k(kt, regular_tiles_f32_kernel<true>, grid, dim3(256), 0, st, A);
                 else
-                    launch_k(kt, regular_tiles_f32_kernel<false>, dim3((unsigned)n), dim3(256), 0, st, A, t0);
+                    launch_k(kt, regular_tiles_f32_kernel<false>, grid, dim3(256), 0, st, A);
             }
         }
         BEM_HIP(hipGetLastError());

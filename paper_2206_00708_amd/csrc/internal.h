@@ -37,16 +37,20 @@ constexpr int NG_MAX = 16;
 // product).  Padding columns hold zeros.
 __host__ __device__ inline int64_t op_ld(int64_t nv) { return (nv + 31) & ~int64_t(31); }
 
-// Per-triangle geometry table, built on the device (44 doubles, 352 B).
+// Per-triangle geometry table, built on the device (46 doubles, 368 B).  The
+// members down to curl, TRI_TILE doubles, are those that the tile kernels keep
+// in LDS.
 struct alignas(16) TriGeo {
-    double p[3][3];     // vertices in the triangle's own corner order
     double qp[6][3];    // points of the 6-point rule
     double n[3];        // unit normal (right-hand rule, outward)
+    double off;         // n . (a vertex): the triangle's plane is n . x = off
     double area;
-    double curl[3][3];  // surface curl of the P1 function of corner a
     double c[3];        // centroid
     double rho;         // largest distance from the centroid to a point of the 6-point rule
+    double curl[3][3];  // surface curl of the P1 function of corner a
+    double p[3][3];     // vertices in the triangle's own corner order
 };
+constexpr int TRI_TILE = 36;
 
 // Single-precision geometry for the mixed-precision regular kernel: the
 // centroid stays FP64 and the quadrature points are stored relative to it,
