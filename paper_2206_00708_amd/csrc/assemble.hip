@@ -197,17 +197,20 @@ __device__ inline bool tile_pair_active(const TileSlots &S, const TileBlocks &B,
 // A wave holds the pairs of four test triangles, so the trial side needs no
 // other wave: it goes through the wave's own four staged rows (one per test
 // triangle), one (operator, test corner) at a time, ordered by the LDS queue
-// alone.  The P rows of V, K and T are kept together, so the workgroup meets
-// once before the test side, whose items load the three operators' rows
-// independently; D follows in a second pass over the same rows (a fourth
-// operator's P rows would leave room for one workgroup per compute unit).
+// alone.  The P rows of all operators are kept together, so the workgroup meets
+// once before the test side, whose items load the operators' rows independently.
+// Rows of SMAX entries for four operators would leave room for one workgroup per
+// compute unit: they are S4 entries where the trial block has that few slots
+// (16 triangles of a compact patch have 13 to 17), else D follows V, K and T in a
+// second pass over the same rows.
 // The kernel is bound by VALU issue, so the places of a run are turned into LDS
 // addresses once per tile and serve every operator; places past a run's end
 // point at an entry that holds zero, and are added like the others.
 constexpr int SROW = 3 * BT + 1;        // staged row: one entry per trial corner, then the zero entry
 constexpr int ST_WAVE = 4 * SROW;       // staged rows of one wave
-constexpr int P_OP = 3 * BT * SMAX + 1; // P rows of one operator, then the zero entry
-constexpr int P_LEN = 3 * P_OP;
+constexpr int S4 = 18;                  // trial slots up to which P holds four operators
+constexpr int p_op(int row) { return 3 * BT * row + 1; }   // P rows of one operator, then the zero entry
+constexpr int P_LEN = std::max(3 * p_op(SMAX), 4 * p_op(S4));
 constexpr int SLOT_IT1 = (SMAX + 15) / 16;   // trial-side items per lane (16 slots x 4 rows at a time)
 
 // Orders the wave's LDS accesses before and after it for the compiler; the
@@ -278,7 +281,9 @@ __device__ inline void tile_slot_sums(int tid, int n1, int n2, int ns1, int ns2,
     const int t1 = tid >> 4, t2 = tid & 15;
     const bool staged = t1 < n1 && t2 < n2;
     if (lane < 4) st[wave * ST_WAVE + lane * SROW + 3 * BT] = C2{0, 0};
-    if (tid < 3) P[tid * P_OP + P_OP - 1] = C2{0, 0};
+    const bool four = ns2 <= S4;
+    const int prow = four ? S4 : SMAX, pop = p_op(prow);
+    if (tid < (four ? 4 : 3)) P[tid * pop + pop - 1] = C2{0, 0};
     // A row is staged corner by corner in the order of the trial triangles (neighbouring lanes write
     // neighbouring places).  Trial-side items of this lane: row (test triangle) lane / 16, slots
     // lane % 16 and so on by 16 (neighbouring lanes write neighbouring sums)
@@ -296,25 +301,34 @@ __device__ inline void tile_slot_sums(int tid, int n1, int n2, int ns1, int ns2,
         for (int v = 0; v < LMAX; ++v) run1[j].at[v] = row_at + EB * (int)(w.at[v >> 2] >> (8 * (v & 3)) & 255u);
     }
 #pragma unroll
-    for (int a = 0; a < 3; ++a) pr[a] = (ti < n1 ? r1[3 * ti + a] : 0) * SMAX + (lane & 15);
+    for (int a = 0; a < 3; ++a) pr[a] = (ti < n1 ? r1[3 * ti + a] : 0) * prow + (lane & 15);
+    // test-side items (q1, q2) of this thread: tid, tid + 256, ..; the places of the first before the barrier
+    const float inv = 1.0f / (float)ns2;
+    RunPlaces run2;
+    int item;
+    auto place = [&](int it) {
+        const int q1 = (int)(((float)it + 0.5f) * inv), q2 = it - q1 * ns2;
+        const int s0 = o1[q1];
+        run2.set_length(o1[q1 + 1] - s0);
+#pragma unroll
+        for (int v = 0; v < LMAX; ++v) run2.at[v] = EB * (v < run2.m ? (s0 + v) * prow + q2 : pop - 1);
+        item = 4 * (q1 * SMAX + q2);
+    };
     auto test_side = [&](int op0, int nop) {   // operators op0 .. op0 + nop - 1 from the P rows 0 .. nop - 1
-        const float inv = 1.0f / (float)ns2;
 #pragma unroll 1
-        for (int it = tid; it < ns1 * ns2; it += 256) {   // (q1, q2) of the ns1 x ns2 sums
-            const int q1 = (int)(((float)it + 0.5f) * inv), q2 = it - q1 * ns2;
-            const int s0 = o1[q1];
-            RunPlaces run2;
-            run2.set_length(o1[q1 + 1] - s0);
+        for (int it = tid;;) {
+            if (it < ns1 * ns2) {
 #pragma unroll
-            for (int v = 0; v < LMAX; ++v) run2.at[v] = EB * (v < run2.m ? (s0 + v) * SMAX + q2 : P_OP - 1);
-            C2 *o = out + 4 * (q1 * SMAX + q2) + op0;
-#pragma unroll
-            for (int q = 0; q < 3; ++q)
-                if (q < nop) {
-                    RunValues<C2> r;
-                    r.load(P + q * P_OP, run2);
-                    o[q] = r.sum(run2);
-                }
+                for (int q = 0; q < 4; ++q)
+                    if (q < nop) {
+                        RunValues<C2> r;
+                        r.load(P + q * pop, run2);
+                        out[item + op0 + q] = r.sum(run2);
+                    }
+            }
+            it += 256;
+            if (it >= ns1 * ns2) break;
+            place(it);
         }
     };
     auto stage = [&](int op, int a) {
@@ -325,7 +339,8 @@ __device__ inline void tile_slot_sums(int tid, int n1, int n2, int ns1, int ns2,
     stage(0, 0);
 #pragma unroll
     for (int op = 0; op < 4; ++op) {
-        if (op == 3) {
+        if (op == 3 && !four) {
+            place(tid < ns1 * ns2 ? tid : 0);
             __syncthreads();
             test_side(0, 3);
             __syncthreads();
@@ -342,11 +357,13 @@ __device__ inline void tile_slot_sums(int tid, int n1, int n2, int ns1, int ns2,
             else if (op < 3) stage(op + 1, 0);
 #pragma unroll
             for (int j = 0; j < SLOT_IT1; ++j)
-                if (16 * j < ns2 && run1[j].m > 0) P[(op % 3) * P_OP + pr[a] + 16 * j] = r[j].sum(run1[j]);
+                if (16 * j < ns2 && run1[j].m > 0) P[(op == 3 && !four ? 0 : op) * pop + pr[a] + 16 * j] = r[j].sum(run1[j]);
         }
     }
+    place(tid < ns1 * ns2 ? tid : 0);
     __syncthreads();
-    test_side(3, 1);
+    if (four) test_side(0, 4);
+    else test_side(3, 1);
 }
 
 // The 6-point rule applied to six values g_0 .. g_5 with the P1 functions:
