@@ -158,3 +158,29 @@ def test_sparse_mass_several_vectors_a_workgroup(ne, ni, R):
     # one vector alone: the FP32 sums of another tile width, times at most 2 by M^-1
     one = p.mtf_matvec_batch(torch.from_numpy(X[:1]), strong=True).cpu().numpy()
     assert _rel(Y[0], one[0]) < 4e-6
+
+
+# rows within and beyond half of the LDS and the whole (complex128 rows of 16 n bytes, complex64 of 8 n), and
+# an odd number of complex64 entries
+@pytest.mark.parametrize("prec,n", [(B.C128, 2048), (B.C128, 2049), (B.C128, 5200), (B.C128, 5601), (B.C128, 10100),
+                                    (B.C64_MIXED, 41), (B.C64_MIXED, 2049), (B.C64_MIXED, 10101),
+                                    (B.C64_MIXED, 11201)])
+def test_operator_in_caller_numbering(prec, n):
+    """The same mesh in another numbering: the same entries, but for the
+    rounding of other blocks' orders of summation."""
+    ctx = B.Context(0)
+    xyz, tri = synth.fibonacci_sphere(n)
+    perm = np.random.default_rng(n).permutation(n)
+    inv = np.argsort(perm)
+    got = []
+    for x, t in ((xyz, tri), (xyz[perm], inv[tri].astype(np.int32))):
+        m = B.Mesh(ctx, x, t)
+        small = B.Mesh(ctx, *synth.icosphere(0))
+        p = B.Problem(ctx, m, small, 1.0, 1.5, 1.0, 1.5, precision=prec)
+        p.assemble_operators()
+        got.append(p.operator(0, "K"))
+        del p
+    i = torch.from_numpy(perm).cuda()
+    want = got[0][i[:, None], i[None, :]]
+    tol = 1e-12 if prec == B.C128 else 2e-5
+    assert (got[1] - want).abs().max() < tol * want.abs().max()
