@@ -925,14 +925,17 @@ __global__ __launch_bounds__(256) void mass_combine_kernel(int ne, int ni, const
 
 // z = M^-1 y with both vectors of a mesh staged whole in LDS: a workgroup of 16
 // waves owns `rows` rows (the two meshes' rows spread over one workgroup per
-// compute unit), a wave takes a quarter of a row at a time (quarters interleaved
-// by steps of 64 lanes), and the four quarters are added in order.  Bound by
-// the stream of M^-1; against the split-column form above (three column chunks
-// per row at 2,562 vertices, whose partial sums a second kernel adds) it
-// stages each vector once per compute unit and needs no second launch:
-// 2,562 + 1,962 vertices FP64 20.8 + 4.8 -> 21.9 us.  For vectors that fit LDS
-// (mass_rows_fit); dynamic LDS: mass_rows_lds bytes.
-constexpr int MASS_WAVES = 16;
+// compute unit), a wave takes a quarter of the columns (quarters interleaved by
+// steps of 64 lanes) of up to MASS_G rows at a time, and the four quarters are
+// added in order.  Bound by the stream of M^-1: the entries of the next step, or
+// of the next rows, are loaded before this one's are used, the first ones
+// before the vectors are staged, and a vector entry read from LDS serves all
+// rows of the wave.  2,562 + 1,962 vertices FP64 (83 MB): 21.8 -> 19.5 us (4.3
+// TB/s) against one row at a time without loads ahead, 20.8 + 4.8 us in the
+// split-column form above and its second launch; rows dealt so that the
+// workgroups of both meshes read the same number of bytes gave nothing more.
+// For vectors that fit LDS (mass_rows_fit); dynamic LDS: mass_rows_lds bytes.
+constexpr int MASS_WAVES = 16, MASS_G = 5;
 inline int mass_rows_per_wg(int ne, int ni) { return std::max(1, (ne + ni + 253) / 254); }
 inline size_t mass_rows_lds(int ne, int ni)
 {
@@ -958,34 +961,55 @@ __global__ __launch_bounds__(64 * MASS_WAVES) void mass_rows_kernel(int ne, int 
     const int i0 = (ext ? blockIdx.x : blockIdx.x - be) * rows, nr = min(rows, nv - i0);
     const double2 *ya = ext ? y : y + 2 * ne;
     double4 *res = reinterpret_cast<double4 *>(sh + 2 * nvp);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // (uniform: row bases in scalar registers)
+    const int64_t ld = minv_ld(nv, f32);
+    const MT *M = (ext ? Me_inv : Mi_inv) + (int64_t)i0 * ld;
+    const int quarter = wave & 3, j0 = VW * (64 * quarter + lane);
+    // rows r0 .. r0 + ng - 1 of this wave: G at a time, the workgroup's four row groups side by side
+    const int G = (nr + 4 * ((nr + 4 * MASS_G - 1) / (4 * MASS_G)) - 1) / (4 * ((nr + 4 * MASS_G - 1) / (4 * MASS_G)));
+    typedef typename std::conditional<f32, v4f, v2d>::type V;
+    V m[MASS_G];
+    auto fetch = [&](int r0, int j) {   // the entries at column j of the rows from r0 on
+        if (j < nv)
+#pragma unroll
+            for (int g = 0; g < MASS_G; ++g)
+                if (g < G && r0 + g < nr)
+                    m[g] = __builtin_nontemporal_load(reinterpret_cast<const V *>(M + (int64_t)(r0 + g) * ld + j));
+    };
+    int r0 = (wave >> 2) * G;
+    fetch(r0, j0);
     for (int t = threadIdx.x; t < nvp; t += 64 * MASS_WAVES) {
         sh[t] = t < nv ? ya[t] : make_double2(0, 0);
         sh[nvp + t] = t < nv ? ya[nv + t] : make_double2(0, 0);
     }
     __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const MT *M = (ext ? Me_inv : Mi_inv) + (int64_t)i0 * minv_ld(nv, f32);
-    for (int u = wave; u < 4 * nr; u += MASS_WAVES) {
-        const MT *row = M + (int64_t)(u >> 2) * minv_ld(nv, f32);
-        double ar = 0, ai = 0, br = 0, bi = 0;
-#pragma unroll 4
-        for (int j = VW * (64 * (u & 3) + lane); j < nv; j += VW * 256) {   // padding columns of the row: zero
-            double m[VW];
-            if constexpr (f32) {
-                const v4f q = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(row + j));
-                m[0] = q.x; m[1] = q.y; m[2] = q.z; m[3] = q.w;
-            } else {
-                const v2d q = __builtin_nontemporal_load(reinterpret_cast<const v2d *>(row + j));
-                m[0] = q.x; m[1] = q.y;
-            }
+    for (; r0 < nr; r0 += 4 * G) {
+        double ar[MASS_G], ai[MASS_G], br[MASS_G], bi[MASS_G];
+#pragma unroll
+        for (int g = 0; g < MASS_G; ++g) ar[g] = ai[g] = br[g] = bi[g] = 0.0;
+        for (int j = j0; j < nv; j += VW * 256) {   // padding columns of the row: zero
+            V c[MASS_G];
+#pragma unroll
+            for (int g = 0; g < MASS_G; ++g) c[g] = m[g];
+            fetch(r0, j + VW * 256);
 #pragma unroll
             for (int e = 0; e < VW; ++e) {
                 const double2 a = sh[j + e], b = sh[nvp + j + e];
-                ar += m[e] * a.x; ai += m[e] * a.y; br += m[e] * b.x; bi += m[e] * b.y;
+#pragma unroll
+                for (int g = 0; g < MASS_G; ++g)
+                    if (g < G && r0 + g < nr) {
+                        const double x = c[g][e];
+                        ar[g] += x * a.x; ai[g] += x * a.y; br[g] += x * b.x; bi[g] += x * b.y;
+                    }
             }
         }
-        ar = wave_sum(ar); ai = wave_sum(ai); br = wave_sum(br); bi = wave_sum(bi);
-        if (lane == 0) res[u] = make_double4(ar, ai, br, bi);
+        fetch(r0 + 4 * G, j0);
+#pragma unroll
+        for (int g = 0; g < MASS_G; ++g)
+            if (g < G && r0 + g < nr) {
+                const double4 s = make_double4(wsum63(ar[g]), wsum63(ai[g]), wsum63(br[g]), wsum63(bi[g]));
+                if (lane == 63) res[4 * (r0 + g) + quarter] = s;
+            }
     }
     __syncthreads();
     double2 *za = ext ? z : z + 2 * ne;
