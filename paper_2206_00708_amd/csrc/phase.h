@@ -113,4 +113,38 @@ template <bool HALF> __device__ inline void small_sincos(double t, double &s, do
     c = fma(z, pc, 1.0);
 }
 
+// exp(u) of a small u by its even and odd parts, economised as above: |u| <= 1/2
+// (HALF, degrees 6 and 5 in u^2, errors below 1e-19 and 2e-17) or |u| <= 1
+// (degree 7, errors below 2e-18 and 1e-19).
+template <bool HALF> __device__ inline double small_exp(double u)
+{
+    const double z = u * u;
+    double po, pe;
+    if constexpr (HALF) {
+        po = fma_const(2.517282343175421e-08, z, 2.755697945753373e-06);
+        po = fma_const(po, z, 0.00019841270281873433);
+        po = fma_const(po, z, 0.00833333333307511);
+        po = fma_const(po, z, 0.1666666666666722);
+        pe = fma_const(2.097735036131617e-09, z, 2.755697317701901e-07);
+        pe = fma_const(pe, z, 2.480158789165942e-05);
+        pe = fma_const(pe, z, 0.001388888888837246);
+        pe = fma_const(pe, z, 0.041666666666668815);
+        pe = fma_const(pe, z, 0.49999999999999994);
+    } else {
+        po = fma_const(7.760411617749028e-13, z, 1.60571992722078e-10);
+        po = fma_const(po, z, 2.505212401145532e-08);
+        po = fma_const(po, z, 2.7557319150687833e-06);
+        po = fma_const(po, z, 0.00019841269841456506);
+        po = fma_const(po, z, 0.0083333333333331);
+        po = fma_const(po, z, 0.16666666666666669);
+        pe = fma_const(1.1663425624683784e-11, z, 2.087361778743318e-09);
+        pe = fma_const(pe, z, 2.7557345820982554e-07);
+        pe = fma_const(pe, z, 2.4801587176816665e-05);
+        pe = fma_const(pe, z, 0.0013888888889206652);
+        pe = fma_const(pe, z, 0.041666666666662695);
+        pe = fma_const(pe, z, 0.5000000000000002);
+    }
+    return 1.0 + fma(z, pe, fma(u * z, po, u));
+}
+
 }  // namespace bemtx

@@ -46,3 +46,22 @@ def test_operators_globe(orc, n, rings, k, prec, tol):
             got = p.operator(mesh, op).cpu().numpy()
             err = np.abs(got - ref[op]).max() / np.abs(ref[op]).max()
             assert err < tol, (mesh, op, err)
+
+
+# the three phase forms of a complex wavenumber, set by k and by the damping; the mixed form beside them
+@pytest.mark.parametrize("k,kim,prec,tol", [(0.5, 0.2, "C128", 1e-12), (0.2, 0.5, "C128", 1e-12),
+                                            (1.3, 0.4, "C128", 1e-12), (0.3, 1.3, "C128", 1e-12),
+                                            (0.3, 4.0, "C128", 1e-12), (6.0, 0.1, "C128", 1e-12),
+                                            (0.3, 1.3, "C64_MIXED", 2e-5)])
+def test_absorbing_operators_globe(orc, k, kim, prec, tol):
+    x, tri = _globe(10, 6, np.random.default_rng(3))
+    ctx = B.Context(0)
+    m = B.Mesh(ctx, x, tri)
+    p = B.Problem(ctx, m, m, k, k, 1.0, 1.0, getattr(B, prec))
+    p.set_k_int_imag(kim)
+    p.assemble_operators()
+    ref = orc.assemble(x, tri, k + 1j * kim)
+    for op in "VKTD":
+        got = p.operator(1, op).cpu().numpy()
+        err = np.abs(got - ref[op]).max() / np.abs(ref[op]).max()
+        assert err < tol, (op, err)
