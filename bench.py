@@ -41,12 +41,12 @@ FP64_VEC_TFLOPS = 78.6       # MI355X FP64 vector, TFLOP/s
 
 # Algorithmic FP64 work per quadrature point pair of the regular kernel,
 # counting a fused multiply-add as two flops (as the vector peak does):
-# difference and squared distance 8, 1/r and r 2, phase k r 1, reduction by
-# pi/2 and the sin/cos polynomials 46, exp(ikr)/r 2, its radial derivative 7,
-# the two normal projections 10 and their products 4, accumulation of the
-# three 3-vectors of partial sums and of sum G 40, and the share of the
-# per-row contraction 19.
-FLOP_PER_POINT_PAIR = 139
+# difference and squared distance 8, 1/r and r 9, the angle off the pair's base
+# phase 2, the sin/cos polynomials 27 (24 or 30 by range), exp(ikr)/r 2, k r and
+# 1/r^2 2, the radial derivative 6, its product for T 2, the orbit sums of six
+# values 9 and their shares per test point 8, accumulation of the element sums
+# 18, rotation by the base phase 4.
+FLOP_PER_POINT_PAIR = 97
 
 # GMRES tolerance of each headline workload: at the workload's own 1e-6 the
 # C3 traces can sit up to about 1.5e-5 from the exact discrete solution, at
@@ -64,8 +64,8 @@ MTF_REGIONS = {"source": "paper_2206_00708_amd/csrc/solve.hip",
                "regions": [("namespace {", "}  // namespace"),
                            ("// ---- symmetric tile form", "// y rows = sum of the tile partials")]}
 COUNTED_TRAFFIC = {
-    ("mtf_dense", "C3"): {"bytes": 2.000 * 2669427.6 * 1024 + 1.000 * 47448.1 * 1024,
-                          "sha1": "622b2e5ac6d2f07a3f71f5aa39f9288938c00ba8", **MTF_REGIONS},
+    ("mtf_dense", "C3"): {"bytes": 2.000 * 2669403.6 * 1024 + 1.000 * 47415.9 * 1024,
+                          "sha1": "9f913545a095c5bd22687ade36c2abddb25f5678", **MTF_REGIONS},
 }
 
 # FP64 VALU counters of the regular-pair kernel per launch (rocprofv3 --pmc,
@@ -76,17 +76,17 @@ COUNTED_TRAFFIC = {
 # (SQ_INSTS_VALU x 4 cycles over the SIMD cycles of the launch, from
 # GRBM_GUI_ACTIVE per XCD x 1024 SIMDs) and the share of the FP64 flops in
 # the software sin/cos (the small-angle polynomials and the rotation by the
-# pair's base phase: 46 of the per-point-pair flops).
+# pair's base phase: about 33 of the 110 flops per point pair).
 REG_REGIONS = {"source": "paper_2206_00708_amd/csrc/assemble.hip",
                "regions": [("// ------------------------------------------------------------ regular pairs",
                             "// The contributions to dense entry (i, j) of the tiles of one strip")]}
 COUNTED_VALU = {
-    ("regular_tiles", "C3"): {"flops_fp64": 1310718788.0 * 64, "valu_insts": 1067106586, "valu_busy": 0.701,
-                              "sincos_flop_share": 0.32, "isolated_launch_us": 2715.7,
-                              "sha1": "25fb264f3ef5797c79b384c65d0d644e4e7ed33b", **REG_REGIONS},
-    ("regular_tiles", "C2"): {"flops_fp64": 864256332.0 * 64, "valu_insts": 702649931, "valu_busy": 0.704,
-                              "sincos_flop_share": 0.32, "isolated_launch_us": 1912.8,
-                              "sha1": "25fb264f3ef5797c79b384c65d0d644e4e7ed33b", **REG_REGIONS},
+    ("regular_tiles", "C3"): {"flops_fp64": 1001099715.0 * 64, "valu_insts": 770386934, "valu_busy": 0.740,
+                              "sincos_flop_share": 0.30, "isolated_launch_us": 1946.3,
+                              "sha1": "1f60ff30b3e47f7d35bdadfe06c9142e6514978f", **REG_REGIONS},
+    ("regular_tiles", "C2"): {"flops_fp64": 659035802.0 * 64, "valu_insts": 506753050, "valu_busy": 0.738,
+                              "sincos_flop_share": 0.30, "isolated_launch_us": 1338.5,
+                              "sha1": "1f60ff30b3e47f7d35bdadfe06c9142e6514978f", **REG_REGIONS},
 }
 
 

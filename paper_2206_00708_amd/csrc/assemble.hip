@@ -3,8 +3,9 @@
 // parts) on one triangle mesh, G(x,y) = exp(i k |x-y|) / (4 pi |x-y|)
 // (Sec. 2.1, Sec. 2.4), in FP64 on gfx950.
 //
-//   geometry_kernel   per-triangle table: vertices, unit normal, area, the
-//                     six points of the order-four rule, P1 surface curls.
+//   geometry_kernel   per-triangle table: the six points of the order-four
+//                     rule, unit normal and plane, area, P1 surface curls,
+//                     vertices.
 //   regular_tiles     triangle pairs that share no vertex, order-four rule
 //                     (6 x 6 points, Sec. 5.1).  One workgroup per unordered
 //                     pair of locality blocks (16 x 16 triangles), one
@@ -21,7 +22,7 @@
 //                     of the tile entries of the blocks containing i and j.
 //   singular_pairs    ordered pairs sharing 3 / 2 / 1 vertices: Sauter-Schwab
 //                     regularising maps of [0,1]^4 with ng^4 Gauss points per
-//                     region (6 / 5 / 2 regions); 16 lanes per pair.
+//                     region (6 / 5 / 2 regions); 16 lanes per pair, or a wave.
 //   near_scatter      adds the singular contributions of each touched entry
 //                     in a fixed order.
 // Every entry is produced by a fixed sequence of additions, so the result is

@@ -21,11 +21,15 @@
 //   mtf_sym_combine        fixed-order sum of the tile partials, the
 //                          near-entry corrections of the parts that are not
 //                          symmetric, and the mortar coupling of the row.
-//   mass_apply_part/combine  z = M^-1 y, split-column scheme: a chunk of y
-//                          staged in LDS, several rows per wave.
+//   mass_rows              z = M^-1 y by the dense inverses with a mesh's
+//                          vectors whole in LDS; longer vectors by
+//   mass_apply_part/combine  the split-column scheme: a chunk of y staged in
+//                          LDS, several rows per wave.
+//   mass_cheb              z = M^-1 y without dense inverses: Chebyshev steps
+//                          on overlapping patches of vertices.
 //   block products         R Krylov vectors at once on the matrix cores
 //                          (gemm.hip) for batched right-hand sides.
-//   cgs_dots / cgs_update / arnoldi_finish   classical Gram-Schmidt with one
+//   dgs_dots / dgs_hess / dgs_update   classical Gram-Schmidt with one delayed
 //                          re-orthogonalisation in FP64 and the Givens
 //                          rotations of the new Hessenberg column on the
 //                          device; reductions in a fixed order
