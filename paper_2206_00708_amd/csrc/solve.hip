@@ -530,6 +530,10 @@ inline bool sym_small(int ne, int ni)
     const int64_t te = sym_ntile(ne, 128), ti = sym_ntile(ni, 128);
     return te * (te + 1) / 2 + ti * (ti + 1) / 2 < 256;
 }
+// 64-column tile pairs up to which a tile takes 16 waves of four rows: no more than one workgroup per compute
+// unit, so that a wave's one batch of loads and its reductions are the whole latency (162 + 162 vertices: 16.7 ->
+// 11.5 us, 642 + 492 complex64 in FP64 22.7 -> 13.2 us, against four waves of sixteen rows); with more tiles the workgroups of four waves overlap each other's batches.
+constexpr int64_t SYM_WIDE_PAIRS = 256;
 
 // task t -> tile pair (a, b), a <= b, in row-major order of the upper triangle
 __device__ inline void sym_pair(int64_t t, int nt, int &a, int &b)
@@ -602,17 +606,17 @@ __device__ inline void st_part(double4 *p, double a, double b, double c, double 
     __builtin_nontemporal_store(v4d_nt{a, b, c, d}, reinterpret_cast<v4d_nt *>(p));
 }
 
-template <class E, class R, int TS>
-__global__ __launch_bounds__(256) void mtf_sym_tile_kernel(MtfArgs A, const double2 *__restrict__ x,
+template <class E, class R, int TS, int NW = 4>
+__global__ __launch_bounds__(64 * NW) void mtf_sym_tile_kernel(MtfArgs A, const double2 *__restrict__ x,
                                                            double4 *__restrict__ part,
                                                            const KrylovState *__restrict__ st)
 {
     using C = typename Cx<R>::T;
-    constexpr int CPL = TS / 64, RPW = TS / 4;   // columns per lane, rows per wave
+    constexpr int CPL = TS / 64, RPW = TS / NW, NTH = 64 * NW;   // columns per lane, rows per wave
     if (st && st->done) return;
     __shared__ C sva[TS], swa[TS], svb[TS], swb[TS];
     __shared__ C rowres[3][TS];
-    __shared__ C colres[4][3][TS];
+    __shared__ C colres[NW][3][TS];
     int64_t t = blockIdx.x;
     const int nte = sym_ntile(A.ne, TS), nti = sym_ntile(A.ni, TS);
     const int64_t te = (int64_t)nte * (nte + 1) / 2;
@@ -629,7 +633,7 @@ __global__ __launch_bounds__(256) void mtf_sym_tile_kernel(MtfArgs A, const doub
     const double2 *xv = ext ? x : x + 2 * A.ne, *xw = xv + nv;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const C zero{0, 0};
-    for (int q = tid; q < TS; q += 256) {
+    for (int q = tid; q < TS; q += NTH) {
         const int ia = a * TS + q, ib = b * TS + q;
         sva[q] = ia < nv ? C{(R)xv[ia].x, (R)xv[ia].y} : zero;
         swa[q] = ia < nv ? C{(R)xw[ia].x, (R)xw[ia].y} : zero;
@@ -706,10 +710,10 @@ __global__ __launch_bounds__(256) void mtf_sym_tile_kernel(MtfArgs A, const doub
         colres[wave][2][colof(u)] = C{c2a[u].x, c2a[u].y};
     }
     __syncthreads();
-    for (int r = tid; r < TS; r += 256) {
+    for (int r = tid; r < TS; r += NTH) {
         double c1x = 0, c1y = 0, c2x = 0, c2y = 0, c3x = 0, c3y = 0;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
+        for (int w = 0; w < NW; ++w) {
             c1x += (double)colres[w][0][r].x; c1y += (double)colres[w][0][r].y;
             c2x += (double)colres[w][1][r].x; c2y += (double)colres[w][1][r].y;
             c3x += (double)colres[w][2][r].x; c3y += (double)colres[w][2][r].y;
@@ -2086,7 +2090,14 @@ bem_status apply_A(const bem_problem *p, const MtfArgs &A, const double2 *x, dou
     const dim3 g((unsigned)((int64_t)nte * (nte + 1) / 2 + (int64_t)nti * (nti + 1) / 2));
     {
         KTimer kt(p->ctx, K_MTF_DENSE);
-        if (A.sym_ts == 64) {
+        if (A.sym_ts == 64 && g.x <= SYM_WIDE_PAIRS) {
+            if (p->prec == BEM_C128)
+                launch_k(kt, mtf_sym_tile_kernel<double2, double, 64, 16>, g, dim3(1024), 0, st, A, x, part, kst);
+            else if (acc64)
+                launch_k(kt, mtf_sym_tile_kernel<float2, double, 64, 16>, g, dim3(1024), 0, st, A, x, part, kst);
+            else
+                launch_k(kt, mtf_sym_tile_kernel<float2, float, 64, 16>, g, dim3(1024), 0, st, A, x, part, kst);
+        } else if (A.sym_ts == 64) {
             if (p->prec == BEM_C128)
                 launch_k(kt, mtf_sym_tile_kernel<double2, double, 64>, g, dim3(256), 0, st, A, x, part, kst);
             else if (acc64)

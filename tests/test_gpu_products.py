@@ -184,3 +184,26 @@ def test_operator_in_caller_numbering(prec, n):
     want = got[0][i[:, None], i[None, :]]
     tol = 1e-12 if prec == B.C128 else 2e-5
     assert (got[1] - want).abs().max() < tol * want.abs().max()
+
+
+# tiles of 16 waves (240 tile pairs) and of four (272), tiles of one vertex, one tile
+@pytest.mark.parametrize("ne,ni", [(959, 960), (961, 1000), (65, 129), (33, 64)])
+@pytest.mark.parametrize("prec,tol", [(B.C128, 1e-13), (B.C64_MIXED, 2e-6)])
+def test_matvec_against_its_operators(ne, ni, prec, tol):
+    """The weak product against the copied operators and the projection; mixed
+    at the bound of two FP32 summation orders."""
+    from scipy.sparse import csr_matrix
+    p = _problem(B.Context(0), ne, ni, prec)
+    rng = np.random.default_rng(7)
+    x = rng.standard_normal(p.n) + 1j * rng.standard_normal(p.n)
+    ve, we, vi, wi = np.split(x, [ne, 2 * ne, 2 * ne + ni])
+    op = {(m, o): p.operator(m, o).to(torch.complex128).cpu().numpy() for m in (0, 1) for o in "VKTD"}
+    rp, col, val = p.projection()
+    P = csr_matrix((val, col, rp), shape=(ni, ne))
+    r = 1.0 / 1.5
+    ref = np.concatenate([-op[0, "K"] @ ve + op[0, "V"] @ we + 0.5 * (P.T @ vi),
+                          op[0, "D"] @ ve + op[0, "T"] @ we + 0.5 * r * (P.T @ wi),
+                          -0.5 * (P @ ve) - op[1, "K"] @ vi + op[1, "V"] @ wi,
+                          -0.5 / r * (P @ we) + op[1, "D"] @ vi + op[1, "T"] @ wi])
+    y = p.mtf_matvec(torch.from_numpy(x), strong=False).cpu().numpy()
+    assert _rel(y, ref) < tol
