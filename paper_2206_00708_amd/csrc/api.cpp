@@ -538,12 +538,10 @@ bem_status bem_problem_footprint(const bem_problem *p, int32_t nrhs, int32_t max
     return BEM_OK;
 }
 
-bem_status bem_assemble_operators(bem_problem *p, int32_t parts)
+// The memory, then the launches of both meshes on the main and gather streams.
+static bem_status queue_assembly(bem_problem *p, int32_t parts)
 {
-    if (!p) return set_error(BEM_E_ARG, "null problem");
-    if (parts < 0 || parts > 3) return set_error(BEM_E_ARG, "parts must be 0..3");
     bem_ctx *ctx = p->ctx;
-    BEM_HIP(hipSetDevice(ctx->device));
     hipStream_t st = ctx->stream;
     // the projection set-up on the auxiliary stream may start once the work queued before this point is done
     if (!p->ev_pre_asm) BEM_HIP(hipEventCreateWithFlags(&p->ev_pre_asm, hipEventDisableTiming));
@@ -561,6 +559,8 @@ bem_status bem_assemble_operators(bem_problem *p, int32_t parts)
             bem_status s = dev_alloc(ctx, p->ops[m][op], nv * op_ld(nv) * eb);
             if (s) return s;
         }
+        bem_status s = dev_alloc(ctx, p->corr[m], std::max<size_t>(meshes[m]->h.near_i.size(), 1) * 3 * sizeof(double2));
+        if (s) return s;
     }
     if (ctx->scratch_bytes < scratch_bytes) {
         if (ctx->scratch) {
@@ -628,11 +628,26 @@ bem_status bem_assemble_operators(bem_problem *p, int32_t parts)
         BEM_HIP(hipStreamWaitEvent(main_stream, ev, 0));
         BEM_HIP(hipEventRecord(p->asm_ev[1][2], main_stream));
     }
+    return BEM_OK;
+}
+
+bem_status bem_assemble_operators(bem_problem *p, int32_t parts)
+{
+    if (!p) return set_error(BEM_E_ARG, "null problem");
+    if (parts < 0 || parts > 3) return set_error(BEM_E_ARG, "parts must be 0..3");
+    bem_ctx *ctx = p->ctx;
+    BEM_HIP(hipSetDevice(ctx->device));
+    const bem_status s = queue_assembly(p, parts);
+    if (s) {
+        // the main stream waits for the gather stream at the end of a whole assembly only: let what a failed one
+        // has queued there end before the operators and the scratch can be used again
+        if (ctx->gather) (void)hipStreamSynchronize(ctx->gather);
+        return s;
+    }
     p->asm_timing_pending = true;
     p->ops_ready = true;
     return BEM_OK;
 }
-
 
 bem_status bem_assemble_projection(bem_problem *p)
 {

@@ -820,8 +820,6 @@ bem_status launch_sym_corrections(bem_problem *p, int mesh, hipStream_t st)
 {
     const bem_mesh *m = mesh == 0 ? p->ext : p->inte;
     const int nv = (int)m->h.nv, nn = (int)m->h.near_i.size();
-    bem_status s = dev_alloc(p->ctx, p->corr[mesh], (size_t)std::max(nn, 1) * 3 * sizeof(double2), st);
-    if (s) return s;
     if (nn == 0) return BEM_OK;
     const dim3 g((nn + 255) / 256);
     if (p->prec == BEM_C128)
