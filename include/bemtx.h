@@ -188,7 +188,10 @@ void bem_problem_destroy(bem_problem *p);
  * Krylov steps (operators, projections, Krylov bases, Hessenberg and triangular factors,
  * assembly scratch; for BEM_C64_MIXED problems all nrhs runs advancing
  * together, up to 64, with the buffers of the matrix-core products); for
- * admission control.  May be called before assembly. */
+ * admission control.  May be called before assembly.  Two small meshes are
+ * assembled side by side, each in a scratch region of its own, where the
+ * context's budget and the device have room beyond this number for the
+ * smaller region (at most 128 MB). */
 bem_status bem_problem_footprint(const bem_problem *p, int32_t nrhs, int32_t maxit, size_t *bytes);
 
 /* Dense Galerkin matrices V, K, T, D on both meshes (Sec. 2.1, 2.4, 5.1),

@@ -487,26 +487,62 @@ bem_status bem_problem_mass_apply(const bem_problem *p, int32_t *sparse)
 }
 
 // Assembly scratch of a problem: one region that the meshes use in turn, or,
-// where two regions are small, one for each (the interior mesh's at off1 > 0):
-// the two meshes are then assembled side by side.  A small mesh's chain of
-// launches leaves most of the device idle (162 + 162 vertices: 375 us one
-// after the other and read back, 300 side by side); meshes of more than a few hundred
-// tiles per compute unit fill it by themselves.
+// where two regions are small, one for each (the interior mesh's after the
+// exterior's): the two meshes are then assembled side by side.  A small mesh's
+// chain of launches leaves most of the device idle (162 + 162 vertices: 375 us
+// one after the other and read back, 300 side by side); meshes of more than a few hundred
+// tiles per compute unit fill it by themselves.  A context that has no memory
+// for two regions uses one.
 constexpr size_t kAssemblyPairMax = size_t(256) << 20;
 
-static size_t assembly_scratch(const bem_problem *p, size_t &off1)
-{
-    const bem_mesh *ms[2] = {p->ext, p->inte};
-    const size_t eb = p->prec == BEM_C128 ? sizeof(double2) : sizeof(float2);
-    size_t need[2];
-    bool one = true;   // a single assembly strip each
-    for (int m = 0; m < 2; ++m) {
-        need[m] = std::max(tile_scratch_bytes(ms[m], eb), ms[m]->h.sing.size() * 36 * sizeof(double2));
-        need[m] = (std::max<size_t>(need[m], 16) + 255) & ~size_t(255);
-        one = one && ms[m]->h.strip_b.size() == 2;
+struct AssemblyScratch {
+    size_t one;    // bytes of the larger region
+    size_t off1;   // both: where the interior mesh's begins (0: no such form)
+    size_t both;
+    explicit AssemblyScratch(const bem_problem *p)
+    {
+        const bem_mesh *ms[2] = {p->ext, p->inte};
+        const size_t eb = p->prec == BEM_C128 ? sizeof(double2) : sizeof(float2);
+        size_t need[2];
+        bool strip = true;   // a single assembly strip each
+        for (int m = 0; m < 2; ++m) {
+            need[m] = std::max(tile_scratch_bytes(ms[m], eb), ms[m]->h.sing.size() * 36 * sizeof(double2));
+            need[m] = (std::max<size_t>(need[m], 16) + 255) & ~size_t(255);
+            strip = strip && ms[m]->h.strip_b.size() == 2;
+        }
+        one = std::max(need[0], need[1]);
+        both = need[0] + need[1];
+        off1 = strip && both <= kAssemblyPairMax ? need[0] : 0;
     }
-    off1 = one && need[0] + need[1] <= kAssemblyPairMax ? need[0] : 0;
-    return off1 ? need[0] + need[1] : std::max(need[0], need[1]);
+};
+
+// At least `bytes` of assembly scratch for the context.
+static bem_status grow_scratch(bem_ctx *ctx, size_t bytes)
+{
+    if (ctx->scratch_bytes >= bytes) return BEM_OK;
+    if (ctx->budget && ctx->in_use - ctx->scratch_bytes - ctx->cached_bytes + bytes > ctx->budget)
+        return set_error(BEM_E_OOM, "context HBM budget exceeded by the assembly scratch");
+    if (ctx->scratch) {
+        BEM_HIP(hipStreamSynchronize(ctx->stream));
+        (void)hipFree(ctx->scratch);
+        ctx->in_use -= ctx->scratch_bytes;
+        ctx->scratch = nullptr;
+        ctx->scratch_bytes = 0;
+    }
+    std::lock_guard<std::mutex> lk(ctx->mem_mu);
+    if (ctx->budget && ctx->in_use + bytes > ctx->budget) drop_cached(ctx, bytes);
+    if (ctx->budget && ctx->in_use + bytes > ctx->budget)
+        return set_error(BEM_E_OOM, "context HBM budget exceeded by the assembly scratch");
+    hipError_t e = hipMalloc(&ctx->scratch, bytes);
+    if (e == hipErrorOutOfMemory && !ctx->free_blocks.empty()) {
+        (void)hipGetLastError();
+        drop_cached(ctx, 0);
+        e = hipMalloc(&ctx->scratch, bytes);
+    }
+    if (e != hipSuccess) { ctx->scratch = nullptr; (void)hipGetLastError(); return hip_error(e, "hipMalloc(scratch)"); }
+    ctx->scratch_bytes = bytes;
+    ctx->in_use += bytes;
+    return BEM_OK;
 }
 
 bem_status bem_problem_footprint(const bem_problem *p, int32_t nrhs, int32_t maxit, size_t *bytes)
@@ -520,8 +556,7 @@ bem_status bem_problem_footprint(const bem_problem *p, int32_t nrhs, int32_t max
         b += 8 * (ne + ni) * (3 * sizeof(int32_t) + sizeof(double) + 14 * (sizeof(int32_t) + sizeof(double)));
     if (!sparse_mass || block_dense_mass(p, p->prec == BEM_C64_MIXED ? std::min(nrhs, 64) : 1))
         b += (ne * ne + ni * ni) * (p->prec == BEM_C128 ? sizeof(double) : sizeof(float));   // dense inverse masses
-    size_t off;
-    b += assembly_scratch(p, off);
+    b += AssemblyScratch(p).one;
     // runs that advance together: every right-hand side of a complex64 problem (up to 64 per block), else one
     const size_t R = p->prec == BEM_C64_MIXED ? (size_t)std::min(nrhs, 64) : 1;
     b += R * ((size_t)(maxit + 1) * n + 8 * n) * sizeof(double2);                 // Krylov bases + work vectors
@@ -551,8 +586,6 @@ static bem_status queue_assembly(bem_problem *p, int32_t parts)
     const double kims[2] = {0.0, p->k_int_im};
     const bool fp32 = p->prec == BEM_C64_MIXED;
     const size_t eb = fp32 ? sizeof(float2) : sizeof(double2);
-    size_t off1 = 0;
-    const size_t scratch_bytes = assembly_scratch(p, off1);
     for (int m = 0; m < 2; ++m) {
         const size_t nv = meshes[m]->h.nv;
         for (int op = 0; op < 4; ++op) {
@@ -562,28 +595,14 @@ static bem_status queue_assembly(bem_problem *p, int32_t parts)
         bem_status s = dev_alloc(ctx, p->corr[m], std::max<size_t>(meshes[m]->h.near_i.size(), 1) * 3 * sizeof(double2));
         if (s) return s;
     }
-    if (ctx->scratch_bytes < scratch_bytes) {
-        if (ctx->scratch) {
-            BEM_HIP(hipStreamSynchronize(st));
-            (void)hipFree(ctx->scratch);
-            ctx->in_use -= ctx->scratch_bytes;
-            ctx->scratch = nullptr;
-            ctx->scratch_bytes = 0;
-        }
-        std::lock_guard<std::mutex> lk(ctx->mem_mu);
-        if (ctx->budget && ctx->in_use + scratch_bytes > ctx->budget) drop_cached(ctx, scratch_bytes);
-        if (ctx->budget && ctx->in_use + scratch_bytes > ctx->budget)
-            return set_error(BEM_E_OOM, "context HBM budget exceeded by the assembly scratch");
-        hipError_t e = hipMalloc(&ctx->scratch, scratch_bytes);
-        if (e == hipErrorOutOfMemory && !ctx->free_blocks.empty()) {
-            (void)hipGetLastError();
-            drop_cached(ctx, 0);
-            e = hipMalloc(&ctx->scratch, scratch_bytes);
-        }
-        if (e != hipSuccess) { ctx->scratch = nullptr; return hip_error(e, "hipMalloc(scratch)"); }
-        ctx->scratch_bytes = scratch_bytes;
-        ctx->in_use += scratch_bytes;
+    const AssemblyScratch sz(p);
+    size_t off1 = sz.off1;   // the interior mesh's region when the meshes go side by side, else 0
+    bem_status sg = grow_scratch(ctx, off1 ? sz.both : sz.one);
+    if (sg == BEM_E_OOM && off1) {   // no memory for two regions: one, as for larger meshes
+        off1 = 0;
+        sg = grow_scratch(ctx, sz.one);
     }
+    if (sg) return sg;
     // events: [mesh][0] before regular, [1] before singular, [2] after; resolved lazily
     for (int m = 0; m < 2; ++m)
         for (int q = 0; q < 3; ++q)

@@ -60,3 +60,36 @@ def test_assembly_over_the_budget_leaves_the_context_usable(unlimited, short):
     cx.trim()
     assert cx.bytes_in_use() == 0
     cx.close()
+
+
+def test_assembly_fits_where_one_region_does(unlimited):
+    """The budget of the operators, the tables and the larger of the two
+    scratch regions is enough.  The regions hold 36,864 bytes per pair of the
+    meshes' blocks of 16 triangles: 20 blocks of 320, 16 of 256 triangles."""
+    want, used, _, _ = unlimited
+    assert len(PAIR[0][1]) == 320 and len(PAIR[1][1]) == 256
+    spare = 16 * 17 // 2 * 36864
+    cx = B.Context(0, hbm_budget_bytes=used - spare)
+    for _ in range(2):   # the second one with the blocks that the first has released
+        got, in_use = _assembled(cx)
+        assert in_use <= used - spare
+        assert all(np.array_equal(g, w) for g, w in zip(got, want))
+    cx.close()
+
+
+def test_footprint_counts_one_region():
+    """The footprint that admission works with: operators, dense inverse
+    masses, the larger scratch region, Krylov basis and work vectors,
+    Hessenberg and triangular factors, partial sums, bound of the couplings."""
+    cx = B.Context(0)
+    me, mi = B.Mesh(cx, *PAIR[0]), B.Mesh(cx, *PAIR[1])
+    p = B.Problem(cx, me, mi, 2.0, 3.0, 1.0, 1.5)
+    ne, ni, maxit = 162, 130, 50
+    n = 2 * (ne + ni)
+    want = (4 * (ne * 192 + ni * 160) * 16 + (ne * ne + ni * ni) * 8 + 20 * 21 // 2 * 36864
+            + ((maxit + 1) * n + 8 * n) * 16 + 2 * maxit * (maxit + 1) * 16
+            + (n + 1023) // 1024 * 2 * (maxit + 1) * 16 + 64 * (ne + ni) * 8)
+    assert p.footprint(1, maxit) == want
+    for h in (p, me, mi):
+        h.close()
+    cx.close()
