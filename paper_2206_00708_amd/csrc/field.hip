@@ -319,13 +319,15 @@ __global__ __launch_bounds__(256) void winding_combine_kernel(int np, int nchunk
     w[i] = 2.0 * s * kInv4Pi;
 }
 
-// triangle chunks for np points: about FLD_WG workgroups, at least FLD_TMIN
-// triangles per chunk
-void chunking(int64_t np, int nt, int &nchunk, int &tpc)
+// Triangle chunks for np points: about FLD_WG workgroups, at least FLD_TMIN
+// triangles per chunk.  lean: the fewer chunks of 256-point workgroups with
+// at least 128 triangles each, where the partial sums have to be small.
+void chunking(int64_t np, int nt, bool lean, int &nchunk, int &tpc)
 {
-    const int64_t pblocks = (np + FLD_PB - 1) / FLD_PB;
-    const int64_t maxc = std::max<int64_t>(1, (nt + FLD_TMIN - 1) / FLD_TMIN);
-    nchunk = (int)std::min<int64_t>(maxc, std::max<int64_t>(1, FLD_WG / std::max<int64_t>(1, pblocks)));
+    const int64_t pblocks = lean ? (np + 255) / 256 : (np + FLD_PB - 1) / FLD_PB;
+    const int64_t tmin = lean ? 128 : FLD_TMIN, wg = lean ? FLD_WG / (256 / FLD_PB) : FLD_WG;
+    const int64_t maxc = std::max<int64_t>(1, (nt + tmin - 1) / tmin);
+    nchunk = (int)std::min<int64_t>(maxc, std::max<int64_t>(1, wg / std::max<int64_t>(1, pblocks)));
     tpc = (nt + nchunk - 1) / nchunk;
     nchunk = (nt + tpc - 1) / tpc;
 }
@@ -333,7 +335,7 @@ void chunking(int64_t np, int nt, int &nchunk, int &tpc)
 // Right-hand sides per launch for the `left` that remain: the smallest built
 // width that holds them (unused ones have zero densities), at most what
 // keeps the densities and partial sums of a launch within 1 GiB (one at the
-// least, as before).
+// least).
 int field_width(int left, size_t bytes_per_rhs)
 {
     const size_t cap = std::max<size_t>(1, (size_t(1) << 30) / std::max<size_t>(1, bytes_per_rhs));
@@ -362,11 +364,59 @@ template <bool CK> void launch_partial(const KTimer &kt, int R, unsigned wg, hip
 
 bem_status launch_to_internal(const bem_problem *p, const double2 *x_caller, double2 *x_int, int nrhs, hipStream_t st);
 
+namespace {
+
+// The points and chunks of region `only` (-1: of both) with nothing in the other.
+void set_regions(FieldArgs &A, const bem_problem *p, const int np[2], int only, bool lean)
+{
+    for (int m = 0; m < 2; ++m) {
+        FieldRegion &g = A.reg[m];
+        g.np = only < 0 || only == m ? np[m] : 0;
+        g.nt = g.np > 0 ? (int)(m == 0 ? p->ext : p->inte)->h.nt : 0;   // no points: no densities
+        chunking(g.np, std::max(1, g.nt), lean, g.nchunk, g.tpc);
+        g.npb = (g.np + FLD_PB - 1) / FLD_PB;
+    }
+}
+size_t dens_bytes(const FieldRegion &g) { return (size_t)g.nt * 6 * sizeof(double4); }      // of one right-hand side
+size_t part_bytes(const FieldRegion &g) { return (size_t)g.nchunk * g.np * sizeof(double2); }
+
+// The launches of A's regions for its right-hand sides, the kernel's width R.
+bem_status launch_regions(bem_problem *p, FieldArgs &A, int R, const FieldSources &src, int64_t npts, double2 *field,
+                          DevMem &dens, DevMem &part, hipStream_t st)
+{
+    FieldRegion *g = A.reg;
+    bem_status s = dev_alloc(p->ctx, dens, R * (dens_bytes(g[0]) + dens_bytes(g[1])));
+    if (!s) s = dev_alloc(p->ctx, part, R * (part_bytes(g[0]) + part_bytes(g[1])));
+    if (s) return s;
+    g[0].dens = dens.as<double4>();
+    g[1].dens = dens.as<double4>() + R * dens_bytes(g[0]) / sizeof(double4);
+    g[0].part = part.as<double2>();
+    g[1].part = part.as<double2>() + R * part_bytes(g[0]) / sizeof(double2);
+    const int64_t nd = 6 * ((int64_t)g[0].nt + g[1].nt), np = (int64_t)g[0].np + g[1].np;
+    hipLaunchKernelGGL(field_density_kernel, dim3((unsigned)((nd + 255) / 256), R), dim3(256), 0, st, A, R);
+    BEM_HIP(hipGetLastError());
+    {
+        KTimer kt(p->ctx, K_FIELD);
+        const unsigned wg = (unsigned)(g[0].npb * g[0].nchunk + g[1].npb * g[1].nchunk);
+        if (p->k_int_im != 0.0) launch_partial<true>(kt, R, wg, st, A);
+        else launch_partial<false>(kt, R, wg, st, A);
+        BEM_HIP(hipGetLastError());
+    }
+    hipLaunchKernelGGL(field_combine_kernel, dim3((unsigned)((np + 255) / 256), A.nrhs), dim3(256), 0, st, A, R, src,
+                       p->incident, p->k_ext, npts, field);
+    BEM_HIP(hipGetLastError());
+    return BEM_OK;
+}
+
+}  // namespace
+
 // Fields of nrhs right-hand sides at the points of both regions: pts [np_0 +
 // np_1][3] and dst on the device, exterior points first; x: the unknowns in
 // caller numbering (device, [nrhs][n]); dirs (host); field [nrhs][npts].  Work
 // buffers: the unknowns of one launch's right-hand sides in internal
-// numbering, their densities and partial sums.
+// numbering, their densities and partial sums.  Where these do not fit the
+// memory, one right-hand side at a time; where that does not, one region at a
+// time in few chunks.
 bem_status launch_field(bem_problem *p, const int np[2], const double *pts, const int32_t *dst, const double2 *x,
                         const double *dirs, int nrhs, double2 *field, DevMem &xint, DevMem &dens, DevMem &part,
                         hipStream_t st)
@@ -375,8 +425,6 @@ bem_status launch_field(bem_problem *p, const int np[2], const double *pts, cons
     const int64_t ne = p->ext->h.nv, ni = p->inte->h.nv, n = 2 * ne + 2 * ni, npts = (int64_t)np[0] + np[1];
     FieldArgs A;
     A.n = n;
-    size_t dens_rhs[2], part_rhs[2];
-    int wg = 0;
     for (int m = 0; m < 2; ++m) {
         FieldRegion &g = A.reg[m];
         g.geo = ms[m]->d.geo.as<TriGeo>();
@@ -388,50 +436,37 @@ bem_status launch_field(bem_problem *p, const int np[2], const double *pts, cons
         g.sgn = m == 0 ? 1.0 : -1.0;
         g.phi = m == 0 ? 0 : 2 * ne;
         g.psi = m == 0 ? ne : 2 * ne + ni;
-        g.nt = np[m] > 0 ? (int)ms[m]->h.nt : 0;   // no points: no densities
-        g.np = np[m];
-        chunking(np[m], std::max(1, g.nt), g.nchunk, g.tpc);
-        g.npb = (np[m] + FLD_PB - 1) / FLD_PB;
-        dens_rhs[m] = (size_t)g.nt * 6 * sizeof(double4);
-        part_rhs[m] = (size_t)g.nchunk * np[m] * sizeof(double2);
-        wg += g.npb * g.nchunk;
     }
     int most = nrhs;
+    bool lean = false;
     for (int r0 = 0; r0 < nrhs;) {
-        const int R = field_width(std::min(most, nrhs - r0), std::max(dens_rhs[0] + dens_rhs[1], part_rhs[0] + part_rhs[1]));
+        set_regions(A, p, np, -1, false);
+        const int R = field_width(std::min(most, nrhs - r0), std::max(dens_bytes(A.reg[0]) + dens_bytes(A.reg[1]),
+                                                                      part_bytes(A.reg[0]) + part_bytes(A.reg[1])));
         A.nrhs = std::min(R, nrhs - r0);
-        bem_status s = dev_alloc(p->ctx, xint, (size_t)R * n * sizeof(double2));
-        if (!s) s = dev_alloc(p->ctx, dens, R * (dens_rhs[0] + dens_rhs[1]));
-        if (!s) s = dev_alloc(p->ctx, part, R * (part_rhs[0] + part_rhs[1]));
-        if (s == BEM_E_OOM && R > 1) {   // little memory left: one right-hand side at a time
-            xint.release();
-            dens.release();
-            part.release();
-            most = 1;
-            continue;
-        }
-        if (!s) s = launch_to_internal(p, x + (int64_t)r0 * n, xint.as<double2>(), A.nrhs, st);
-        if (s) return s;
-        A.x = xint.as<double2>();
-        A.reg[0].dens = dens.as<double4>();
-        A.reg[1].dens = dens.as<double4>() + (size_t)R * 6 * A.reg[0].nt;
-        A.reg[0].part = part.as<double2>();
-        A.reg[1].part = part.as<double2>() + R * part_rhs[0] / sizeof(double2);
-        const int64_t nd = 6 * ((int64_t)A.reg[0].nt + A.reg[1].nt);
-        hipLaunchKernelGGL(field_density_kernel, dim3((unsigned)((nd + 255) / 256), R), dim3(256), 0, st, A, R);
-        BEM_HIP(hipGetLastError());
-        {
-            KTimer kt(p->ctx, K_FIELD);
-            if (p->k_int_im != 0.0) launch_partial<true>(kt, R, (unsigned)wg, st, A);
-            else launch_partial<false>(kt, R, (unsigned)wg, st, A);
-            BEM_HIP(hipGetLastError());
-        }
         FieldSources src{};
         for (int r = 0; r < A.nrhs; ++r)
             for (int c = 0; c < 3; ++c) src.d[r][c] = dirs[3 * (r0 + r) + c];
-        hipLaunchKernelGGL(field_combine_kernel, dim3((unsigned)((npts + 255) / 256), A.nrhs), dim3(256), 0, st, A, R, src,
-                           p->incident, p->k_ext, npts, field + (int64_t)r0 * npts);
-        BEM_HIP(hipGetLastError());
+        bem_status s = dev_alloc(p->ctx, xint, (size_t)R * n * sizeof(double2));
+        if (!s) {
+            s = launch_to_internal(p, x + (int64_t)r0 * n, xint.as<double2>(), A.nrhs, st);
+            if (s) return s;
+            A.x = xint.as<double2>();
+            for (int only = lean ? 0 : -1; only < (lean ? 2 : 0) && !s; ++only) {
+                if (lean && np[only] == 0) continue;
+                if (lean) set_regions(A, p, np, only, true);
+                s = launch_regions(p, A, R, src, npts, field + (int64_t)r0 * npts, dens, part, st);
+            }
+        }
+        if (s == BEM_E_OOM && !lean) {   // little memory left
+            xint.release();
+            dens.release();
+            part.release();
+            lean = R == 1;
+            most = 1;
+            continue;
+        }
+        if (s) return s;
         r0 += A.nrhs;
     }
     return BEM_OK;
@@ -442,8 +477,12 @@ bem_status launch_winding(const bem_mesh *m, int np, const double *pts, double *
     if (np == 0) return BEM_OK;
     const int nt = (int)m->h.nt;
     int nchunk, tpc;
-    chunking(np, nt, nchunk, tpc);
+    chunking(np, nt, false, nchunk, tpc);
     bem_status s = dev_alloc(m->ctx, part, (size_t)nchunk * np * sizeof(double));
+    if (s == BEM_E_OOM) {   // little memory left
+        chunking(np, nt, true, nchunk, tpc);
+        s = dev_alloc(m->ctx, part, (size_t)nchunk * np * sizeof(double));
+    }
     if (s) return s;
     const int npb = (np + FLD_PB - 1) / FLD_PB;
     hipLaunchKernelGGL(winding_partial_kernel, dim3((unsigned)npb * nchunk), dim3(FLD_PB), 0, st, np, pts, nt, tpc, npb,

@@ -93,3 +93,42 @@ def test_footprint_counts_one_region():
     for h in (p, me, mi):
         h.close()
     cx.close()
+
+
+def test_field_and_winding_fit_where_one_region_does():
+    """A field of one right-hand side needs, beside its points, the unknowns,
+    368 bytes per triangle of one region and 16 bytes per point and chunk of
+    it (13 chunks of the 5,120 triangles for 40,000 points); a winding number
+    8 bytes per point and chunk (40 for 256 points).  In allocation sizes:
+    2, 1/2, 1/4, 2 and 10 MB, and 1/8 MB.  The sums run in another order than
+    without a limit (1e-12 of the largest value)."""
+    ext, inte, _ = synth.make_pair(7, 4, "ico", 0.02, (1.0, 0.9, 0.8), int_level=4)
+    rng = np.random.default_rng(4)
+    pts = torch.as_tensor(rng.uniform(1.5, 3.0, (80000, 3)), device="cuda")
+    region = torch.arange(80000, device="cuda", dtype=torch.int32) % 2
+    n = 2 * (len(ext[0]) + len(inte[0]))
+    x = torch.as_tensor(rng.standard_normal((2, n)) + 1j * rng.standard_normal((2, n)), device="cuda")
+    d = synth.plane_wave_directions(2, rng)
+
+    def base():
+        cx = B.Context(0)
+        me, mi = B.Mesh(cx, *ext), B.Mesh(cx, *inte)
+        b = cx.bytes_in_use()
+        for h in (me, mi, cx):
+            h.close()
+        return b
+
+    def run(budget, call):
+        cx = B.Context(0, hbm_budget_bytes=budget)
+        me, mi = B.Mesh(cx, *ext), B.Mesh(cx, *inte)
+        p = B.Problem(cx, me, mi, 3.0, 4.0)
+        out = call(p, me).cpu().numpy()
+        for h in (p, me, mi, cx):
+            h.close()
+        return out
+
+    tables = base()
+    for call, mb in ((lambda p, m: p.field(d, x, pts, region), 14.75), (lambda p, m: m.winding(pts[:256]), 0.125)):
+        want = run(0, call)
+        got = run(tables + int(mb * (1 << 20)), call)
+        assert np.max(np.abs(got - want)) < 1e-12 * max(1.0, np.max(np.abs(want)))
