@@ -407,7 +407,7 @@ static_assert(sizeof(TileGeo) == (TRI_TILE + 2) * sizeof(double) && offsetof(Tri
 // (y - x).n_y is the same for every y on the plane of Y and (x - y).n_x for
 // every x on the plane of X: one factor per test point and one per trial
 // point.  BASE: phase from the per-pair base (see the caller; 1 up to 1, 2 up
-// to 1/2 radian off it), whose factor exp(i k r0) is applied to the sums.  CK:
+// to kShortPhase radian off it), whose factor exp(i k r0) is applied to the sums.  CK:
 // complex wavenumber k + i kim; the damping exp(-kim r) has the same base.
 template <bool CK, int BASE>
 __device__ inline void pair_quadrature(const TileGeo &X, const TileGeo &Y, double k, double kim, double (&vr)[9],
@@ -576,12 +576,12 @@ __global__ __launch_bounds__(256, 2) void regular_tiles_kernel(TileArgs A)
     // the wave: with r0 the centroid distance, |k (r - r0)| <= 1 for every
     // point pair, so exp(i k r) = exp(i k r0) exp(i k (r - r0)) takes one
     // reduced sin/cos per pair and short polynomials per point pair (shorter
-    // ones up to 1/2).  The choice is the wave's, so that its lanes run one
+    // ones up to kShortPhase).  The choice is the wave's, so that its lanes run one
     // of the three forms.
     // Complex k: the damping's exponent is held to the same bounds (2,252 + 1,692 vertices with an absorbing
     // interior: 3.32 -> 3.18 ms against the library's exp and the full reduction at every point).
     const double spread = active ? (CK ? fmax(k, A.kim) : k) * (X.rho + Y.rho) : 0.0;
-    const int base = __any(spread > 1.0) ? 0 : (__any(spread > 0.5) ? 1 : 2);
+    const int base = __any(spread > 1.0) ? 0 : (__any(spread > kShortPhase) ? 1 : 2);
     if (active) {
         if (base == 2) pair_quadrature<CK, 2>(X, Y, k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
         else if (base == 1) pair_quadrature<CK, 1>(X, Y, k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
@@ -602,24 +602,6 @@ __global__ __launch_bounds__(256, 2) void regular_tiles_kernel(TileArgs A)
                        else
                            return make_double2(cc * sr - k2r * nn * vr[e], cc * si - k2r * nn * vi[e]);
                    });
-}
-
-// sin and cos of a small angle t, |t| <= 1, FP32: as small_sincos, economised
-// on z = t^2 in [0, 1] to degree 4 (errors below 1e-10 and 1e-9, far below
-// FP32 rounding).
-__device__ inline void small_sincos(float t, float &s, float &c)
-{
-    const float z = t * t;
-    float ps = 2.6937597575879865e-06f;
-    ps = fmaf(ps, z, -0.0001983586640864844f);
-    ps = fmaf(ps, z, 0.008333314069456277f);
-    ps = fmaf(ps, z, -0.16666666426123591f);
-    s = fmaf(t * z, ps, t);
-    float pc = 2.412120108186752e-05f;
-    pc = fmaf(pc, z, -0.0013882960343166483f);
-    pc = fmaf(pc, z, 0.041666455375340986f);
-    pc = fmaf(pc, z, -0.49999997362171766f);
-    c = fmaf(z, pc, 1.f);
 }
 
 // The point pairs of one regular triangle pair in FP32.  The phase k|x - y|
@@ -674,7 +656,7 @@ __device__ inline void pair_quadrature_f32(const TriGeoF &X, const TriGeoF &Y, d
                 const float num = q0 * (f00 + d0) + q1 * (f01 + d1) + q2 * (f02 + d2);
                 const float dr = num * __builtin_amdgcn_rcpf(r + r0f);
                 float sd, cd;
-                if constexpr (SMALL) small_sincos(kf * dr, sd, cd);
+                if constexpr (SMALL) small_sincos_f32(kf * dr, sd, cd);
                 else sincosf(kf * dr, &sd, &cd);
                 gr[o] = cd * rinv; gi[o] = sd * rinv;              // exp(ik(r - r0))/r
                 const float kr_ = kf * r, rinv2 = rinv * rinv;

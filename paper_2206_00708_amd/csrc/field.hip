@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256) void field_density_kernel(FieldArgs A, int R)
 // right-hand sides: sum over its quadrature points of G psi - dG/dn phi,
 // times 4 pi.  (y - x).n is the same for every y of the triangle.  BASE: the
 // phase from the triangle's centroid, exp(i k r) = exp(i k r0) exp(i k (r - r0))
-// with |k (r - r0)| <= k rho <= 1/2 (short polynomials instead of a reduction
+// with |k (r - r0)| <= k rho <= kShortPhase (short polynomials instead of a reduction
 // per point); the factor exp(i k r0) is applied to the triangle's sums for
 // few right-hand sides and to the values for many.
 template <bool CK, bool BASE, int R>
@@ -181,7 +181,7 @@ __device__ inline void field_chunk(const FieldRegion &g, int chunk, int i, bool 
     for (int r = 0; r < R; ++r) ar[r] = ai[r] = 0.0;
 #pragma unroll 1
     for (int t = t0; t < t1; ++t) {
-        if (g.k * geo[t].rho <= 0.5)
+        if (g.k * geo[t].rho <= kShortPhase)
             field_triangle<CK, true, R>(geo[t], dens + (int64_t)6 * R * t, x0, x1, x2, g.k, g.kim, ar, ai);
         else
             field_triangle<CK, false, R>(geo[t], dens + (int64_t)6 * R * t, x0, x1, x2, g.k, g.kim, ar, ai);

@@ -58,9 +58,10 @@ __host__ __device__ inline void phase_sincos(double x, double *s, double *c)
     *c = cv;
 }
 
-// 1 / sqrt(x) of a positive finite x: the hardware estimate (relative error e
-// below 2^-20) with one third-order step, 1 + e/2 + 3 e^2 / 8 (error below
-// 2^-60); without the library function's handling of 0 and infinity.
+// 1 / sqrt(x) of a positive finite x: the hardware estimate y and one
+// third-order step, 1 + e/2 + 3 e^2 / 8 with e = 1 - x y^2; of |e| < 2^-19 (y
+// within 2^-20) it leaves 5 e^3 / 16 < 2^-58; without the library function's
+// handling of 0 and infinity.
 __device__ inline double rsqrt_pos(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);
@@ -71,80 +72,105 @@ __device__ inline double rsqrt_pos(double x)
 // fma(a, b, c) with c in scalar registers (a constant): the compiler's own
 // choice copies c into vector registers first (v_fmac needs its addend
 // there), one instruction more per polynomial step.
-__device__ inline double fma_const(double a, double b, double c)
+template <class R> __host__ __device__ inline R fma_const(R a, R b, double c)
 {
+#ifdef __HIP_DEVICE_COMPILE__
     double r;
     asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
     return r;
+#else
+    return std::fma(a, b, R(c));
+#endif
 }
 
-// sin and cos of a small angle t: the Taylor series of sin(t)/t and cos t as
-// polynomials in z = t^2, economised by Chebyshev polynomials (Lanczos) on
-// the range of z.  HALF: |t| <= 1/2, degrees 5 and 6, errors below 2e-17 and
-// 1e-19; else |t| <= 1, degree 7, errors below 1e-19 and 2e-18.
-template <bool HALF> __device__ inline void small_sincos(double t, double &s, double &c)
+// sin and cos of a small angle t, |t| <= 1 or, SHORT, |t| <= kShortPhase: t + t z
+// ps(z) and 1 - z/2 + z^2 pc(z), z = t^2.  ps and pc are minimax polynomials
+// (Remez) of the error they leave in sin(t)/t and cos t, made one coefficient at a
+// time from the lowest: each is rounded to a double before the rest is fitted
+// again.  (A fitted linear term of cos t rounds to a double that is further off than
+// all the rest.)  The errors of these coefficients, in exact arithmetic: sin(t)/t
+// below 2e-19 and cos t 3e-18, SHORT 2e-18 and 1e-20.  R: double, or a wider type on
+// the host.
+constexpr double kShortPhase = 0.4;
+template <bool SHORT, class R> __host__ __device__ inline void small_sincos(R t, R &s, R &c)
 {
-    const double z = t * t;
-    double ps, pc;
-    if constexpr (HALF) {
-        ps = fma_const(-2.493193700544346e-08, z, 2.7556981496282986e-06);
-        ps = fma_const(ps, z, -0.00019841269403639427);
-        ps = fma_const(ps, z, 0.008333333333076967);
-        ps = fma_const(ps, z, -0.16666666666666116);
-        pc = fma_const(2.077661169102768e-09, z, -2.7556975230704026e-07);
-        pc = fma_const(pc, z, 2.4801586715453357e-05);
-        pc = fma_const(pc, z, -0.0013888888888376136);
-        pc = fma_const(pc, z, 0.04166666666666453);
+    using std::fma;
+    const R z = t * t;
+    R ps, pc;
+    if constexpr (SHORT) {
+        ps = fma_const(R(-2.4976067312917476e-08), z, 2.755718514904267e-06);
+        ps = fma_const(ps, z, -0.0001984126973393321);
+        ps = fma_const(ps, z, 0.008333333333295828);
+        ps = fma_const(ps, z, -0.16666666666666624);
+        pc = fma_const(R(2.0816733191749955e-09), z, -2.7557199177696807e-07);
+        pc = fma_const(pc, z, 2.4801587188281747e-05);
+        pc = fma_const(pc, z, -0.0013888888888839263);
+        pc = fma_const(pc, z, 0.04166666666666659);
     } else {
-        ps = fma_const(-7.535488064487613e-13, z, 1.6057233337039862e-10);
-        ps = fma_const(ps, z, -2.5052093083699724e-08);
-        ps = fma_const(ps, z, 2.7557319152309194e-06);
-        ps = fma_const(ps, z, -0.00019841269841087476);
-        ps = fma_const(ps, z, 0.008333333333333106);
+        ps = fma_const(R(-7.533046014929189e-13), z, 1.6057158896981951e-10);
+        ps = fma_const(ps, z, -2.5052092231784496e-08);
+        ps = fma_const(ps, z, 2.7557319147879288e-06);
+        ps = fma_const(ps, z, -0.00019841269841078057);
+        ps = fma_const(ps, z, 0.008333333333333104);
         ps = fma_const(ps, z, -0.16666666666666666);
-        pc = fma_const(-1.1281052794952459e-11, z, 2.0873682510844006e-09);
-        pc = fma_const(pc, z, -2.755729324310771e-07);
-        pc = fma_const(pc, z, 2.4801587179897263e-05);
-        pc = fma_const(pc, z, -0.0013888888888579293);
-        pc = fma_const(pc, z, 0.0416666666666628);
+        pc = fma_const(R(-1.1291217635465988e-11), z, 2.0874052633329625e-09);
+        pc = fma_const(pc, z, -2.755729858163397e-07);
+        pc = fma_const(pc, z, 2.480158721850318e-05);
+        pc = fma_const(pc, z, -0.0013888888888724743);
+        pc = fma_const(pc, z, 0.04166666666666546);
     }
+    pc = fma(pc, z, R(-0.5));
     s = fma(t * z, ps, t);
-    pc = fma(pc, z, -0.5);
-    c = fma(z, pc, 1.0);
+    c = fma(z, pc, R(1));
 }
 
-// exp(u) of a small u by its even and odd parts, economised as above: |u| <= 1/2
-// (HALF, degrees 6 and 5 in u^2, errors below 1e-19 and 2e-17) or |u| <= 1
-// (degree 7, errors below 2e-18 and 1e-19).
-template <bool HALF> __device__ inline double small_exp(double u)
+// exp(u) of a small u, |u| in the same ranges, by its odd and even parts u + u z
+// po(z) and 1 + z/2 + z^2 pe(z), z = u^2, made alike: errors below 5e-18, SHORT 1e-18.
+template <bool SHORT, class R> __host__ __device__ inline R small_exp(R u)
 {
-    const double z = u * u;
-    double po, pe;
-    if constexpr (HALF) {
-        po = fma_const(2.517282343175421e-08, z, 2.755697945753373e-06);
-        po = fma_const(po, z, 0.00019841270281873433);
-        po = fma_const(po, z, 0.00833333333307511);
-        po = fma_const(po, z, 0.1666666666666722);
-        pe = fma_const(2.097735036131617e-09, z, 2.755697317701901e-07);
-        pe = fma_const(pe, z, 2.480158789165942e-05);
-        pe = fma_const(pe, z, 0.001388888888837246);
-        pe = fma_const(pe, z, 0.041666666666668815);
-        pe = fma_const(pe, z, 0.49999999999999994);
+    using std::fma;
+    const R z = u * u;
+    R po, pe;
+    if constexpr (SHORT) {
+        po = fma_const(R(2.513215181439118e-08), z, 2.7557168716934236e-06);
+        po = fma_const(po, z, 0.00019841269972635465);
+        po = fma_const(po, z, 0.008333333333281427);
+        po = fma_const(po, z, 0.16666666666666738);
+        pe = fma_const(R(2.0936373936805533e-09), z, 2.755720112542241e-07);
+        pe = fma_const(pe, z, 2.4801587411782334e-05);
+        pe = fma_const(pe, z, 0.0013888888888841302);
+        pe = fma_const(pe, z, 0.04166666666666674);
     } else {
-        po = fma_const(7.760411617749028e-13, z, 1.60571992722078e-10);
-        po = fma_const(po, z, 2.505212401145532e-08);
-        po = fma_const(po, z, 2.7557319150687833e-06);
-        po = fma_const(po, z, 0.00019841269841456506);
-        po = fma_const(po, z, 0.0083333333333331);
+        po = fma_const(R(7.766168042632597e-13), z, 1.6056980220536488e-10);
+        po = fma_const(po, z, 2.5052127169502674e-08);
+        po = fma_const(po, z, 2.755731912852184e-06);
+        po = fma_const(po, z, 0.0001984126984153636);
+        po = fma_const(po, z, 0.008333333333332965);
         po = fma_const(po, z, 0.16666666666666669);
-        pe = fma_const(1.1663425624683784e-11, z, 2.087361778743318e-09);
-        pe = fma_const(pe, z, 2.7557345820982554e-07);
-        pe = fma_const(pe, z, 2.4801587176816665e-05);
-        pe = fma_const(pe, z, 0.0013888888889206652);
-        pe = fma_const(pe, z, 0.041666666666662695);
-        pe = fma_const(pe, z, 0.5000000000000002);
+        pe = fma_const(R(1.1653018610758553e-11), z, 2.0873996840137114e-09);
+        pe = fma_const(pe, z, 2.7557340351663354e-07);
+        pe = fma_const(pe, z, 2.4801587216386585e-05);
+        pe = fma_const(pe, z, 0.001388888888905748);
+        pe = fma_const(pe, z, 0.04166666666666542);
     }
-    return 1.0 + fma(z, pe, fma(u * z, po, u));
+    pe = fma(pe, z, R(0.5));
+    return R(1) + fma(z, pe, fma(u * z, po, u));
+}
+
+// sin and cos of a small angle t, |t| <= 1, FP32, made alike: errors of sin(t)/t below
+// 4e-10 and of cos t 2e-9, far below FP32 rounding.  R: float, or a wider type on the host.
+template <class R> __host__ __device__ inline void small_sincos_f32(R t, R &s, R &c)
+{
+    using std::fma;
+    const R z = t * t;
+    R ps = fma(R(2.7279914e-06f), z, R(-0.00019842645f));
+    ps = fma(ps, z, R(0.008333355f));
+    ps = fma(ps, z, R(-0.16666667f));
+    s = fma(t * z, ps, t);
+    R pc = fma(R(2.4213992e-05f), z, R(-0.0013884894f));
+    pc = fma(pc, z, R(0.041666582f));
+    pc = fma(pc, z, R(-0.5f));
+    c = fma(z, pc, R(1));
 }
 
 }  // namespace bemtx
