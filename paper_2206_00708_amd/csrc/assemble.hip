@@ -984,9 +984,12 @@ __device__ inline void singular_pair(const TriGeo *__restrict__ geo, const SingP
                     double xs0, xs1, ys0, ys1, jac;
                     ss_map(kind, reg, xi, e1, e2, e3, xs0, xs1, ys0, ys1, jac);
                     const double wt = gl.w[i0] * gl.w[i1] * w23 * jac;
+                    // both points by the same operations (left to itself, the compiler fuses the difference into one
+                    // of the two): the regions come in pairs with x and y exchanged, and in K and T of a coincident
+                    // pair, whose (x - y).n is rounding alone, the two cancel if d changes its sign exactly
                     double d[3];
                     for (int c = 0; c < 3; ++c)
-                        d[c] = (xs0 * ax[0][c] + xs1 * ax[1][c]) - (ys0 * ay[0][c] + ys1 * ay[1][c]);
+                        d[c] = fma(xs1, ax[1][c], xs0 * ax[0][c]) - fma(ys1, ay[1][c], ys0 * ay[0][c]);
                     const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
                     const double rinv = rsqrt_pos(r2);
                     const double r = r2 * rinv, kr_ = k * r;
