@@ -94,7 +94,10 @@ __global__ __launch_bounds__(256) void field_density_kernel(FieldArgs A, int R)
 
 // The contribution of one triangle at the point x to the sums of R
 // right-hand sides: sum over its quadrature points of G psi - dG/dn phi,
-// times 4 pi.  (y - x).n is the same for every y of the triangle.  BASE: the
+// times 4 pi.  (y - x).n is the same for every y of the triangle, but is taken at
+// each: next to a facet the nearest point, which counts most, then has the
+// smallest error (one value from the centroid made fields near a body 4 % and more
+// further off than the sums without BASE; 873 against 884 us on 100 x 100 points).  BASE: the
 // phase from the triangle's centroid, exp(i k r) = exp(i k r0) exp(i k (r - r0))
 // with |k (r - r0)| <= k rho <= kShortPhase (short polynomials instead of a reduction
 // per point); the factor exp(i k r0) is applied to the triangle's sums for
@@ -105,16 +108,14 @@ __device__ inline void field_triangle(const TriGeo &g, const double4 *__restrict
 {
     constexpr bool late = R <= 4;   // factors on the triangle's sums
     const double c0 = g.c[0] - x0, c1 = g.c[1] - x1, c2 = g.c[2] - x2;
-    const double dn = c0 * g.n[0] + c1 * g.n[1] + c2 * g.n[2];
     double er = 1.0, ei = 0.0, kr0 = 0.0;
     if constexpr (BASE) {
         kr0 = k * sqrt(c0 * c0 + c1 * c1 + c2 * c2);
         phase_sincos(kr0, &ei, &er);
     }
-    double gr_[R], gi_[R], fr_[R], fi_[R];
-    if constexpr (late)
+    double tr[R], ti[R];   // the triangle's sums without exp(i k r0) (late)
 #pragma unroll
-        for (int r = 0; r < R; ++r) gr_[r] = gi_[r] = fr_[r] = fi_[r] = 0.0;
+    for (int r = 0; r < R; ++r) tr[r] = ti[r] = 0.0;
 #pragma unroll
     for (int q = 0; q < 6; ++q) {
         const double d0 = g.qp[q][0] - x0, d1 = g.qp[q][1] - x1, d2 = g.qp[q][2] - x2;   // y - x
@@ -125,47 +126,35 @@ __device__ inline void field_triangle(const TriGeo &g, const double4 *__restrict
         if constexpr (BASE) small_sincos<true>(fma(k, rr, -kr0), sn, cs);
         else phase_sincos(kr, &sn, &cs);
         double gr = cs * rinv, gi = sn * rinv;                            // exp(ikr) / r
-        const double rinv2 = rinv * rinv;
-        double fr, fi;                                                    // exp(ikr)(ikr - 1) / r^3
+        const double s = -(d0 * g.n[0] + d1 * g.n[1] + d2 * g.n[2]) * (rinv * rinv);
+        double fr, fi;                                                    // -exp(ikr)(ikr - 1)(y-x).n / r^3
         if constexpr (CK) {
             const double dmp = exp(-kim * rr), am = -1.0 - kim * rr;
             gr *= dmp; gi *= dmp;
-            fr = (gr * am - gi * kr) * rinv2;
-            fi = (gr * kr + gi * am) * rinv2;
+            fr = (gr * am - gi * kr) * s;
+            fi = (gr * kr + gi * am) * s;
         } else {
-            fr = (-gr - gi * kr) * rinv2;
-            fi = (gr * kr - gi) * rinv2;
+            fr = (-gr - gi * kr) * s;
+            fi = (gr * kr - gi) * s;
         }
-        if constexpr (late) {
+        if constexpr (BASE && !late) {
+            const double g0 = gr, f0 = fr;
+            gr = g0 * er - gi * ei; gi = g0 * ei + gi * er;
+            fr = f0 * er - fi * ei; fi = f0 * ei + fi * er;
+        }
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const double4 w = dens[q * R + r];
-                gr_[r] = fma(-gi, w.y, fma(gr, w.x, gr_[r]));
-                gi_[r] = fma(gi, w.x, fma(gr, w.y, gi_[r]));
-                fr_[r] = fma(-fi, w.w, fma(fr, w.z, fr_[r]));
-                fi_[r] = fma(fi, w.z, fma(fr, w.w, fi_[r]));
-            }
-        } else {
-            if constexpr (BASE) {
-                const double g0 = gr, f0 = fr;
-                gr = g0 * er - gi * ei; gi = g0 * ei + gi * er;
-                fr = f0 * er - fi * ei; fi = f0 * ei + fi * er;
-            }
-            fr *= -dn; fi *= -dn;
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const double4 w = dens[q * R + r];
-                ar[r] = fma(-fi, w.w, fma(fr, w.z, fma(-gi, w.y, fma(gr, w.x, ar[r]))));
-                ai[r] = fma(fi, w.z, fma(fr, w.w, fma(gi, w.x, fma(gr, w.y, ai[r]))));
-            }
+        for (int r = 0; r < R; ++r) {
+            const double4 w = dens[q * R + r];
+            double &zr = late ? tr[r] : ar[r], &zi = late ? ti[r] : ai[r];
+            zr = fma(-fi, w.w, fma(fr, w.z, fma(-gi, w.y, fma(gr, w.x, zr))));
+            zi = fma(fi, w.z, fma(fr, w.w, fma(gi, w.x, fma(gr, w.y, zi))));
         }
     }
     if constexpr (late)
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const double tr = gr_[r] - dn * fr_[r], ti = gi_[r] - dn * fi_[r];
-            ar[r] = fma(-ti, ei, fma(tr, er, ar[r]));
-            ai[r] = fma(ti, er, fma(tr, ei, ai[r]));
+            ar[r] = fma(-ti[r], ei, fma(tr[r], er, ar[r]));
+            ai[r] = fma(ti[r], er, fma(tr[r], ei, ai[r]));
         }
 }
 

@@ -39,3 +39,53 @@ def test_singular_double_layer(orc, seed):
         assert _rel(p.operator(0, op).cpu().numpy(), ref[op]) < 3.5e-15, op
     for h in (p, m, cx):
         h.close()
+
+
+def _field(T, xyz, tri, k, phi, psi, pts):
+    """[SLP psi - DLP phi] at points, in the real type T."""
+    x = xyz.astype(T)[tri]
+    cr = np.cross(x[:, 1] - x[:, 0], x[:, 2] - x[:, 0])
+    ln = np.sqrt((cr * cr).sum(1))
+    n, area = cr / ln[:, None], ln / 2
+    a = np.array([0.445948490915964886, 0.091576213509770743]).astype(T)
+    w = np.array([0.223381589678011466, 0.109951743655321867]).astype(T)
+    bary = np.stack([np.where(np.arange(3) == q % 3, 1 - 2 * a[q // 3], a[q // 3]) for q in range(6)])
+    c = np.result_type(T, np.complex64)
+    y = np.einsum("qa,tac->tqc", bary, x)
+    W = area[:, None] * np.repeat(w, 3)
+    ph, ps = (W * np.einsum("qa,ta->tq", bary, v.astype(c)[tri]) for v in (phi, psi))
+    d = y[None] - pts.astype(T)[:, None, None, :]
+    r = np.sqrt((d * d).sum(-1))
+    e = np.cos(k * r) + 1j * np.sin(k * r)
+    dn = (d * n[None, :, None, :]).sum(-1)
+    pi4 = 16 * np.arctan(T(1))
+    return ((e / r * ps - e * (1j * k * r - 1) * dn / (r * r * r) * ph) / pi4).sum((1, 2))
+
+
+@pytest.mark.parametrize("k,nrhs,before", [(1.5, 1, 6.85e-16), (1.5, 6, 7.74e-16), (9.0, 1, 7.51e-16)])
+def test_field_near_the_surface(k, nrhs, before):
+    """Points next to the facets of a body, by the triangle's phase and by the
+    points' (k rho below and above 0.4): the error against extended precision
+    is at most `before`, that of one launch per right-hand side and region
+    with a full phase at every quadrature point on the same inputs."""
+    xyz, tri = _mesh(3, 1)
+    rng = np.random.default_rng(5)
+    t = rng.integers(0, len(tri), 300)
+    lam = rng.dirichlet((1.0, 1.0, 1.0), 300)
+    pts = np.einsum("pa,pac->pc", lam, xyz[tri[t]]) * (1 - rng.uniform(0.02, 0.2, (300, 1)))
+    nv = len(xyz)
+    cx = B.Context(0)
+    m = B.Mesh(cx, xyz, tri)
+    p = B.Problem(cx, m, m, 1.0, k)
+    x = rng.standard_normal((nrhs, 4 * nv)) + 1j * rng.standard_normal((nrhs, 4 * nv))
+    d = synth.plane_wave_directions(nrhs, rng)
+    got = p.field(d, torch.as_tensor(x), pts, torch.ones(300, dtype=torch.int32)).cpu().numpy()
+    err = size = 0.0
+    for r in range(nrhs):
+        v, w = -x[r, 2 * nv:3 * nv], -x[r, 3 * nv:]
+        ref = _field(np.longdouble, xyz, tri, np.longdouble(k), v, w, pts)
+        err += float((np.abs(got[r] - ref) ** 2).sum())
+        size += float((np.abs(ref) ** 2).sum())
+    assert (err / size) ** 0.5 <= before
+    for h in (p, m, cx):
+        h.close()
