@@ -248,15 +248,31 @@ __global__ __launch_bounds__(256) void field_combine_kernel(FieldArgs A, int R, 
 // length from its square; 0 for 0
 __device__ inline double length_of(double r2) { return r2 * rsqrt_pos(fmax(r2, 1e-300)); }
 
-// part[chunk][i] = half the chunk's solid angle: the sum over its triangles of
-// arg z, z = den + i num.  The sum of arguments is the argument of the
-// product of the z plus 2 pi per crossing of the negative real axis, so one
-// arctangent serves the whole chunk: the product P has crossed it when P
-// before and z lie on one side of the real axis and P after on the other
-// (sides by the sign bit, so that arguments of +-0 and +-pi count as atan2
-// gives them).  z is scaled by a power of two, P every 64 triangles.  Bound by
-// FP64 issue; 10,000 points x 5,120 triangles: 319 us with an arctangent per
-// triangle, 190 us.
+// atan2(num, den).  The half solid angle of all triangles but those next to the
+// point is small: |num| <= den / 8 takes the quotient (hardware reciprocal, one Newton
+// step, one correction of the quotient) and q + q z p(z), z = q^2, p minimax as in
+// phase.h with errors below 2e-18 relative to q.  den is bounded so that its reciprocal is
+// neither 0 nor infinite; a point far enough for the lengths' product to overflow, a corner
+// (0, 0) and NaN take the library function.
+__device__ inline double half_angle(double num, double den)
+{
+    if (!(fabs(num) <= 0.125 * den && den > 1e-290 && den < 1e290)) return atan2(num, den);
+    double y = __builtin_amdgcn_rcp(den);
+    y = fma(y, fma(-den, y, 1.0), y);
+    double q = num * y;
+    q = fma(fma(-den, q, num), y, q);
+    const double z = q * q;
+    double p = fma_const(0.07342729565358729, z, -0.0908360288044579);
+    p = fma_const(p, z, 0.11111035635624597);
+    p = fma_const(p, z, -0.14285713890803944);
+    p = fma_const(p, z, 0.19999999999049253);
+    p = fma_const(p, z, -0.3333333333333257);
+    return fma(q * z, p, q);
+}
+
+// part[chunk][i] = half the chunk's solid angle, the sum over its triangles of
+// atan2(num, den).  Bound by FP64 issue; a call for 10,000 points and 5,120
+// triangles takes 303 us with the library's arctangent for every triangle, 177 us so.
 __global__ __launch_bounds__(FLD_PB) void winding_partial_kernel(int np, const double *__restrict__ pts, int nt,
                                                                  int tpc, int npb, const TriGeo *__restrict__ geo,
                                                                  double *__restrict__ part)
@@ -266,8 +282,7 @@ __global__ __launch_bounds__(FLD_PB) void winding_partial_kernel(int np, const d
     const bool live = i < np;
     const double x0 = live ? pts[3 * (int64_t)i] : 0.0, x1 = live ? pts[3 * (int64_t)i + 1] : 0.0,
                  x2 = live ? pts[3 * (int64_t)i + 2] : 0.0;
-    double pr = 1.0, pi = 0.0;
-    int turns = 0;
+    double acc = 0.0;
 #pragma unroll 1
     for (int t = t0; t < t1; ++t) {
         const double(*v)[3] = geo[t].p;
@@ -276,36 +291,30 @@ __global__ __launch_bounds__(FLD_PB) void winding_partial_kernel(int np, const d
         const double c0 = v[2][0] - x0, c1 = v[2][1] - x1, c2 = v[2][2] - x2;
         const double la = length_of(a0 * a0 + a1 * a1 + a2 * a2), lb = length_of(b0 * b0 + b1 * b1 + b2 * b2),
                      lc = length_of(c0 * c0 + c1 * c1 + c2 * c2);
-        double num = a0 * (b1 * c2 - b2 * c1) + a1 * (b2 * c0 - b0 * c2) + a2 * (b0 * c1 - b1 * c0);
-        double den = la * lb * lc + (a0 * b0 + a1 * b1 + a2 * b2) * lc + (a0 * c0 + a1 * c1 + a2 * c2) * lb +
-                     (b0 * c0 + b1 * c1 + b2 * c2) * la;
-        if (num == 0.0 && den == 0.0) den = 1.0;   // atan2(0, 0) = 0: the point is a corner
-        const int e = __builtin_amdgcn_frexp_exp(fmax(fabs(num), fabs(den)));
-        num = ldexp(num, -e);
-        den = ldexp(den, -e);
-        const double nr = pr * den - pi * num, ni = pr * num + pi * den;
-        const bool s0 = signbit(pi), s1 = signbit(num), s2 = signbit(ni);
-        if (s0 == s1 && s2 != s0) turns += s0 ? -1 : 1;
-        pr = nr;
-        pi = ni;
-        if (((t - t0) & 63) == 63) {
-            const int f = __builtin_amdgcn_frexp_exp(fmax(fabs(pr), fabs(pi)));
-            pr = ldexp(pr, -f);
-            pi = ldexp(pi, -f);
-        }
+        const double num = a0 * (b1 * c2 - b2 * c1) + a1 * (b2 * c0 - b0 * c2) + a2 * (b0 * c1 - b1 * c0);
+        const double den = la * lb * lc + (a0 * b0 + a1 * b1 + a2 * b2) * lc + (a0 * c0 + a1 * c1 + a2 * c2) * lb +
+                           (b0 * c0 + b1 * c1 + b2 * c2) * la;
+        acc += half_angle(num, den);
     }
-    if (live) part[(int64_t)chunk * np + i] = atan2(pi, pr) + 6.283185307179586 * turns;
+    if (live) part[(int64_t)chunk * np + i] = acc;
 }
 
+// w[i] = the chunks' sum over 2 pi.  With the errors of its additions (exact, by
+// two-sum) added at the end: up to a few hundred chunks of a closed body add to
+// 2 pi or cancel, and plain addition was the largest error of the result.
 __global__ __launch_bounds__(256) void winding_combine_kernel(int np, int nchunk, const double *__restrict__ part,
                                                               double *__restrict__ w)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= np) return;
-    double s = 0.0;
+    double s = 0.0, e = 0.0;
 #pragma unroll 8
-    for (int c = 0; c < nchunk; ++c) s += part[(int64_t)c * np + i];
-    w[i] = 2.0 * s * kInv4Pi;
+    for (int c = 0; c < nchunk; ++c) {
+        const double v = part[(int64_t)c * np + i], t = s + v, d = t - s;
+        e += (s - (t - d)) + (v - d);
+        s = t;
+    }
+    w[i] = 2.0 * (s + e) * kInv4Pi;
 }
 
 // Triangle chunks for np points: about FLD_WG workgroups, at least FLD_TMIN
