@@ -376,16 +376,27 @@ constexpr double kR6G = kW1 * (1.0 - 3.0 * kA1);
 constexpr double kR6C = kW2 * (1.0 - 3.0 * kA2) / kR6G;
 constexpr double kR6H = kW1 * kA1 / kR6G;
 constexpr double kR6S = kW2 * kA2 / kR6G - kR6H * kR6C;
+template <class R> struct Rule6Const {
+    static constexpr R G = kR6G, C = kR6C, H = kR6H, S = kR6S;
+};
+// (Mixed operators against FP64 ones, 10,242 + 7,842 vertices: V 5.0e-8, K and T 6.1e-8, D 9.4e-8; 5.7e-8, 8.7e-8 and
+// 9.2e-8 with correctly rounded 1 / r and the plain weights.)  In FP32 the constants' own rounding would put errors up to 9e-8 on the orbits' weights, the same for all
+// pairs; C, H and S are the floats within 6 ulps, with their G, that leave the least: 3e-9, the weights' sum exact.
+template <> struct Rule6Const<float> {
+    static constexpr double G = kR6G * 1.000000060973267;
+    static constexpr float C = -1.0566645860671997f, H = -1.3199776411056519f, S = -1.5281931161880493f;
+};
 template <class R> struct Rule6Sum {
+    using Q = Rule6Const<R>;
     R h[3], s;
     __device__ void add(int b, R g0, R g1)   // g_b and g_{b+3}, b = 0, 1, 2 in this order
     {
-        h[b] = g0 + (R)kR6C * g1;
+        h[b] = g0 + Q::C * g1;
         s = b == 0 ? g1 : s + g1;
     }
     __device__ void finish()
     {
-        const R m = (R)kR6H * (h[0] + h[1] + h[2]) + (R)kR6S * s;
+        const R m = Q::H * (h[0] + h[1] + h[2]) + Q::S * s;
 #pragma unroll
         for (int b = 0; b < 3; ++b) h[b] += m;
     }
@@ -609,7 +620,9 @@ __global__ __launch_bounds__(256, 2) void regular_tiles_kernel(TileArgs A)
 // |d0|, exp(i k r) = exp(i k r0) exp(i k D), where exp(i k r0) is evaluated
 // once in FP64 and applied to the sums, and D = r - r0 = e.(2 d0 + e) / (r +
 // r0), e = (x - c_x) - (y - c_y), is small and accurate in FP32; FP32 alone
-// would lose about k r * 6e-8 of phase.  SMALL: |k D| <= 1 at every point
+// would lose about k r * 6e-8 of phase.  1 / r is the hardware estimate (1 ulp) with a
+// Newton step, since it enters K and T three times; the quotient in D takes the
+// hardware reciprocal, whose error meets the small phase k D only.  SMALL: |k D| <= 1 at every point
 // pair.  CK: the damping exp(-kim r) splits like the phase, exp(-kim r0) in
 // FP64 per pair and exp(-kim D) in FP32 per point.
 template <bool CK, bool SMALL>
@@ -651,7 +664,8 @@ __device__ inline void pair_quadrature_f32(const TriGeoF &X, const TriGeoF &Y, d
                 const float q0 = x0 - Y.dq[q][0], q1 = x1 - Y.dq[q][1], q2 = x2 - Y.dq[q][2];   // e
                 const float d0 = f00 + q0, d1 = f01 + q1, d2 = f02 + q2;                         // x - y
                 const float r2 = d0 * d0 + d1 * d1 + d2 * d2;
-                const float rinv = __builtin_amdgcn_rsqf(r2);
+                const float ri = __builtin_amdgcn_rsqf(r2);
+                const float rinv = fmaf(0.5f * ri, fmaf(-r2 * ri, ri, 1.f), ri);
                 const float r = r2 * rinv;
                 const float num = q0 * (f00 + d0) + q1 * (f01 + d1) + q2 * (f02 + d2);
                 const float dr = num * __builtin_amdgcn_rcpf(r + r0f);
@@ -675,13 +689,13 @@ __device__ inline void pair_quadrature_f32(const TriGeoF &X, const TriGeoF &Y, d
             htr.add(b, fr[0] * dtq[b], fr[1] * dtq[b + 3]); hti.add(b, fi[0] * dtq[b], fi[1] * dtq[b + 3]);
         }
         hvr.finish(); hvi.finish(); hkr.finish(); hki.finish(); htr.finish(); hti.finish();
-        const float wp = (float)kR6G * (p < 3 ? (float)kW1 : (float)kW2);
-        const float ap = p < 3 ? (float)kA1 : (float)kA2;
-        const float am = p < 3 ? (float)(1.0 - 2.0 * kA1) : (float)(1.0 - 2.0 * kA2);
-        const int pc = p < 3 ? p : p - 3;
+        constexpr double G = Rule6Const<float>::G;
+        const float wo = p < 3 ? (float)(G * kW1 * kA1) : (float)(G * kW2 * kA2);
+        const float wc = p < 3 ? (float)(G * kW1 * (1.0 - 2.0 * kA1)) : (float)(G * kW2 * (1.0 - 2.0 * kA2));
+        const int pc = p < 3 ? p : p - 3;   // corner carrying 1 - 2a
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            const float W = wp * (a == pc ? am : ap), Wk = W * dkp;
+            const float W = a == pc ? wc : wo, Wk = W * dkp;
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
                 vr[3 * a + b] += W * hvr.h[b]; vi[3 * a + b] += W * hvi.h[b];
