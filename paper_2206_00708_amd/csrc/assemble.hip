@@ -622,9 +622,10 @@ __global__ __launch_bounds__(256, 2) void regular_tiles_kernel(TileArgs A)
 // r0), e = (x - c_x) - (y - c_y), is small and accurate in FP32; FP32 alone
 // would lose about k r * 6e-8 of phase.  1 / r is the hardware estimate (1 ulp) with a
 // Newton step, since it enters K and T three times; the quotient in D takes the
-// hardware reciprocal, whose error meets the small phase k D only.  SMALL: |k D| <= 1 at every point
-// pair.  CK: the damping exp(-kim r) splits like the phase, exp(-kim r0) in
-// FP64 per pair and exp(-kim D) in FP32 per point.
+// hardware reciprocal, whose error meets the small phase k D only.  SMALL: |k D| and, CK, |kim D| <= 1
+// at every point pair.  CK: the damping exp(-kim r) splits like the phase, exp(-kim r0) in
+// FP64 per pair and exp(-kim D) in FP32 per point; where kim D is not small, both
+// go to each value (exp(-kim D) / r^3 alone can leave the range of FP32).
 template <bool CK, bool SMALL>
 __device__ inline void pair_quadrature_f32(const TriGeoF &X, const TriGeoF &Y, double k, double kim, float (&vr)[9],
                                            float (&vi)[9], float (&kr)[9], float (&ki)[9], float (&tr)[9],
@@ -639,6 +640,8 @@ __device__ inline void pair_quadrature_f32(const TriGeoF &X, const TriGeoF &Y, d
         s0 *= dm0;
         c0 *= dm0;
     }
+    constexpr bool EACH = CK && !SMALL;   // the pair's factor on the values instead of the sums
+    const float e0r = (float)c0, e0i = (float)s0;
     const float kf = (float)k, kimf = (float)kim;
     const float f00 = (float)d00, f01 = (float)d01, f02 = (float)d02, r0f = (float)r0;
     const float ny0 = Y.n[0], ny1 = Y.n[1], ny2 = Y.n[2];
@@ -672,11 +675,19 @@ __device__ inline void pair_quadrature_f32(const TriGeoF &X, const TriGeoF &Y, d
                 float sd, cd;
                 if constexpr (SMALL) small_sincos_f32(kf * dr, sd, cd);
                 else sincosf(kf * dr, &sd, &cd);
+                if constexpr (EACH) {
+                    const float dd = expf(-kimf * dr), x = cd;
+                    cd = (e0r * x - e0i * sd) * dd;
+                    sd = (e0r * sd + e0i * x) * dd;
+                }
                 gr[o] = cd * rinv; gi[o] = sd * rinv;              // exp(ik(r - r0))/r
                 const float kr_ = kf * r, rinv2 = rinv * rinv;
                 if constexpr (CK) {
-                    const float dd = expf(-kimf * dr), am = -1.f - kimf * r;
-                    gr[o] *= dd; gi[o] *= dd;
+                    const float am = -1.f - kimf * r;
+                    if constexpr (!EACH) {
+                        const float dd = expf(-kimf * dr);
+                        gr[o] *= dd; gi[o] *= dd;
+                    }
                     fr[o] = (gr[o] * am - gi[o] * kr_) * rinv2;
                     fi[o] = (gr[o] * kr_ + gi[o] * am) * rinv2;
                 } else {
@@ -704,7 +715,7 @@ __device__ inline void pair_quadrature_f32(const TriGeoF &X, const TriGeoF &Y, d
             }
         }
     }
-    const float scale = X.area * Y.area * (float)kInv4Pi, er = scale * (float)c0, ei = scale * (float)s0;
+    const float scale = X.area * Y.area * (float)kInv4Pi, er = EACH ? scale : scale * e0r, ei = EACH ? 0.f : scale * e0i;
     auto turn = [&](float &re, float &im) {
         const float x = re;
         re = x * er - im * ei;
@@ -757,8 +768,8 @@ __global__ __launch_bounds__(256, 3) void regular_tiles_f32_kernel(TileArgsF A)
     float vr[9], vi[9], kr[9], ki[9], tr[9], ti[9], sr = 0.f, si = 0.f;
 #pragma unroll
     for (int e = 0; e < 9; ++e) { vr[e] = vi[e] = kr[e] = ki[e] = tr[e] = ti[e] = 0.f; }
-    // |k (r - r0)| <= 1 at every point pair of every pair of the wave: short polynomials
-    const bool tame = !__any(active && kf * (X.rho + Y.rho) > 1.f);
+    // |k (r - r0)| <= 1, and the damping's exponent alike, at every point pair of every pair of the wave
+    const bool tame = !__any(active && (CK ? fmaxf(kf, (float)A.kim) : kf) * (X.rho + Y.rho) > 1.f);
     if (active) {
         if (tame) pair_quadrature_f32<CK, true>(X, Y, A.k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);
         else pair_quadrature_f32<CK, false>(X, Y, A.k, A.kim, vr, vi, kr, ki, tr, ti, sr, si);

@@ -139,3 +139,25 @@ def test_mixed_operators():
     before = np.array([4.982e-8, 7.820e-8, 7.822e-8, 6.397e-8])
     err = np.mean([_mixed_errors(s) for s in (1, 2, 3, 4)], axis=0)
     assert np.all(err <= before * np.array([1, 1, 1, 1.02])), err
+
+
+def test_mixed_operators_with_strong_damping(orc):
+    """A body of radius 1e-6 whose medium damps by exp(-78) across a pair of
+    neighbouring triangles' quadrature points: exp(-kim (r - r0)) / r^3 leaves
+    the range of FP32, the values do not.  Bounds of the mixed operators:
+    2e-5 and 1e-4 of the largest entry."""
+    xyz, tri = _mesh(5, 1)
+    xyz = 1e-6 * xyz
+    k, kim = 1e5, 1.5e8
+    cx = B.Context(0)
+    m = B.Mesh(cx, xyz, tri)
+    p = B.Problem(cx, m, m, k, k, precision=B.C64_MIXED)
+    p.set_k_int_imag(kim)
+    p.assemble_operators()
+    ref = orc.assemble(xyz, tri, k + 1j * kim)
+    for op in "VKTD":
+        got = p.operator(1, op).cpu().numpy().astype(np.complex128)
+        assert np.all(np.isfinite(got.view(np.float64))), op
+        assert _rel(got, ref[op]) < 2e-5 and np.abs(got - ref[op]).max() < 1e-4 * np.abs(ref[op]).max(), op
+    for h in (p, m, cx):
+        h.close()
