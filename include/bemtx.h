@@ -91,7 +91,8 @@ typedef struct {
     int32_t ir_steps;
     double rel_residual;      /* worst strong-form relative residual, recomputed in FP64 at exit */
     double t_geometry_ms;
-    double t_regular_ms, t_singular_ms;   /* device time of each part, summed over the two meshes */
+    double t_regular_ms, t_singular_ms;   /* device time of each part, summed over the two meshes (two small
+                                             meshes are assembled side by side: their times then overlap) */
     double t_projection_ms;   /* host time of bem_assemble_projection */
     double t_matrix_ms;       /* t_assembly_ms + t_projection_ms */
     double t_solve_ms;

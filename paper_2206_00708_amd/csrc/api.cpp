@@ -202,9 +202,9 @@ void flush_kernel_timing(bem_ctx *c)
 bem_status resolve_assembly_timing(bem_problem *p)
 {
     if (!p->asm_timing_pending) return BEM_OK;
-    BEM_HIP(hipEventSynchronize(p->asm_ev[1][2]));
+    BEM_HIP(hipEventSynchronize(p->asm_end));
     float span = 0;
-    BEM_HIP(hipEventElapsedTime(&span, p->asm_ev[0][0], p->asm_ev[1][2]));
+    BEM_HIP(hipEventElapsedTime(&span, p->asm_ev[0][0], p->asm_end));
     double t_reg = 0, t_sing = 0;
     for (int m = 0; m < 2; ++m) {
         float a = 0, b = 0;
@@ -441,6 +441,7 @@ void bem_problem_destroy(bem_problem *p)
     for (int m = 0; m < 2; ++m)
         for (int q = 0; q < 3; ++q)
             if (p->asm_ev[m][q]) (void)hipEventDestroy(p->asm_ev[m][q]);
+    if (p->asm_end) (void)hipEventDestroy(p->asm_end);
     if (p->ev_pre_asm) (void)hipEventDestroy(p->ev_pre_asm);
     if (p->ev_proj) (void)hipEventDestroy(p->ev_proj);
     delete p;
@@ -603,10 +604,12 @@ static bem_status queue_assembly(bem_problem *p, int32_t parts)
         sg = grow_scratch(ctx, sz.one);
     }
     if (sg) return sg;
-    // events: [mesh][0] before regular, [1] before singular, [2] after; resolved lazily
+    // events: [mesh][0] before regular, [1] before singular, [2] after, on the mesh's stream, and the end of both
+    // meshes; resolved lazily
     for (int m = 0; m < 2; ++m)
         for (int q = 0; q < 3; ++q)
             if (!p->asm_ev[m][q]) BEM_HIP(hipEventCreate(&p->asm_ev[m][q]));
+    if (!p->asm_end) BEM_HIP(hipEventCreate(&p->asm_end));
     hipStream_t side = st;   // stream of the interior mesh
     if (off1) {
         if (!ctx->gather) BEM_HIP(hipStreamCreateWithFlags(&ctx->gather, hipStreamNonBlocking));
@@ -636,7 +639,8 @@ static bem_status queue_assembly(bem_problem *p, int32_t parts)
                                            static_cast<double2 *>(scratch), ops, st);
             if (s) return s;
         }
-        if (!(off1 && m == 1)) BEM_HIP(hipEventRecord(p->asm_ev[m][2], st));
+        BEM_HIP(hipEventRecord(p->asm_ev[m][2], st));
+        if (m == 1 && !off1) BEM_HIP(hipEventRecord(p->asm_end, st));
         bem_status s = launch_sym_corrections(p, m, st);
         if (s) return s;
     }
@@ -645,7 +649,7 @@ static bem_status queue_assembly(bem_problem *p, int32_t parts)
         if (!ev) BEM_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
         BEM_HIP(hipEventRecord(ev, side));
         BEM_HIP(hipStreamWaitEvent(main_stream, ev, 0));
-        BEM_HIP(hipEventRecord(p->asm_ev[1][2], main_stream));
+        BEM_HIP(hipEventRecord(p->asm_end, main_stream));
     }
     return BEM_OK;
 }
