@@ -439,7 +439,8 @@ bem_status bem_mesh_winding(const bem_mesh *m, const double *points, int64_t npt
  * <K chunks, exterior> <K chunks, interior> <k per LDS stage>" for the
  * multi-right-hand-side operator product (an entry in another format is
  * tuned again), "gemm-mass:..." likewise for the dense inverse-mass product,
- * "mtf-c128:..." / "mtf-c64:... <tile edge>" for the symmetric mat-vec;
+ * "mtf-c128:..." / "mtf-c64:... <tile edge>" for the symmetric mat-vec (with
+ * ":small" behind the classes where the pair is too small to be timed);
  * class = round(4 log2 N) of the exterior and interior vertex counts.  The
  * table is shared by all contexts of the process and kept in the file
  * $BEMTX_TUNE_FILE (else $XDG_CACHE_HOME/bemtx/tune-gfx950.txt, else

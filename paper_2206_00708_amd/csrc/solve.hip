@@ -2117,17 +2117,20 @@ bem_status apply_A(const bem_problem *p, const MtfArgs &A, const double2 *x, dou
     return BEM_OK;
 }
 
-// Tile edge of the symmetric mat-vec (64 or 128) by timing both on the
-// problem's operators once per size class and precision (tuning table).
-// x: any n-vector; y, part: work buffers.
+// Tile edge of the symmetric mat-vec: 64 for a small pair, else 64 or 128 by
+// timing both on the problem's operators once per size class and precision
+// (tuning table; small pairs have entries of their own, so that a class on the
+// line between the two is still timed for its larger pairs).  x: any n-vector;
+// y, part: work buffers.
 bem_status mtf_tune(bem_problem *p, const double2 *x, double2 *y, double4 *part)
 {
     if (p->mtf_ts) return BEM_OK;
+    const bool small = sym_small((int)p->ext->h.nv, (int)p->inte->h.nv);
     const std::string key = std::string(p->prec == BEM_C128 ? "mtf-c128" : "mtf-c64") + ":e" +
-                            std::to_string(tune_class(p->ext->h.nv)) + ":i" + std::to_string(tune_class(p->inte->h.nv));
+                            std::to_string(tune_class(p->ext->h.nv)) + ":i" + std::to_string(tune_class(p->inte->h.nv)) +
+                            (small ? ":small" : "");
     hipStream_t st = p->ctx->stream;
     std::vector<int> v;
-    const bool small = sym_small((int)p->ext->h.nv, (int)p->inte->h.nv);
     auto valid = [&](const std::vector<int> &q) { return q.size() == 1 && (q[0] == 64 || (q[0] == 128 && !small)); };
     bem_status s = tuned(key, v, [&](std::vector<int> &out) -> bem_status {
         if (small) {
@@ -2160,7 +2163,7 @@ bem_status mtf_tune(bem_problem *p, const double2 *x, double2 *y, double4 *part)
         return BEM_OK;
     }, valid);
     if (s) return s;
-    p->mtf_ts = valid(v) ? v[0] : 128;
+    p->mtf_ts = valid(v) ? v[0] : (small ? 64 : 128);
     return BEM_OK;
 }
 
