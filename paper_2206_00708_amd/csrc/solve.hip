@@ -1830,7 +1830,9 @@ bem_status launch_to_internal(const bem_problem *p, const double2 *x_caller, dou
 // is read as it lies into LDS (its first `cap` 16-byte units; what does not fit is read from memory) and
 // taken apart there, so that memory sees whole lines both ways.  It moves the bytes at the rate of a copy:
 // 10,242 x 10,242 complex128 875 -> 608 us (5.5 TB/s read and written), complex64 505 -> 306 us, against
-// reading the entries from memory one by one (cap = 0: the form of short rows, which the caches hold).
+// reading the entries from memory one by one (cap = 0: the form of short rows, which the caches hold).  Rows
+// far longer than the LDS gain as much, since its share of a row is still read whole: 30,000 x 30,000
+// complex128 9.3 -> 5.7 ms, 40,000 x 40,000 complex64 10.4 -> 6.5 ms.
 template <class C2, int NTH>
 __global__ __launch_bounds__(NTH) void permute_mat_kernel(int nv, int cap, const int32_t *__restrict__ perm,
                                                           const C2 *__restrict__ src, C2 *__restrict__ dst)
@@ -1871,7 +1873,9 @@ bem_status launch_permute_mat(const bem_problem *p, int nv, const int32_t *perm,
     const C2 *s = static_cast<const C2 *>(src);
     C2 *d = static_cast<C2 *>(dst);
     hipStream_t st = p->ctx->stream;
-    if (nv <= 2048) {   // (162 vertices: 8 staged copies took 3 to 10 us longer)
+    // short rows: 162 vertices, 8 staged copies took 3 to 10 us longer; complex64 2,052 vertices 28 against 33 us
+    // staged, 3,202 44 against 45, 4,002 59 against 53; complex128 2,052 35 against 36, 3,202 109 against 76
+    if (nv <= (sizeof(C2) == 8 ? 3200 : 2048)) {
         hipLaunchKernelGGL((permute_mat_kernel<C2, 256>), dim3(nv), dim3(256), 0, st, nv, 0, perm, s, d);
     } else {
         const size_t row = (nv * sizeof(C2) + 15) / 16 * 16;
