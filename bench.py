@@ -76,7 +76,8 @@ COUNTED_TRAFFIC = {
 # (SQ_INSTS_VALU x 4 cycles over the SIMD cycles of the launch, from
 # GRBM_GUI_ACTIVE per XCD x 1024 SIMDs) and the share of the FP64 flops in
 # the software sin/cos (the small-angle polynomials and the rotation by the
-# pair's base phase: about 33 of the 110 flops per point pair).
+# pair's base phase: about 33 of the 110 counted flops per point pair, which
+# the model above holds as 97 without the work per triangle pair and tile).
 REG_REGIONS = {"source": "paper_2206_00708_amd/csrc/assemble.hip",
                "regions": [("// ------------------------------------------------------------ regular pairs",
                             "// The contributions to dense entry (i, j) of the tiles of one strip")]}
@@ -467,11 +468,15 @@ def serving_run(B, synth, n_requests=24, n_sustained=32, slots=4, tol=1e-5, maxi
     return out
 
 
-# FP64 operations per quadrature-point evaluation of the field kernel (FMA =
-# 2): y - x 3, r^2 5, 1/r 1, k r 2, phase reduction and sin/cos polynomials
-# 45, exp(ikr)/r 2, (y - x).n / r^2 7, the radial factor 6, the two complex
-# products and sums 16.
-FIELD_FLOP_PER_EVAL = 87
+# FP64 operations per quadrature-point evaluation of the field kernel for one
+# right-hand side (FMA = 2), in the form that takes the phase from the
+# triangle's centroid (this workload's): y - x 3, r^2 5, 1/r and r 9, k r 1,
+# the angle off the base phase 2, the short sin/cos polynomials 24,
+# exp(ikr)/r 2, (y - x).n / r^2 7, the radial factor 6, the two complex
+# products and sums 16: 75; and a sixth of a triangle's own 63 (the base
+# phase: centroid distance 10, reduction and polynomials 45; rotation of its
+# sums 8).
+FIELD_FLOP_PER_EVAL = 85.5
 
 
 def field_run(ctx, B, synth, np, reps=5):
@@ -704,7 +709,7 @@ def main():
     # the timed steps carry events on the two roofline kernels only
     timed = ("regular_tiles", "mtf_dense")
     breakdown = ("regular_tiles", "gather_tiles", "singular_pairs", "mtf_dense", "mass_apply", "cgs_dots",
-                 "cgs_update", "arnoldi_finish", "krylov_normalize")
+                 "cgs_update", "arnoldi_finish")
     t_bench = time.perf_counter()
     r = run_workload(ctx, B, c, B.C128, tol, args.steps, args.warmup, timed, breakdown)
     head = summarise(c, r, args.steps, B.C128, tol, name)
