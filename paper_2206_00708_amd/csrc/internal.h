@@ -222,7 +222,7 @@ void transpose_csr(const Csr &A, Csr &At);
 // Sparse inverse-mass apply (mass_cheb.cpp): Chebyshev iteration on the
 // Jacobi-scaled mass matrix, s steps per launch on overlapping patches of
 // vertices (owned range + every vertex within s edges, listed by distance).
-constexpr int CHEB_OWN_MAX = 512;    // owned vertices per patch (halved until the patches fit)
+constexpr int CHEB_OWN_MAX = 512;    // owned vertices per patch (fewer until the patches fit)
 constexpr int CHEB_LMAX = 2048;      // vertices per patch: 2 per thread of a 1024-thread workgroup
 constexpr int CHEB_WMAX = 16;        // entries per mass-matrix row (the vertex and its neighbours)
 constexpr int CHEB_S = 12;           // steps per launch
@@ -234,9 +234,6 @@ struct ChebTables {
     HVec<int32_t> cnt;                // [patch][s + 1] vertices within d edges of the owned range
     HVec<int32_t> vert;               // local vertex -> mesh vertex (internal numbering)
     HVec<double> dinv;                // 1 / M_vv
-    HVec<int32_t> rptr;               // [local vertex + 1] row starts into col / val (rows within s - 1 edges)
-    HVec<int32_t> col;                // local column index within the patch
-    HVec<double> val;
     int ell_w = 0;                    // entries beside the diagonal, at most; the rows as ELL blocks [q][local row]:
     HVec<uint16_t> ecol;              // patch p at ell_w vbeg[p], local columns
     HVec<double> eval;                // patch p at (ell_w + 1) vbeg[p], the diagonal first

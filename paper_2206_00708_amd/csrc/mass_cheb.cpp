@@ -12,6 +12,7 @@
 // patch's vertices are listed by distance from the owned range, so that the
 // rows updated at step t are a prefix of the list.
 #include <algorithm>
+#include <atomic>
 #include <vector>
 
 #include "internal.h"
@@ -52,7 +53,8 @@ std::vector<std::vector<int32_t>> clusters(const Csr &M, int own)
     return out;
 }
 
-void build_patch(const Csr &M, const std::vector<int32_t> &owned, int s, std::vector<int32_t> &dist,
+// (a patch of more than lmax vertices: the vertices only)
+void build_patch(const Csr &M, const std::vector<int32_t> &owned, int s, int lmax, std::vector<int32_t> &dist,
                  std::vector<int32_t> &loc, Patch &P)
 {
     P.vert.clear();
@@ -79,6 +81,10 @@ void build_patch(const Csr &M, const std::vector<int32_t> &owned, int s, std::ve
         front = end;
     }
     const int32_t L = (int32_t)P.vert.size();
+    if (L > lmax) {
+        for (int32_t v : P.vert) dist[v] = -1;
+        return;
+    }
     for (int32_t l = 0; l < L; ++l) loc[P.vert[l]] = l;
     P.cnt.assign(s + 1, 0);
     for (int32_t l = 0; l < L; ++l) P.cnt[dist[P.vert[l]]]++;
@@ -111,11 +117,21 @@ void build_patch(const Csr &M, const std::vector<int32_t> &owned, int s, std::ve
 bem_status cheb_tables(const Csr M[2], int s, ChebTables &T)
 {
     T.s = s;
-    // owned range per patch: halved until the largest patch fits the kernel's register and LDS budget
+    // Rows are the same in every patch, so their width is looked at first.
+    for (int m = 0; m < 2; ++m)
+        for (int64_t v = 0; v < M[m].nrows; ++v)
+            if (M[m].ptr[v + 1] - M[m].ptr[v] > CHEB_WMAX)
+                return set_error(BEM_E_MESH, "inverse-mass rows wider than the kernel's limit "
+                                             "(a vertex with more than 15 neighbours)");
+    // Owned vertices per patch: halved until the largest patch fits the kernel's register and LDS budget.  A patch
+    // that does not fit ends its try at once.  (Steps of an eighth find larger patches, 448 owned for 10,242 + 8,002
+    // vertices: 64 runs 436 -> 317 us per launch, but one run, whose launch takes as long as its largest patch, 18.3 ->
+    // 20.2 us.)
     for (int own = CHEB_OWN_MAX; own >= 32; own /= 2) {
+        std::atomic<bool> over{false};
         std::vector<Patch> patches;
         std::vector<int32_t> pm;
-        for (int m = 0; m < 2; ++m) {
+        for (int m = 0; m < 2 && !over; ++m) {
             const int32_t nv = (int32_t)M[m].nrows;
             const std::vector<std::vector<int32_t>> cl = clusters(M[m], own);
             const int32_t np = (int32_t)cl.size();
@@ -125,65 +141,58 @@ bem_status cheb_tables(const Csr M[2], int s, ChebTables &T)
             pm.insert(pm.end(), np, m);
             parallel_for(np, 1, [&](int64_t a, int64_t b) {
                 std::vector<int32_t> dist(nv, -1), loc(nv, -1);
-                for (int64_t q = a; q < b; ++q) build_patch(M[m], cl[q], s, dist, loc, patches[first + q]);
+                for (int64_t q = a; q < b && !over; ++q) {
+                    build_patch(M[m], cl[q], s, CHEB_LMAX, dist, loc, patches[first + q]);
+                    if (patches[first + q].vert.size() > (size_t)CHEB_LMAX) over = true;
+                }
             });
         }
+        if (over) continue;
         int lmax = 0;
         for (const Patch &P : patches) lmax = std::max(lmax, (int)P.vert.size());
-        int wmax = 1;
-        for (const Patch &P : patches)
-            for (size_t l = 0; l + 1 < P.rptr.size(); ++l) wmax = std::max(wmax, P.rptr[l + 1] - P.rptr[l]);
-        if (wmax > CHEB_WMAX) return set_error(BEM_E_MESH, "inverse-mass rows wider than the kernel's limit "
-                                                           "(a vertex with more than 15 neighbours)");
-        if (lmax > CHEB_LMAX && own > 32) continue;
-        if (lmax > CHEB_LMAX) return set_error(BEM_E_MESH, "inverse-mass patches exceed the kernel's limit");
         T.own = own;
         T.lmax = lmax;
         T.pmesh.assign(pm.begin(), pm.end());
-        T.vbeg.assign(1, 0);
-        T.cnt.clear();
-        T.vert.clear();
-        T.dinv.clear();
-        T.rptr.clear();
-        T.col.clear();
-        T.val.clear();
-        for (const Patch &P : patches) {
-            const int32_t coff = (int32_t)T.col.size();
-            T.vert.insert(T.vert.end(), P.vert.begin(), P.vert.end());
-            T.dinv.insert(T.dinv.end(), P.dinv.begin(), P.dinv.end());
-            T.cnt.insert(T.cnt.end(), P.cnt.begin(), P.cnt.end());
-            for (size_t l = 0; l + 1 < P.rptr.size(); ++l) T.rptr.push_back(coff + P.rptr[l]);
-            T.col.insert(T.col.end(), P.col.begin(), P.col.end());
-            T.val.insert(T.val.end(), P.val.begin(), P.val.end());
-            T.vbeg.push_back((int32_t)T.vert.size());
-        }
-        T.rptr.push_back((int32_t)T.col.size());
-        // the same rows as ELL blocks per patch, [q][local row], for the kernel, which keeps a row's entries in
+        const int32_t np = (int32_t)patches.size();
+        T.vbeg.assign(np + 1, 0);
+        for (int32_t q = 0; q < np; ++q) T.vbeg[q + 1] = T.vbeg[q] + (int32_t)patches[q].vert.size();
+        T.cnt.resize((size_t)np * (s + 1));
+        T.vert.resize(T.vbeg[np]);
+        T.dinv.resize(T.vbeg[np]);
+        // the rows as ELL blocks per patch, [q][local row], for the kernel, which keeps a row's entries in
         // registers for all steps of a launch: w columns beside the diagonal, padded with zero entries on the
         // row's own vertex, and w + 1 values, the diagonal first
         int w = 1;
-        for (size_t l = 0; l + 1 < T.rptr.size(); ++l) w = std::max(w, T.rptr[l + 1] - T.rptr[l] - 1);
+        for (int m = 0; m < 2; ++m)
+            for (int64_t v = 0; v < M[m].nrows; ++v) w = std::max(w, M[m].ptr[v + 1] - M[m].ptr[v] - 1);
         T.ell_w = w;
-        T.ecol.assign((size_t)w * T.vert.size(), 0);
-        T.eval.assign((size_t)(w + 1) * T.vert.size(), 0.0);
-        for (size_t q = 0; q + 1 < T.vbeg.size(); ++q) {
-            const int32_t vb = T.vbeg[q], L = T.vbeg[q + 1] - vb;
-            uint16_t *ec = T.ecol.data() + (size_t)w * vb;
-            double *ev = T.eval.data() + (size_t)(w + 1) * vb;
-            for (int32_t l = 0; l < L; ++l) {
-                int e = 0;
-                for (int32_t k = T.rptr[vb + l]; k < T.rptr[vb + l + 1]; ++k) {
-                    if (T.col[k] == l) {
-                        ev[l] += T.val[k];
-                        continue;
+        T.ecol.resize((size_t)w * T.vert.size());
+        T.eval.resize((size_t)(w + 1) * T.vert.size());
+        parallel_for(np, 1, [&](int64_t q0, int64_t q1) {
+            for (int64_t q = q0; q < q1; ++q) {
+                const Patch &P = patches[q];
+                const int32_t vb = T.vbeg[q], L = (int32_t)P.vert.size();
+                std::copy(P.cnt.begin(), P.cnt.end(), T.cnt.begin() + q * (s + 1));
+                std::copy(P.vert.begin(), P.vert.end(), T.vert.begin() + vb);
+                std::copy(P.dinv.begin(), P.dinv.end(), T.dinv.begin() + vb);
+                uint16_t *ec = T.ecol.data() + (size_t)w * vb;
+                double *ev = T.eval.data() + (size_t)(w + 1) * vb;
+                std::fill(ev, ev + (size_t)(w + 1) * L, 0.0);
+                for (int32_t l = 0; l < L; ++l) {
+                    int e = 0;
+                    for (int32_t k = P.rptr[l]; k < P.rptr[l + 1]; ++k) {
+                        if (P.col[k] == l) {
+                            ev[l] += P.val[k];
+                            continue;
+                        }
+                        ec[(size_t)e * L + l] = (uint16_t)P.col[k];
+                        ev[(size_t)(e + 1) * L + l] = P.val[k];
+                        ++e;
                     }
-                    ec[(size_t)e * L + l] = (uint16_t)T.col[k];
-                    ev[(size_t)(e + 1) * L + l] = T.val[k];
-                    ++e;
+                    for (; e < w; ++e) ec[(size_t)e * L + l] = (uint16_t)l;
                 }
-                for (; e < w; ++e) ec[(size_t)e * L + l] = (uint16_t)l;
             }
-        }
+        });
         return BEM_OK;
     }
     return set_error(BEM_E_MESH, "inverse-mass patches exceed the kernel's limit");
