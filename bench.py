@@ -82,12 +82,12 @@ REG_REGIONS = {"source": "paper_2206_00708_amd/csrc/assemble.hip",
                "regions": [("// ------------------------------------------------------------ regular pairs",
                             "// The contributions to dense entry (i, j) of the tiles of one strip")]}
 COUNTED_VALU = {
-    ("regular_tiles", "C3"): {"flops_fp64": 1001099715.0 * 64, "valu_insts": 770386934, "valu_busy": 0.740,
-                              "sincos_flop_share": 0.30, "isolated_launch_us": 1946.3,
-                              "sha1": "1f60ff30b3e47f7d35bdadfe06c9142e6514978f", **REG_REGIONS},
-    ("regular_tiles", "C2"): {"flops_fp64": 659035802.0 * 64, "valu_insts": 506753050, "valu_busy": 0.738,
-                              "sincos_flop_share": 0.30, "isolated_launch_us": 1338.5,
-                              "sha1": "1f60ff30b3e47f7d35bdadfe06c9142e6514978f", **REG_REGIONS},
+    ("regular_tiles", "C3"): {"flops_fp64": 1001099715.0 * 64, "valu_insts": 770386934, "valu_busy": 0.749,
+                              "sincos_flop_share": 0.30, "isolated_launch_us": 1899.0,
+                              "sha1": "6c3f9b259177bf0f68c0485ef68f9d45d0c4fbb0", **REG_REGIONS},
+    ("regular_tiles", "C2"): {"flops_fp64": 659035802.0 * 64, "valu_insts": 506753050, "valu_busy": 0.750,
+                              "sincos_flop_share": 0.30, "isolated_launch_us": 1287.5,
+                              "sha1": "6c3f9b259177bf0f68c0485ef68f9d45d0c4fbb0", **REG_REGIONS},
 }
 
 
